@@ -328,14 +328,14 @@ int32_t pisa_forward(const pisa_shape* shape, const void* q, const void* k, cons
   const hipStream_t st = (hipStream_t)stream;
 
   // bf16: the statistics launches also write what the attention kernel's pre-pass would (the
-  // centroid tiles from the statistics kernel, the packed hsum from the reduction), and on short
-  // sequences the reduction rides in the selection's single launch: three launches in all.
+  // centroid tiles from the statistics kernel, the packed hsum from the reduction).  On short sequences
+  // of either type the reduction rides in the selection's single launch: three launches in all.
   StatsExtras extra;
   const bool fused = dm.dtype == PISA_BF16;
   if (fused) {
     attention_workspace_carve(dm, ws + c.attn, &extra.kcen, &extra.vbar, &extra.hpack);
-    extra.defer_reduce = k_top > 0 && select_fuses_reduce(dm);
   }
+  extra.defer_reduce = k_top > 0 && select_fuses_reduce(dm);
   hipError_t e = launch_block_stats(dm, q, k, v, qbar, kbar, vsum, hsum, qbar64, kbar64, partial, extra, st);
   if (e != hipSuccess) return hip_fail("pisa_forward (statistics)", e);
   if (k_top > 0) {
