@@ -33,3 +33,48 @@ def test_fp32_all_blocks_selected_is_bitwise_dense(lib, L, H):
     res = lib.forward_in_steps(q, k, v, w.block, 0.0, want_lse=True)
     dense, lse = lib.dense_attention(q, k, v, w.block, want_lse=True)
     assert torch.equal(res["out"], dense) and torch.equal(res["lse"], lse)
+
+
+# Spectral norm of the block heterogeneity: matrices whose Krylov space ends early, and clustered singular values
+@pytest.mark.parametrize("d,dtype", [(128, "bf16"), (64, "bf16"), (128, "fp32"), (64, "fp32")])
+@pytest.mark.parametrize("B", [64, 128])
+def test_spectral_heterogeneity_of_special_blocks(lib, d, dtype, B):
+    """Per key block j a centred H_j of known structure, H_bar included by the reference (numpy SVD in fp64): random
+    rows, 1 or 2 or 5 distinct tokens (rank 0, 1, 4), pairs of tokens with equal weight in orthogonal channels (repeated
+    singular values), a ragged last block of 3 tokens.  1e-9 of the largest norm is what the fp64 products and a Ritz
+    value with a 1e-7 residual leave room for (its error is quadratic in the residual)."""
+    import numpy as np
+    g = torch.Generator().manual_seed(d + B)
+    n, rows = 9, []
+    for j in range(n):
+        m = 3 if j == n - 1 else B
+        k, v = torch.randn(m, d, generator=g), torch.randn(m, d, generator=g)
+        if j in (1, 2, 3):                       # few distinct tokens
+            pick = torch.arange(m) % (1, 2, 5)[j - 1]
+            k, v = k[pick], v[pick]
+        if j == 4:                               # +- unit vectors: every singular value of sum k^T v equal
+            k = torch.eye(d)[torch.arange(m) // 2 % d] * (1.0 - 2.0 * (torch.arange(m) % 2))[:, None]
+            v = k.clone()
+        rows.append((k, v))
+    k, v = (torch.cat([r[i] for r in rows])[None, None] for i in range(2))
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    k, v = k.to(dt).to(DEV), v.to(dt).to(DEV)
+    shape = lib.make_shape(k, B)
+    st = lib.block_stats(k, k, v, B)
+    for norm, ord_ in ((lib.PISA_NORM_SPECTRAL, 2), (lib.PISA_NORM_FROBENIUS, "fro")):
+        log_m = lib.block_heterogeneity(shape, k, v, st["kbar64"], norm, 1e-6)[0, 0].cpu().numpy()
+        K, V = k[0, 0].double().cpu().numpy(), v[0, 0].double().cpu().numpy()
+        H = [(K[j * B:(j + 1) * B] - K[j * B:(j + 1) * B].mean(0)).T @ V[j * B:(j + 1) * B] for j in range(n)]
+        bar = sum(H) / n
+        M = np.array([np.linalg.norm(h - bar, ord_) for h in H])
+        assert np.abs(np.exp(log_m) - 1e-6 - M).max() <= 1e-9 * M.max(), norm
+
+
+def test_spectral_heterogeneity_of_identical_blocks(lib):
+    """All blocks alike: H_j - H_bar is rounding only, log(M + eps) is log(eps) to the last digits."""
+    g = torch.Generator().manual_seed(5)
+    k, v = (torch.randn(64, 128, generator=g).repeat(4, 1)[None, None].bfloat16().to(DEV) for _ in range(2))
+    st = lib.block_stats(k, k, v, 64)
+    log_m = lib.block_heterogeneity(lib.make_shape(k, 64), k, v, st["kbar64"], lib.PISA_NORM_SPECTRAL, 1e-6)
+    # |H_j| is about 100; its fp64 rounding, times 128 channels, stays below 1e-11
+    assert float((log_m.exp() - 1e-6).abs().max()) < 1e-11
