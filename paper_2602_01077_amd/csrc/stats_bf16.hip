@@ -1,16 +1,16 @@
 // pisa_block_stats for bf16 inputs, head_dim 128 or 64, block 64 or 128: one streaming pass
 // (Alg. 1, "Prepare" step).  Written out for head_dim 128; the differences at 64 are noted where they occur.
 //
-// Grid (n_chunks, batch*heads); a workgroup of 4 waves walks `chunk_blocks` consecutive
+// Grid (n_chunks, batch*heads); a workgroup of 8 waves walks `chunk_blocks` consecutive
 // blocks of one head.  Per 64-token (sub-)block:
-//   * wave w loads rows 16w..16w+15 of the Q, K and V tiles, one 4-byte channel pair per
+//   * wave w loads rows 8w..8w+7 of the Q, K and V tiles, one 4-byte channel pair per
 //     lane (a wave-load is one 256-byte row), one sub-block ahead of their use, and adds
 //     them in fp64 (exact for bf16 data);
-//     the four waves' partial column sums meet in LDS and are added in wave order;
+//     the waves' partial column sums meet in LDS and are added in wave order;
 //   * K is centred on the block mean in registers, split into bf16 hi + lo parts and
 //     written to LDS together with V (rows swizzled for conflict-free transposed reads);
-//   * H += Kc^T V on the matrix cores: wave w owns the 32 key channels 32w..32w+31 and all
-//     128 value channels (four 32x32 accumulators); both operands are contracted over
+//   * H += Kc^T V on the matrix cores: wave w owns 32 key channels and 64 value
+//     channels (two 32x32 accumulators); both operands are contracted over
 //     tokens, so both come from ds_read_b64_tr_b16.
 // The partial H of the chunk goes to scratch; partials are added in chunk order by the
 // caller's reduction kernel, so hsum is run-to-run identical.
@@ -70,16 +70,25 @@ __device__ inline bf16x8 read_operand(LDS_PTR(const unsigned char) tile, int lan
 // block's H_j follows from  sum_n (k_n - c_s)^T v_n = sum_n (k_n - kbar_j)^T v_n + (kbar_j - c_s)^T Vhat_s :
 //   H_j = sum_s [ A_s + (c_s - kbar_j)^T Vhat_s ],
 // a small rank-one correction per sub-block (c_s is close to kbar_j, so nothing cancels).
-// Head_dim 64: a 256-byte wave-load is two rows (lane = row parity x channel pair), a lane
-// holds 8 rows per tensor instead of 16, the two row parities are added with one lane
+// Head_dim 64: four waves, a 256-byte wave-load is two rows (lane = row parity x channel pair), a
+// lane holds 8 rows per tensor, the two row parities are added with one lane
 // exchange, and the 64 x 64 matrix H is four 32 x 32 tiles, one per wave.
 //
 // HETERO: the same walk used for the covariance-aware score instead of the statistics: every
 // block's H_j is rebuilt exactly as above (same centring, same hi/lo split, same products, so
 // the same bits that went into hsum), kept per block instead of summed over the chunk, and
 // reduced to log(||H_j - hsum / N||_F + eps); nothing else is written and Q is not read.
+//
+// Waves per workgroup.  The launch is bound by memory (input rows, and the partial H it writes), but
+// with four waves at two workgroups per CU a SIMD had two waves for a chain of three barriers, 190 fp64
+// instructions and 32 MFMAs per 64 rows, and 39 % of their time went into waiting.  At head_dim 128 eight
+// waves halve the chain (2 heads of 1 000 tokens 9.2 -> 7.3 us, 24 heads of 4 608 31.3 -> 28.8 us,
+// 40 heads of 75 600 598 -> 571 us = 4.1 TB/s); at 64 a wave has half the rows and an eighth of the MFMAs,
+// and there are only four 32 x 32 tiles of H to hand out: four waves.
+constexpr int stats_waves(int d) { return d == 128 ? 8 : 4; }
+
 template <int D, int TPB, bool HETERO>
-__global__ __launch_bounds__(256, 2) void stats_bf16_kernel(
+__global__ __launch_bounds__(64 * stats_waves(D), D == 128 ? 4 : 2) void stats_bf16_kernel(
     const unsigned int* __restrict__ q, const unsigned int* __restrict__ k, const unsigned int* __restrict__ v,
     float* __restrict__ qbar, float* __restrict__ kbar, float* __restrict__ vsum,
     double* __restrict__ qbar64, double* __restrict__ kbar64, float* __restrict__ partial_h,
@@ -90,18 +99,20 @@ __global__ __launch_bounds__(256, 2) void stats_bf16_kernel(
   constexpr int TILEB = kTile * 2 * D;
   constexpr int LPR = D / 2;            // lanes per row (one channel pair each)
   constexpr int RPW = 64 / LPR;         // rows per wave-load
-  constexpr int NR = 16 / RPW;          // loads per lane and tensor
-  constexpr int NB = D / 32 / (D == 128 ? 1 : 2);   // value tiles per wave: 4, or 1
+  constexpr int NW = stats_waves(D);
+  constexpr int RW = kTile / NW;        // rows per wave
+  constexpr int NR = RW / RPW;          // loads per lane and tensor
+  constexpr int NB = D / 32 / 2;        // value tiles per wave: 2, or 1
   __shared__ __attribute__((aligned(1024))) unsigned char khi_s[TILEB];
   __shared__ __attribute__((aligned(1024))) unsigned char klo_s[TILEB];
   __shared__ __attribute__((aligned(1024))) unsigned char v_s[TILEB];
-  __shared__ __attribute__((aligned(16))) double red[3][4][D];
+  __shared__ __attribute__((aligned(16))) double red[3][NW][D];
   __shared__ double tot[3][D];          // block totals over the sub-blocks (q, k, v)
   __shared__ double csub[2][D];         // sub-block key means c_s
   __shared__ float vsub[2][D];          // sub-block value sums Vhat_s
   __shared__ float dks[2][D];           // c_s - kbar_j
   __shared__ float kmean_s[D];
-  __shared__ double hnorm_s[4];         // HETERO: per-wave sums of squares
+  __shared__ double hnorm_s[NW];         // HETERO: per-wave sums of squares
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: row addresses stay scalar
@@ -116,8 +127,9 @@ __global__ __launch_bounds__(256, 2) void stats_bf16_kernel(
   LDS_PTR(unsigned char) vt = (LDS_PTR(unsigned char))v_s;
   const int lam = lane & 31, h = lane >> 5;
   const int rp = lane / LPR, cp = lane % LPR;        // row parity inside a wave-load, channel pair
-  const int ktile = D == 128 ? wave : (wave & 1);    // this wave's 32 key channels of H
-  const int vtile0 = D == 128 ? 0 : (wave >> 1);     // its first 32-value-channel tile
+  const int ktile = wave & (D / 32 - 1);             // this wave's 32 key channels of H
+  const int vtile0 = NB * (wave / (D / 32));         // its first 32-value-channel tile
+  const int grp = tid / D, ch = tid % D;             // block sums: tensor (0 q, 1 k, 2 v; 3 idle) and channel
 
   f32x16 acc[NB];
 #pragma unroll
@@ -130,34 +142,28 @@ __global__ __launch_bounds__(256, 2) void stats_bf16_kernel(
   // Optional second form of the block outputs, for the attention kernel's centroid phase: the
   // key mean and the value mean of block j as bf16 rows of tiles [bh][npad][D] (the fp32
   // values just written, rounded to nearest even; rows N .. npad - 1 are zero).  Called by
-  // the threads tid < D.
-  auto centroid_rows = [&](int j, float kmean, float vs, int rows_in_block) {
-    if (!kcen) return;
-    const size_t o = (bh * (size_t)npad + j) * D + tid;
-    kcen[o] = (unsigned short)pack_bf16(kmean, 0.f);
-    vbar[o] = (unsigned short)pack_bf16(vs * (1.f / (float)rows_in_block), 0.f);
+  // the threads of the k group and of the v group, each for its own tensor.
+  auto centroid_row = [&](unsigned short* dst, int j, float mean) {
+    if (!dst) return;
+    dst[(bh * (size_t)npad + j) * D + ch] = (unsigned short)pack_bf16(mean, 0.f);
     if (j == N - 1)
-      for (int jj = N; jj < npad; ++jj) {
-        const size_t oz = (bh * (size_t)npad + jj) * D + tid;
-        kcen[oz] = 0;
-        vbar[oz] = 0;
-      }
+      for (int jj = N; jj < npad; ++jj) dst[(bh * (size_t)npad + jj) * D + ch] = 0;
   };
 
-  // This wave's 16 rows of one 64-token sub-block, one channel pair per lane.  Rows past the
+  // This wave's RW rows of one 64-token sub-block, one channel pair per lane.  Rows past the
   // end repeat the last valid row (the users mask them), so the loads carry no conditions.
   auto load_rows = [&](const unsigned int* src, int row0, int rows, unsigned int (&x)[NR]) {
     if (rows <= 0) return;
 #pragma unroll
     for (int i = 0; i < NR; ++i)
-      x[i] = src[(size_t)(row0 + min(16 * wave + RPW * i + rp, rows - 1)) * (D / 2) + cp];
+      x[i] = src[(size_t)(row0 + min(RW * wave + RPW * i + rp, rows - 1)) * (D / 2) + cp];
   };
 
   const int j_begin = chunk * chunk_blocks;
   const int j_end = min(N, j_begin + chunk_blocks);
   // The rows of sub-block t + 1 are requested while sub-block t is worked on (K and V at its
   // start into a second register set, Q into its own registers once its sums are taken), so a
-  // wave always has 8 to 12 KB of loads in flight.
+  // wave always has 4 to 6 KB of loads in flight (8 waves; twice that with four).
   unsigned int kx[NR] = {}, vx[NR] = {}, qx[NR] = {}, kn[NR] = {}, vn[NR] = {};
   if (j_begin < j_end) {
     const int rows = min(kTile, L - j_begin * B);
@@ -173,6 +179,11 @@ __global__ __launch_bounds__(256, 2) void stats_bf16_kernel(
       const int rows = min(kTile, L - row0);
       if (rows <= 0) break;                       // uniform: the block ends inside its first half
       n_sub = sub + 1;
+      // LDS addresses are made again per sub-block from this copy: hoisted, they cost more registers
+      // than eight waves a workgroup leave.
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      const int cpn = ln % LPR, rpn = ln / LPR;
       int next_row0, next_rows;
       {
         int nj = j, ns = sub + 1;
@@ -185,11 +196,11 @@ __global__ __launch_bounds__(256, 2) void stats_bf16_kernel(
         load_rows(kh, next_row0, next_rows, kn);
         load_rows(vh, next_row0, next_rows, vn);
       }
-      // ---- fp64 column sums of the 16 rows (absent rows are zeroed first) ----
+      // ---- fp64 column sums of the wave's rows (absent rows are zeroed first) ----
       double sq0 = 0, sq1 = 0, sk0 = 0, sk1 = 0, sv0 = 0, sv1 = 0;
 #pragma unroll
       for (int i = 0; i < NR; ++i) {
-        if (16 * wave + RPW * i + rp >= rows) {   // uniform at head_dim 128
+        if (RW * wave + RPW * i + rp >= rows) {   // uniform at head_dim 128
           qx[i] = kx[i] = vx[i] = 0u;
         }
         sq0 += (double)__uint_as_float(qx[i] << 16);
@@ -211,38 +222,40 @@ __global__ __launch_bounds__(256, 2) void stats_bf16_kernel(
       }
       if (!HETERO) load_rows(qh, next_row0, next_rows, qx);    // Q(t) is used up
       __syncthreads();
-      if (tid < D) {
-        const double sq = ((red[0][0][tid] + red[0][1][tid]) + red[0][2][tid]) + red[0][3][tid];
-        const double sk = ((red[1][0][tid] + red[1][1][tid]) + red[1][2][tid]) + red[1][3][tid];
-        const double sv = ((red[2][0][tid] + red[2][1][tid]) + red[2][2][tid]) + red[2][3][tid];
-        const double cm = sk / (double)rows;
+      if (grp < 3) {
+        double sum = red[grp][0][ch];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum += red[grp][w][ch];
+        const double mean = sum / (double)rows;
         if (TPB == 1) {
           if (!HETERO) {
-            const double qm = sq / (double)rows;
-            const size_t o = (bh * N + j) * D + tid;
-            qbar[o] = (float)qm;
-            kbar[o] = (float)cm;
-            vsum[o] = (float)sv;
-            if (qbar64) qbar64[o] = qm;
-            if (kbar64) kbar64[o] = cm;
-            centroid_rows(j, (float)cm, (float)sv, rows);
+            const size_t o = (bh * N + j) * D + ch;
+            if (grp == 0) {
+              qbar[o] = (float)mean;
+              if (qbar64) qbar64[o] = mean;
+            } else if (grp == 1) {
+              kbar[o] = (float)mean;
+              if (kbar64) kbar64[o] = mean;
+              centroid_row(kcen, j, (float)mean);
+            } else {
+              vsum[o] = (float)sum;
+              centroid_row(vbar, j, (float)sum * (1.f / (float)rows));
+            }
           }
         } else {
-          tot[0][tid] = sub == 0 ? sq : tot[0][tid] + sq;
-          tot[1][tid] = sub == 0 ? sk : tot[1][tid] + sk;
-          tot[2][tid] = sub == 0 ? sv : tot[2][tid] + sv;
-          csub[sub][tid] = cm;
-          vsub[sub][tid] = (float)sv;
+          tot[grp][ch] = sub == 0 ? sum : tot[grp][ch] + sum;
+          if (grp == 1) csub[sub][ch] = mean;
+          if (grp == 2) vsub[sub][ch] = (float)sum;
         }
-        kmean_s[tid] = (float)cm;
+        if (grp == 1) kmean_s[ch] = (float)mean;
       }
       __syncthreads();
       // ---- centre K on the sub-block mean, split hi/lo, stage with V ----
       {
-        const float m0 = kmean_s[2 * cp], m1 = kmean_s[2 * cp + 1];
+        const float m0 = kmean_s[2 * cpn], m1 = kmean_s[2 * cpn + 1];
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
-          const int n = 16 * wave + RPW * i + rp;
+          const int n = RW * wave + RPW * i + rpn;
           unsigned int hi = 0u, lo = 0u;
           if (n < rows) {
             const float c0 = __uint_as_float(kx[i] << 16) - m0;
@@ -250,7 +263,7 @@ __global__ __launch_bounds__(256, 2) void stats_bf16_kernel(
             hi = pack_bf16(c0, c1);
             lo = pack_bf16(c0 - __uint_as_float(hi << 16), c1 - __uint_as_float(hi & 0xffff0000u));
           }
-          const int a = swz_pair<D>(n, cp);
+          const int a = swz_pair<D>(n, cpn);
           *reinterpret_cast<LDS_PTR(unsigned int)>(khi + a) = hi;
           *reinterpret_cast<LDS_PTR(unsigned int)>(klo + a) = lo;
           *reinterpret_cast<LDS_PTR(unsigned int)>(vt + a) = vx[i];
@@ -260,11 +273,11 @@ __global__ __launch_bounds__(256, 2) void stats_bf16_kernel(
       // ---- H[32 ktile .. +32][this wave's value tiles] += Kc^T V over the 64 tokens ----
 #pragma unroll
       for (int step = 0; step < 4; ++step) {
-        const bf16x8 ahi = read_operand<D>(khi, lane, step, ktile);
-        const bf16x8 alo = read_operand<D>(klo, lane, step, ktile);
+        const bf16x8 ahi = read_operand<D>(khi, ln, step, ktile);
+        const bf16x8 alo = read_operand<D>(klo, ln, step, ktile);
 #pragma unroll
         for (int bt = 0; bt < NB; ++bt) {
-          const bf16x8 b = read_operand<D>(vt, lane, step, vtile0 + bt);
+          const bf16x8 b = read_operand<D>(vt, ln, step, vtile0 + bt);
           acc[bt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi, b, acc[bt], 0, 0, 0);
           acc[bt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo, b, acc[bt], 0, 0, 0);
         }
@@ -278,18 +291,24 @@ __global__ __launch_bounds__(256, 2) void stats_bf16_kernel(
     }
     if (TPB == 2) {
       // ---- block outputs from the sub-block totals, then the rank-one corrections ----
-      if (tid < D) {
-        const double qm = tot[0][tid] / (double)block_rows, km = tot[1][tid] / (double)block_rows;
+      if (grp < 3) {
+        const double sum = tot[grp][ch], mean = sum / (double)block_rows;
         if (!HETERO) {
-          const size_t o = (bh * N + j) * D + tid;
-          qbar[o] = (float)qm;
-          kbar[o] = (float)km;
-          vsum[o] = (float)tot[2][tid];
-          if (qbar64) qbar64[o] = qm;
-          if (kbar64) kbar64[o] = km;
-          centroid_rows(j, (float)km, (float)tot[2][tid], block_rows);
+          const size_t o = (bh * N + j) * D + ch;
+          if (grp == 0) {
+            qbar[o] = (float)mean;
+            if (qbar64) qbar64[o] = mean;
+          } else if (grp == 1) {
+            kbar[o] = (float)mean;
+            if (kbar64) kbar64[o] = mean;
+            centroid_row(kcen, j, (float)mean);
+          } else {
+            vsum[o] = (float)sum;
+            centroid_row(vbar, j, (float)sum * (1.f / (float)block_rows));
+          }
         }
-        for (int sub = 0; sub < n_sub; ++sub) dks[sub][tid] = (float)(csub[sub][tid] - km);
+        if (grp == 1)
+          for (int sub = 0; sub < n_sub; ++sub) dks[sub][ch] = (float)(csub[sub][ch] - mean);
       }
       __syncthreads();
       for (int sub = 0; sub < n_sub; ++sub) {
@@ -307,13 +326,14 @@ __global__ __launch_bounds__(256, 2) void stats_bf16_kernel(
       // acc holds H_j; this lane's elements sit at fixed positions of the matrix
       double ss = 0.0;
       const float* hp = hs_head;
-      asm volatile("" : "+s"(hp));    // keeps the 64 loads below inside the block loop (hoisted, they spill)
+      unsigned hoff = 4 * h * D + lam;
+      asm volatile("" : "+s"(hp), "+v"(hoff));    // keeps the loads below inside the block loop (hoisted, they spill)
 #pragma unroll
       for (int bt = 0; bt < NB; ++bt) {
         float hb[16];                 // the elements of hsum at this lane's accumulator positions (see the store below)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          hb[r] = hp[(size_t)(32 * ktile + (r / 4) * 8 + 4 * h + (r % 4)) * D + 32 * (vtile0 + bt) + lam];
+          hb[r] = (hp + (32 * ktile + (r / 4) * 8 + (r % 4)) * D + 32 * (vtile0 + bt))[hoff];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const double dlt = (double)fmaf(-hb[r], inv_n, acc[bt][r]);   // both terms carry fp32 rounding already
@@ -325,8 +345,12 @@ __global__ __launch_bounds__(256, 2) void stats_bf16_kernel(
       for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
       if (lane == 0) hnorm_s[wave] = ss;
       __syncthreads();
-      if (tid == 0)
-        log_m[bh * N + j] = log(sqrt(((hnorm_s[0] + hnorm_s[1]) + hnorm_s[2]) + hnorm_s[3]) + eps);
+      if (tid == 0) {
+        double sum = hnorm_s[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum += hnorm_s[w];
+        log_m[bh * N + j] = log(sqrt(sum) + eps);
+      }
       // hnorm_s is written again only after the next block's barriers
     }
   }
@@ -349,7 +373,7 @@ hipError_t launch_block_stats_bf16(const Dims& dm, const void* q, const void* k,
   const int npad = ((dm.N + kTile - 1) / kTile) * kTile;
   const dim3 grid(plan.n_chunks, dm.bh());
 #define PISA_STATS_BF16(DD, TPB)                                                                           \
-  hipLaunchKernelGGL((stats_bf16_kernel<DD, TPB, false>), grid, dim3(256), 0, stream, (const unsigned int*)q, \
+  hipLaunchKernelGGL((stats_bf16_kernel<DD, TPB, false>), grid, dim3(64 * stats_waves(DD)), 0, stream, (const unsigned int*)q, \
                      (const unsigned int*)k, (const unsigned int*)v, qbar, kbar, vsum, qbar64, kbar64,     \
                      partial_h, (unsigned short*)kcen, (unsigned short*)vbar, npad, dm.L, dm.N,                \
                      plan.chunk_blocks, plan.n_chunks, nullptr, 0.0, nullptr)
@@ -368,7 +392,7 @@ hipError_t launch_block_heterogeneity_fast(const Dims& dm, const void* k, const 
   const StatsPlan plan = stats_plan(dm);
   const dim3 grid(plan.n_chunks, dm.bh());
 #define PISA_HET_FAST(DD, TPB)                                                                              \
-  hipLaunchKernelGGL((stats_bf16_kernel<DD, TPB, true>), grid, dim3(256), 0, stream, nullptr,               \
+  hipLaunchKernelGGL((stats_bf16_kernel<DD, TPB, true>), grid, dim3(64 * stats_waves(DD)), 0, stream, nullptr,               \
                      (const unsigned int*)k, (const unsigned int*)v, nullptr, nullptr, nullptr, nullptr,    \
                      nullptr, nullptr, nullptr, nullptr, 0, dm.L, dm.N, plan.chunk_blocks, plan.n_chunks,   \
                      hsum, eps, log_m)
