@@ -670,10 +670,9 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
     LDS_PTR(unsigned int) w_s = (LDS_PTR(unsigned int))(lds);                       // [128] shared words
     LDS_PTR(unsigned int) w_a = w_s + MASK_WORDS;                                    // first block only
     LDS_PTR(unsigned int) w_b = w_a + MASK_WORDS;                                    // second block only
-    LDS_PTR(unsigned short) l_s = (LDS_PTR(unsigned short))(w_b + MASK_WORDS);       // [4096] compacted
-    LDS_PTR(unsigned short) l_a = l_s + kMaxBlocks;
+    LDS_PTR(unsigned short) l_a = (LDS_PTR(unsigned short))(w_b + MASK_WORDS);       // [4096] unshared tiles, compacted
     LDS_PTR(unsigned short) l_b = l_a + kMaxBlocks;
-    static_assert(3 * MASK_WORDS * 4 + 3 * kMaxBlocks * 2 <= 4 * Geo<64>::TILEB, "list scratch must fit the staging area");
+    static_assert(3 * MASK_WORDS * 4 + 2 * kMaxBlocks * 2 <= 4 * Geo<64>::TILEB, "list scratch must fit the staging area");
     if (wave == 0) {
       // lane l owns mask words 2l, 2l + 1: split them, count, exclusive scan over the lanes
       unsigned ws[2], wa[2], wb[2];
@@ -703,8 +702,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
         cab += __builtin_popcount(wa[u]) | (__builtin_popcount(wb[u]) << 16);
       }
       unsigned is = cs, iab = cab;                       // inclusive scans (counts <= 4096: 16-bit halves never carry)
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
+      for (int off = 1; 2 * off < nwords; off <<= 1) {   // lanes past the last word have nothing to add
         const unsigned ts = __shfl_up(is, off), tab = __shfl_up(iab, off);
         if (lane >= off) {
           is += ts;
@@ -718,22 +716,24 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
       pre_a[2 * lane + 1] = (unsigned short)((eab + cab0) & 0xffffu);
       pre_b[2 * lane] = (unsigned short)(eab >> 16);
       pre_b[2 * lane + 1] = (unsigned short)((eab + cab0) >> 16);
-      if (lane == 63) {
+      if (lane == (nwords - 1) / 2) {
         pre_s[MASK_WORDS] = (unsigned short)is;
         pre_a[MASK_WORDS] = (unsigned short)(iab & 0xffffu);
         pre_b[MASK_WORDS] = (unsigned short)(iab >> 16);
       }
-      // compaction: this lane's tiles, ascending, at their ranks
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int w = 2 * lane + u;
-        unsigned rs = u == 0 ? es : es + cs0;
-        unsigned ra = (u == 0 ? eab : eab + cab0) & 0xffffu;
-        unsigned rb = (u == 0 ? eab : eab + cab0) >> 16;
-        for (unsigned m = ws[u]; m; m &= m - 1u) l_s[rs++] = (unsigned short)(32 * w + __builtin_ctz(m));
-        for (unsigned m = wa[u]; m; m &= m - 1u) l_a[ra++] = (unsigned short)(32 * w + __builtin_ctz(m));
-        for (unsigned m = wb[u]; m; m &= m - 1u) l_b[rb++] = (unsigned short)(32 * w + __builtin_ctz(m));
-      }
+    }
+    __syncthreads();
+    // A thread per tile: the unshared ones are compacted by rank, a shared one goes straight to its place,
+    // behind the pairs that lie wholly below it.  (The lanes that own the mask words used to walk their bits one
+    // by one: 24 heads of 4 608 tokens 87.2 -> 85.0 us for the kernel.)
+    for (int t = tid; t < n_tiles; t += 256) {
+      const int w = t >> 5;
+      const unsigned bit = 1u << (t & 31), low = bit - 1u;
+      const unsigned ms = w_s[w], ma = w_a[w], mb = w_b[w];
+      const int na = pre_a[w] + __builtin_popcount(ma & low), nb = pre_b[w] + __builtin_popcount(mb & low);
+      if (ms & bit) trip_list[pre_s[w] + __builtin_popcount(ms & low) + 2 * min(na, nb)] = (unsigned short)t;
+      if (ma & bit) l_a[na] = (unsigned short)t;
+      if (mb & bit) l_b[nb] = (unsigned short)t;
     }
     __syncthreads();
     const int n_s = pre_s[MASK_WORDS], n_a = pre_a[MASK_WORDS], n_b = pre_b[MASK_WORDS];
@@ -744,13 +744,6 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
       const int below = pre_s[key >> 5] + __builtin_popcount(w_s[key >> 5] & ((1u << (key & 31)) - 1u));
       trip_list[2 * i + below] = (unsigned short)(ta | (1 << 13));
       trip_list[2 * i + below + 1] = (unsigned short)(tb | (1 << 13));
-    }
-    for (int m = tid; m < n_s; m += 256) {               // shared tile m sits behind the pairs that lie wholly below it
-      const int t = l_s[m];
-      const unsigned low = (1u << (t & 31)) - 1u;
-      const int na = pre_a[t >> 5] + __builtin_popcount(w_a[t >> 5] & low);
-      const int nb = pre_b[t >> 5] + __builtin_popcount(w_b[t >> 5] & low);
-      trip_list[m + 2 * min(na, nb)] = (unsigned short)t;
     }
     const int base = n_s + 2 * n_pairs;
     for (int i = n_pairs + tid; i < n_a; i += 256) trip_list[base + i - n_pairs] = (unsigned short)(l_a[i] | (2 << 13));
