@@ -56,21 +56,51 @@ static int32_t resolve(const pisa_shape* s, Dims* dm) {
   return PISA_OK;
 }
 
+// Up to this many blocks in all, the number of blocks the fullest compute unit gets decides.
+static bool few_blocks(const Dims& dm) { return (long long)dm.N * dm.bh() <= 4096; }
+
+static StatsPlan plan_of_chunk(const Dims& dm, int chunk_blocks) {
+  StatsPlan p;
+  p.chunk_blocks = chunk_blocks;
+  p.n_chunks = (dm.N + chunk_blocks - 1) / chunk_blocks;
+  return p;
+}
+
+StatsPlan matrix_bound_plan(const Dims& dm) {
+  // Kernels bound by the matrix instruction (fp32, fp64) gain nothing from a second workgroup on a
+  // compute unit: their time is the number of blocks the fullest of the 256 compute units works
+  // through, plus the partial sums, which cost about a quarter of a block each to write and read
+  // again.  fp32, 8 heads of 4 500 tokens: 288 workgroups of two blocks (four on the fullest unit)
+  // 33.0 us, 192 of three 25.7 us.  fp64 sums of 24 heads of 4 608: 432 workgroups of four blocks or
+  // 216 of eight, eight on the fullest unit either way, 84 us both; half the partial sums take their
+  // reduction from 10.0 to 5.9 us.
+  if (!few_blocks(dm)) return stats_plan(dm);
+  int best = 1;
+  double best_cost = 1e300;
+  for (int c = 1; c <= dm.N; ++c) {
+    const long long groups = (long long)dm.bh() * ((dm.N + c - 1) / c);
+    const double cost = (double)((groups + 255) / 256) * c + 0.25 * (double)groups / 256.0;
+    if (cost <= best_cost) {
+      best = c;
+      best_cost = cost;
+    }
+  }
+  return plan_of_chunk(dm, best);
+}
+
 StatsPlan stats_plan(const Dims& dm) {
+  if (dm.dtype == PISA_FP32 && few_blocks(dm)) return matrix_bound_plan(dm);
   // The streaming kernels keep two workgroups on each of the 256 compute units, and all
   // their workgroups take about the same time: the launch should be a whole number of rounds
   // of 512, never a few workgroups more.  Aim at two rounds (one when that still leaves a
   // workgroup only a handful of blocks, to halve the partial sums written and re-read).
   const int kSlots = 512;
   int target = 2 * kSlots;
-  if ((long long)dm.N * dm.bh() <= 8LL * kSlots) target = kSlots;
+  if (few_blocks(dm)) target = kSlots;
   int want = target / dm.bh();
   if (want < 1) want = 1;
   if (want > dm.N) want = dm.N;
-  StatsPlan p;
-  p.chunk_blocks = (dm.N + want - 1) / want;
-  p.n_chunks = (dm.N + p.chunk_blocks - 1) / p.chunk_blocks;
-  return p;
+  return plan_of_chunk(dm, (dm.N + want - 1) / want);
 }
 
 static size_t stats_workspace_bytes(const Dims& dm) {

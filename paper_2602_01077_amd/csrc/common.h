@@ -38,6 +38,7 @@ struct StatsPlan {
   int n_chunks;
 };
 StatsPlan stats_plan(const Dims& dm);
+StatsPlan matrix_bound_plan(const Dims& dm);
 
 // What the fused forward call asks of the statistics launches beyond the plain outputs (all
 // optional; bf16 only): the centroid tiles and the packed hsum in the form the attention kernel

@@ -628,14 +628,14 @@ __global__ __launch_bounds__(256, 2) void hetero_kernel(const T* __restrict__ k,
 }  // namespace
 
 size_t hetero_workspace_bytes(const Dims& dm) {
-  const StatsPlan plan = stats_plan(dm);
+  const StatsPlan plan = matrix_bound_plan(dm);
   return (size_t)dm.bh() * (plan.n_chunks + 1) * dm.d * dm.d * sizeof(double);
 }
 
 hipError_t launch_block_heterogeneity(const Dims& dm, const void* k, const void* v, const double* kbar64,
                                       const float* hsum, int spectral, int n_iter, double eps, double* log_m,
                                       double* workspace, hipStream_t stream) {
-  const StatsPlan plan = stats_plan(dm);
+  const StatsPlan plan = matrix_bound_plan(dm);
   const int dd = dm.d * dm.d;
   double* partial = workspace;
   double* hbar = workspace + (size_t)dm.bh() * plan.n_chunks * dd;

@@ -78,3 +78,33 @@ def test_spectral_heterogeneity_of_identical_blocks(lib):
     log_m = lib.block_heterogeneity(lib.make_shape(k, 64), k, v, st["kbar64"], lib.PISA_NORM_SPECTRAL, 1e-6)
     # |H_j| is about 100; its fp64 rounding, times 128 channels, stays below 1e-11
     assert float((log_m.exp() - 1e-6).abs().max()) < 1e-11
+
+
+def _centred_products(k, v, B):
+    """[N, d, d] fp64: sum over the tokens of each block of (k_n - kbar_j)^T v_n (one head)."""
+    k, v = k.double(), v.double()
+    return torch.stack([(kb - kb.mean(0)).T @ vb for kb, vb in zip(k.split(B), v.split(B))])
+
+
+# Partial sums over chunks of blocks: chunks of one and of three blocks with a short last one, more blocks in all
+# than the rule for few blocks covers, and the eight-wave bf16 kernel (64 rows, ragged, block 128 ending in its first half)
+@pytest.mark.parametrize("dtype,H,L,d,B", [
+    (torch.float32, 8, 64 * 70 + 20, 128, 64), (torch.float32, 12, 64 * 64, 64, 64),
+    (torch.float32, 65, 64 * 63 + 1, 64, 64), (torch.float32, 7, 128 * 31 + 70, 128, 128),
+    (torch.bfloat16, 1, 64, 128, 64), (torch.bfloat16, 24, 64 * 22 + 9, 128, 64), (torch.bfloat16, 3, 128 * 11 + 5, 128, 128),
+])
+def test_sums_over_chunks(lib, dtype, H, L, d, B):
+    g = torch.Generator().manual_seed(L)
+    q, k, v = (torch.randn(1, H, L, d, generator=g).to(dtype).to(DEV) for _ in range(3))
+    st = lib.block_stats(q, k, v, B)
+    log_m = lib.block_heterogeneity(lib.make_shape(k, B), k, v, st["kbar64"], lib.PISA_NORM_FROBENIUS, 0.0)
+    for h in sorted({0, H // 2, H - 1}):
+        ref = _centred_products(k[0, h], v[0, h], B)
+        # fp32 products and sums, or the bf16 hi + lo split of the centred keys (2^-17 of each product at most)
+        assert float((st["hsum"][0, h] - ref.sum(0)).norm() / ref.sum(0).norm()) < 2.0 ** -17
+        for name, x in (("qbar", q), ("kbar", k)):
+            means = torch.stack([b.double().mean(0) for b in x[0, h].split(B)])
+            assert float((st[name + "64"][0, h] - means).abs().max()) < 1e-12 and torch.equal(st[name][0, h], st[name + "64"][0, h].float())
+        norms = (ref - ref.mean(0)).flatten(1).norm(dim=1)
+        if ref.shape[0] > 1:
+            assert float((log_m[0, h].exp() - norms).abs().max() / norms.max()) < 1e-9
