@@ -38,6 +38,9 @@
 // themselves arrive in; vsum_j / B_j), written by a small pre-pass or, in the one-call entry
 // point, by the statistics kernels; Phase 3 multiplies by the pre-packed hi/lo split of hsum,
 // staged through LDS once per workgroup.
+//
+// Calls with few workgroups take attn_bf16_short_kernel (64 rows per workgroup, keys split over wave
+// pairs); the rule and both kernels' times stand at the launch.
 #include <mutex>
 #include <type_traits>
 
@@ -1015,6 +1018,341 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
   }
 }
 
+// ---------------------------------------------------------------------------------
+// Short calls: 64 query rows per workgroup, keys split over wave pairs
+// ---------------------------------------------------------------------------------
+// A call of a few heads of a few thousand tokens has fewer 128-row workgroups than the chip has CUs, and
+// its time is one workgroup's: a chain of tiles, each a load, a softmax and two products.  Here a workgroup has
+// half the rows and a wave half the keys: a tile takes half as long, a sparse workgroup walks its own index
+// row instead of the union of two, and twice as many CUs work.  The price is that every tile is loaded
+// for 64 rows instead of 128.  2 heads of 1 000 tokens, r = 0.8: one call 31.6 -> 24.7 us.
+// Wave w owns rows 32 (w >> 1) .. + 31 of the query tile and half e = w & 1 of the keys of every staged
+// tile; staging, operand layouts and the trip pipeline are the main kernel's.  The two partial results of
+// a row (each with a running maximum of its own) meet in LDS once, before Phase 3, and each wave of the
+// pair finishes half of the channels.  The tiles of one index row are walked straight from its bitmask.
+
+// 32 staged keys, start to finish, with the exact softmax step (ragged tile, centroid tiles); see absorb_tile.
+template <int D, bool TAIL, bool RAGGED, int KOFF, int VOFF>
+__device__ inline void absorb_rows(State<D>& st, const bf16x8 (&qreg)[D / 16], const LaneCtx& lc,
+                                   LDS_PTR(const float) bias, int nvalid, float c) {
+  f32x16 s;
+  bf16x8 pb[2];
+  qk_rows<D, KOFF, 0>(s, qreg, lc);
+  const int h = lc.h;
+  if (TAIL) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f32x4 b = *reinterpret_cast<LDS_PTR(const f32x4)>(bias + 8 * g + 4 * h);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[4 * g + i] = fmaf(s[4 * g + i], c, b[i]);
+    }
+  }
+  const float tmax = max_rows(s);
+  raise_max<D>(st, TAIL ? tmax : tmax * c);
+  const float nm = st.m == -INFINITY ? 0.f : -st.m;
+  float psum = 0.f;
+#pragma unroll
+  for (int step = 0; step < 2; ++step) {
+    u32x4 pw;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float x[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int r = 8 * step + 2 * i + u;
+        x[u] = __builtin_amdgcn_exp2f(TAIL ? s[r] + nm : fmaf(s[r], c, nm));
+        if (RAGGED && (r / 4) * 8 + 4 * h + (r % 4) >= nvalid) x[u] = 0.f;
+        psum += x[u];
+      }
+      pw[i] = pack_bf16(x[0], x[1]);
+    }
+    pb[step] = __builtin_bit_cast(bf16x8, pw);
+  }
+  st.l += psum;
+  if (TAIL) st.l_tail += psum;
+  pv_rows<D, VOFF, 0>(st, pb[0], pb[1], lc);
+}
+
+template <int D, bool DENSE, int TPB>
+__global__ __launch_bounds__(256, 2) void attn_bf16_short_kernel(PB p) {
+  constexpr int ROWB = Geo<D>::ROWB, TILEB = Geo<D>::TILEB, NKS = Geo<D>::NKS, NDT = Geo<D>::NDT;
+  constexpr int CPR = Geo<D>::CPR, RPL = Geo<D>::RPL, HDT = NDT / 2, HALFB = TILEB / 2;
+  constexpr int KST0 = 0, KST1 = TILEB, VST0 = 2 * TILEB, VST1 = 3 * TILEB;
+  __shared__ __attribute__((aligned(1024))) unsigned char stage[4 * TILEB];   // K0 | K1 | V0 | V1
+  __shared__ unsigned int chosen[MASK_WORDS];
+  __shared__ __attribute__((aligned(16))) float bias_s[2][kTile];             // [stage parity][centroid]
+  __shared__ float merge_s[4][3][32];                                         // [wave]: max, sum, tail sum
+
+  const int item = blockIdx.x;
+  if (item >= p.total) return;
+  const size_t bh = item / p.n_super;
+  const int qt = item % p.n_super;                   // 64-row query tile
+  const int blk = qt / TPB;                          // its block (PISA)
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lam = lane & 31, h = lane >> 5, e = wave & 1;
+  const int L = p.L, N = p.N;
+  const unsigned char* kg = reinterpret_cast<const unsigned char*>(p.k + bh * (size_t)L * D);
+  const unsigned char* vg = reinterpret_cast<const unsigned char*>(p.v + bh * (size_t)L * D);
+  const float c = p.scale * 1.44269504088896340736f;
+  LDS_PTR(unsigned char) lds = (LDS_PTR(unsigned char)) & stage[0];
+  const unsigned lds_addr = (unsigned)(unsigned long long)lds;
+
+  LaneCtx lc;
+  lc.h = h;
+  lc.wave = wave;
+  {
+    const int pos = lane % CPR;
+    lc.dma_r0 = RPL * Geo<D>::NLD * wave + lane / CPR;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = lc.dma_r0 + RPL * i;
+      const int in_piece = (lane / CPR) * ROWB;
+      lc.dma_k[i] = in_piece + ((pos ^ kswz<D>(r)) << 4);
+      lc.dma_v[i] = in_piece + (((((pos >> 1) ^ vswz<D>(r)) << 1) | (pos & 1)) << 4);
+    }
+    const int j16 = lane & 15, kq = 4 * h + (j16 >> 2), lhalf = (lane >> 4) & 1;
+    // this wave's 32 rows of a stage (32 is a multiple of both swizzles' periods)
+    lc.kbase = lds + (32 * e + lam) * ROWB + ((kswz<D>(lam) ^ h) << 4);
+    lc.vbase = lds + (32 * e + kq) * ROWB + 8 * (j16 & 3) + ((lhalf ^ vswz<D>(kq)) << 5);
+  }
+
+  const int32_t* row = DENSE ? nullptr : p.idx + (bh * N + blk) * (size_t)p.k_top;
+  int j_first = -1;
+  if (!DENSE && tid < p.k_top) j_first = row[tid];
+  const int q_row = qt * kTile + 32 * (wave >> 1) + lam;
+  bf16x8 qreg[NKS];
+  {
+    const __bf16* qg = p.q + bh * (size_t)L * D;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      u32x4 w = {0, 0, 0, 0};
+      if (q_row < L) w = *reinterpret_cast<const u32x4*>(qg + (size_t)q_row * D + 16 * ks + 8 * h);
+      qreg[ks] = __builtin_bit_cast(bf16x8, w);
+    }
+  }
+  State<D> st;
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt) st.ot[dt] = (f32x16){0};
+  st.m = -INFINITY;
+  st.l = 0.f;
+  st.l_tail = 0.f;
+
+  const int nwords = (N + 31) / 32;
+  if (!DENSE) {
+    for (int w = tid; w < MASK_WORDS; w += 256) chosen[w] = 0u;
+    __syncthreads();
+    int j = j_first;
+    for (int t = tid; t < p.k_top; t += 256) {
+      if (t != tid) j = row[t];
+      if ((unsigned)j < (unsigned)N) atomicOr(&chosen[j >> 5], 1u << (j & 31));   // entries outside [0, N) are ignored
+    }
+    __syncthreads();
+  }
+
+  // ---- Phase 1 ----
+  const int n_tiles = L / kTile;
+  int w_word = -1, pend = -1, dense_t = 0;
+  unsigned int w_bits = 0u;
+  auto next_tile = [&](int& off) -> bool {            // byte offset of the next full exact tile
+    int tile;
+    if (DENSE) {
+      tile = dense_t++;
+    } else if (pend >= 0) {
+      tile = pend;
+      pend = -1;
+    } else {
+      while (w_bits == 0u) {
+        if (++w_word >= nwords) return false;
+        w_bits = __builtin_amdgcn_readfirstlane(chosen[w_word]);
+      }
+      tile = TPB * (w_word * 32 + __builtin_ctz(w_bits));
+      w_bits &= w_bits - 1u;
+      if (TPB == 2 && tile + 1 < n_tiles) pend = tile + 1;
+    }
+    if (tile >= n_tiles) return false;                // only the ragged tile is left
+    off = tile * TILEB;
+    return true;
+  };
+  {
+    f32x16 sc;
+    int off0 = 0, off1 = 0, off2 = 0;
+    bool have0 = next_tile(off0), have1 = false, have2 = false;
+    if (have0) {
+      load_stage<D, true>(lc, kg, Trip{off0, off0 + HALFB}, lds_addr + KST0);
+      have1 = next_tile(off1);
+      wait_async_loads();
+      __syncthreads();
+      if (have1) load_stage<D, true>(lc, kg, Trip{off1, off1 + HALFB}, lds_addr + KST1);
+      load_stage<D, false>(lc, vg, Trip{off0, off0 + HALFB}, lds_addr + VST0);
+      qk_rows<D, KST0, 0>(sc, qreg, lc);
+    }
+    auto trip = [&](auto parity_tag) {
+      constexpr int P = decltype(parity_tag)::value;
+      constexpr int K_NEXT = P ? KST0 : KST1, K_FREE = P ? KST1 : KST0;
+      constexpr int V_CUR = P ? VST1 : VST0, V_FREE = P ? VST0 : VST1;
+      have2 = have1 && next_tile(off2);
+      wait_async_loads();
+      __syncthreads();
+      if (have2) load_stage<D, true>(lc, kg, Trip{off2, off2 + HALFB}, lds_addr + K_FREE);
+      if (have1) load_stage<D, false>(lc, vg, Trip{off1, off1 + HALFB}, lds_addr + V_FREE);
+      bf16x8 p0, p1;
+      float pa = 0.f, pc = 0.f;
+      exp_rows(sc, c, -st.m, p0, p1, pa, pc);
+      if (__any(!(pa + pc < kStaleLimit))) {           // first keys of this wave, or a maximum that ran away
+        raise_max<D>(st, max_rows(sc) * c);
+        pa = pc = 0.f;
+        exp_rows(sc, c, -st.m, p0, p1, pa, pc);
+      }
+      st.l += pa + pc;
+      pv_rows<D, V_CUR, 0>(st, p0, p1, lc);
+      if (have1) qk_rows<D, K_NEXT, 0>(sc, qreg, lc);
+      off0 = off1;
+      have0 = have1;
+      off1 = off2;
+      have1 = have2;
+    };
+    while (have0) {
+      trip(std::integral_constant<int, 0>{});
+      if (!have0) break;
+      trip(std::integral_constant<int, 1>{});
+    }
+  }
+
+  // ---- ragged last tile ----
+  if (L % kTile != 0) {
+    const int jb = n_tiles / TPB;
+    if (DENSE || ((chosen[jb >> 5] >> (jb & 31)) & 1u)) {            // uniform over the workgroup
+      __syncthreads();
+      load_tile_async<D, true>(lc, kg + (size_t)n_tiles * TILEB, L - n_tiles * kTile, lds_addr + KST0);
+      load_tile_async<D, false>(lc, vg + (size_t)n_tiles * TILEB, L - n_tiles * kTile, lds_addr + VST0);
+      wait_async_loads();
+      __syncthreads();
+      absorb_rows<D, false, true, KST0, VST0>(st, qreg, lc, nullptr, L - n_tiles * kTile - 32 * e, c);
+    }
+  }
+
+  // ---- Phase 2: centroid tiles ----
+  const bool approx = !DENSE && p.k_top < N && p.kcen != nullptr;
+  if (approx) {
+    const unsigned char* kcg = reinterpret_cast<const unsigned char*>(p.kcen + bh * (size_t)p.npad * D);
+    const unsigned char* vbg = reinterpret_cast<const unsigned char*>(p.vbar + bh * (size_t)p.npad * D);
+    const float log2_full = __builtin_amdgcn_logf((float)p.B);
+    const float log2_last = __builtin_amdgcn_logf((float)(L - (N - 1) * p.B));
+    auto fetch = [&](int g0, auto parity_tag) {
+      constexpr int P = decltype(parity_tag)::value;
+      load_tile_async<D, true>(lc, kcg + (size_t)g0 * ROWB, kTile, lds_addr + (P ? KST1 : KST0));
+      load_tile_async<D, false>(lc, vbg + (size_t)g0 * ROWB, kTile, lds_addr + (P ? VST1 : VST0));
+      if (tid < kTile) {
+        const int j = g0 + tid;
+        const bool masked = j >= N || ((chosen[(j >> 5) & (MASK_WORDS - 1)] >> (j & 31)) & 1u);
+        bias_s[P][tid] = masked ? -INFINITY : (j == N - 1 ? log2_last : log2_full);
+      }
+    };
+    auto absorb = [&](int g0, auto parity_tag) {
+      constexpr int P = decltype(parity_tag)::value;
+      wait_async_loads();
+      __syncthreads();
+      if (g0 + kTile < N) fetch(g0 + kTile, std::integral_constant<int, 1 - P>{});
+      absorb_rows<D, true, false, (P ? KST1 : KST0), (P ? VST1 : VST0)>(
+          st, qreg, lc, (LDS_PTR(const float)) & bias_s[P][32 * e], kTile, c);
+    };
+    __syncthreads();
+    fetch(0, std::integral_constant<int, 0>{});
+    for (int g0 = 0; g0 < N; g0 += 2 * kTile) {
+      absorb(g0, std::integral_constant<int, 0>{});
+      if (g0 + kTile < N) absorb(g0 + kTile, std::integral_constant<int, 1>{});
+    }
+  }
+
+  // ---- merge: lane halves, then the two waves of a pair; a wave keeps channel tiles e HDT .. + HDT - 1 ----
+  {
+    st.l += __shfl_xor(st.l, 32);
+    st.l_tail += __shfl_xor(st.l_tail, 32);
+    LDS_PTR(unsigned char) mine = lds + wave * (HDT * 4096) + lane * 16;
+    LDS_PTR(const unsigned char) theirs = lds + (wave ^ 1) * (HDT * 4096) + lane * 16;
+    __syncthreads();                            // the stages are free
+#pragma unroll
+    for (int dt = 0; dt < HDT; ++dt) {
+      const f32x16 give = e ? st.ot[dt] : st.ot[HDT + dt];
+      if (e) st.ot[dt] = st.ot[HDT + dt];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 w = {give[4 * g], give[4 * g + 1], give[4 * g + 2], give[4 * g + 3]};
+        *reinterpret_cast<LDS_PTR(f32x4)>(mine + (dt * 4 + g) * 1024) = w;
+      }
+    }
+    if (h == 0) {
+      merge_s[wave][0][lam] = st.m;
+      merge_s[wave][1][lam] = st.l;
+      merge_s[wave][2][lam] = st.l_tail;
+    }
+    __syncthreads();
+    const float om = merge_s[wave ^ 1][0][lam];
+    const float m = fmaxf(st.m, om);
+    // a wave that met no key at all (maximum still -inf) holds zeros
+    const float f0 = st.m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(st.m - m);
+    const float f1 = om == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(om - m);
+    st.m = m;
+    st.l = st.l * f0 + merge_s[wave ^ 1][1][lam] * f1;
+    st.l_tail = st.l_tail * f0 + merge_s[wave ^ 1][2][lam] * f1;
+#pragma unroll
+    for (int dt = 0; dt < HDT; ++dt)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 w = *reinterpret_cast<LDS_PTR(const f32x4)>(theirs + (dt * 4 + g) * 1024);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) st.ot[dt][4 * g + i] = fmaf(st.ot[dt][4 * g + i], f0, w[i] * f1);
+      }
+  }
+
+  // ---- Phase 3, as in the main kernel, for this wave's channels ----
+  if (approx && p.first_order) {
+    const unsigned char* hp = reinterpret_cast<const unsigned char*>(p.hpack + bh * (size_t)(2 * D * D));
+    constexpr int HP_LOADS = 4 * D * D / (4 * 1024);
+    __syncthreads();                            // the merge has been read
+#pragma unroll
+    for (int i = 0; i < HP_LOADS; ++i) {
+      const unsigned off = (unsigned)__builtin_amdgcn_readfirstlane((int)((lc.wave * HP_LOADS + i) * 1024));
+      set_dma_lds_base(lds_addr + off);
+      dma_1kb<0>((unsigned)(lane * 16), hp + off);
+    }
+    wait_async_loads();
+    __syncthreads();
+    LDS_PTR(const unsigned char) hl = lds + lane * 16 + e * HDT * 1024;
+    f32x16 rt[HDT];
+#pragma unroll
+    for (int dt = 0; dt < HDT; ++dt) rt[dt] = (f32x16){0};
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+      for (int dt = 0; dt < HDT; ++dt) {
+        const bf16x8 ahi = *reinterpret_cast<LDS_PTR(const bf16x8)>(hl + (ks * NDT + dt) * 1024);
+        const bf16x8 alo = *reinterpret_cast<LDS_PTR(const bf16x8)>(hl + 2 * D * D + (ks * NDT + dt) * 1024);
+        rt[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi, qreg[ks], rt[dt], 0, 0, 0);
+        rt[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo, qreg[ks], rt[dt], 0, 0, 0);
+      }
+    const float w = st.l_tail / (float)L * p.scale;
+#pragma unroll
+    for (int dt = 0; dt < HDT; ++dt) st.ot[dt] += rt[dt] * w;
+  }
+
+  if (q_row < L) {
+    const float inv_l = 1.f / st.l;
+    __bf16* orow = p.out + (bh * (size_t)L + q_row) * D + 32 * HDT * e;
+#pragma unroll
+    for (int dt = 0; dt < HDT; ++dt)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const u32x2 w = {pack_bf16(st.ot[dt][4 * g] * inv_l, st.ot[dt][4 * g + 1] * inv_l),
+                         pack_bf16(st.ot[dt][4 * g + 2] * inv_l, st.ot[dt][4 * g + 3] * inv_l)};
+        *reinterpret_cast<u32x2*>(orow + 32 * dt + 8 * g + 4 * h) = w;
+      }
+    if (p.lse && h == 0 && e == 0)
+      p.lse[bh * (size_t)L + q_row] = (st.m + __builtin_amdgcn_logf(st.l)) * 0.69314718055994530942f;
+  }
+}
+
 }  // namespace
 
 // The kernels that walk two tiles per block without a trip list: dense_attention and block 128.
@@ -1059,7 +1397,24 @@ static hipError_t launch_attention_bf16_d(const Dims& dm, const AttnArgs& a, hip
   p.scale = dm.scale;
   p.first_order = a.hsum != nullptr;
 
+  // Which kernel: by the number of 128-row workgroups the main kernel would have on the 256 CUs (us per
+  // call, main / short kernel, head_dim 128 unless noted).  Dense: 16 workgroups 22.4 / 15.4, 144 79.2 / 72.2,
+  // 180 85.6 / 83.6, 192 39.0 / 40.2, 256 43.6 / 45.3, 432 131 / 158.  Block 128: 128 workgroups
+  // 40.8 / 35.8, 160 41.9 / 41.2, 192 42.6 / 42.3, 256 44.2 / 47.1.  Block 64, where the main kernel walks the
+  // union of two index rows: 16 31.6 / 24.7, 96 37.5 / 29.3, 256 (2 heads of 16 384) 133.9 / 94.8, 288
+  // 66.7 / 65.8, 320 57.3 / 56.9, 384 64.2 / 64.8, 432 71.4 / 75.9 (head_dim 64 48.7 / 46.1).  With every
+  // block selected a call takes the line of the dense one, whose bits it has to give.
+  constexpr int kShortDense = 176, kShortBlock64 = 320;
+  const bool short_call = p.total <= (a.dense || a.k_top == dm.N || dm.B != kTile ? kShortDense : kShortBlock64);
+  if (short_call) {
+    p.n_super = (dm.L + kTile - 1) / kTile;
+    p.total = p.n_super * dm.bh();
+  }
   const int grid = ((p.total + 63) / 64) * 64;
+  if (a.dense && short_call) {
+    hipLaunchKernelGGL((attn_bf16_short_kernel<D, true, 1>), dim3(p.total), dim3(256), 0, stream, p);
+    return hipGetLastError();
+  }
   if (a.dense) return launch_attention_two_tiles<D>(p, true, grid, stream);
   if (a.k_top < dm.N && a.kbar) {
     void *kcen_v, *vbar_v, *hpack_v;                      // kcen | vbar | hpack
@@ -1076,6 +1431,11 @@ static hipError_t launch_attention_bf16_d(const Dims& dm, const AttnArgs& a, hip
     p.kcen = kcen;
     p.vbar = vbar;
     p.hpack = hpack;
+  }
+  if (short_call) {
+    if (dm.B == kTile) hipLaunchKernelGGL((attn_bf16_short_kernel<D, false, 1>), dim3(p.total), dim3(256), 0, stream, p);
+    else hipLaunchKernelGGL((attn_bf16_short_kernel<D, false, 2>), dim3(p.total), dim3(256), 0, stream, p);
+    return hipGetLastError();
   }
   if (pairing_pays(dm, a.k_top) && a.workspace) {
     // the pairing scratch follows the pre-pass results (whether or not those are in use)

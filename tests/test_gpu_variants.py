@@ -108,3 +108,32 @@ def test_sums_over_chunks(lib, dtype, H, L, d, B):
         norms = (ref - ref.mean(0)).flatten(1).norm(dim=1)
         if ref.shape[0] > 1:
             assert float((log_m[0, h].exp() - norms).abs().max() / norms.max()) < 1e-9
+
+
+# bf16 attention: the kernel with 64 rows per workgroup (few workgroups) on both sides of its lines: 176 workgroups of
+# 128 rows for block 128, 320 for block 64; ragged tiles of 1, 9, 33 and 63 rows, one and two centroid tiles, no full
+# tile, no selected block
+@pytest.mark.parametrize("L,H,d,B,r,check", [
+    (40, 2, 128, 64, 0.0, [0, 1]), (65, 1, 64, 64, 0.5, [0]), (1000, 2, 128, 64, 0.8, [0, 1]),
+    (64 * 3 + 33, 3, 128, 128, 0.5, [0, 2]), (64 * 5 + 63, 2, 64, 128, 1.0, [0, 1]), (64 * 9 + 9, 2, 128, 64, 1.0, [1]),
+    (64 * 70 + 1, 2, 128, 64, 0.9, [0, 1]), (64 * 129, 1, 64, 64, 0.95, [0]),
+    (1400, 16, 128, 128, 0.7, [0, 15]), (1409, 16, 128, 128, 0.7, [0, 15]),
+    (2048, 20, 128, 64, 0.85, [0, 19]), (2049, 20, 128, 64, 0.85, [0, 19]),
+])
+def test_bf16_short_calls(lib, L, H, d, B, r, check):
+    w = WORKLOADS["flux"].with_(name=f"short-{L}-{H}", heads=H, seq_len=L, head_dim=d, block=B, sparsity=r, grid=None,
+                                seed=L + H)
+    n = -(-L // B)
+    run_full_case(lib, w, blocks_per_head=sorted({x for x in (0, 1, n // 2, n - 2, n - 1) if 0 <= x < n}), heads=check)
+
+
+@pytest.mark.parametrize("L,H,B", [(1000, 2, 64), (1400, 16, 64), (1400, 16, 128), (1500, 16, 64), (2048, 20, 64), (63, 1, 128)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_bf16_all_blocks_selected_is_bitwise_dense(lib, L, H, B, d):
+    """Past the short kernel's line the number of blocks is even: the 128-row kernel walks the last of an odd number
+    on its own, in half tiles, whose row sums add up in another order."""
+    w = WORKLOADS["flux"].with_(heads=H, seq_len=L, head_dim=d, block=B, sparsity=0.0, grid=None)
+    q, k, v = (x.to(DEV) for x in make_qkv(w))
+    res = lib.forward_in_steps(q, k, v, B, 0.0, want_lse=True)
+    dense, lse = lib.dense_attention(q, k, v, B, want_lse=True)
+    assert torch.equal(res["out"], dense) and torch.equal(res["lse"], lse)
