@@ -26,8 +26,9 @@ typedef double f64x2 __attribute__((ext_vector_type(2)));
 //   reads of a V row feed four 16-channel tiles (tile t of half hf <-> channels 64 hf + 4 i + t); of the key
 //   channels each wave owns D / 4: channels 64 (w / 2) + 4 i + 2 (w % 2) + {0, 1} (head_dim 64: 4 i + w).
 // 8 heads of 4 500 tokens, head_dim 128: 63 us as a vector-ALU kernel that read K and V twice in 4-byte
-// pieces, 33 us now (55 MB of inputs and 19 MB of partial H; with two blocks to a workgroup the launch is one
-// round of the chip, so this is the latency of the loads of two blocks plus 2 x 3.4 us of products).
+// pieces, 25.7 us now (55 MB of inputs and 13 MB of partial H; 192 workgroups of three blocks, so this is the
+// latency of the first loads plus 3 x 3.4 us of products and the stores; 33 us with two blocks to a workgroup, where
+// some compute units had two workgroups).
 // 2 heads of 1 024 tokens, head_dim 64: 11.1 us, now 5.6 us.
 template <int D, int TPB>
 __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void stats_fp32_kernel(

@@ -4,6 +4,7 @@ tolerances are those of test_gpu_parity.py."""
 import pytest
 import torch
 
+import test_gpu_parity
 from test_gpu_parity import DEV, run_full_case
 from workloads import WORKLOADS, make_qkv
 
@@ -137,3 +138,9 @@ def test_bf16_all_blocks_selected_is_bitwise_dense(lib, L, H, B, d):
     res = lib.forward_in_steps(q, k, v, B, 0.0, want_lse=True)
     dense, lse = lib.dense_attention(q, k, v, B, want_lse=True)
     assert torch.equal(res["out"], dense) and torch.equal(res["lse"], lse)
+
+
+# the pairing belongs to the 128-row kernel: the same checks at sizes past the short kernel's line (340 and 322 workgroups)
+@pytest.mark.parametrize("L,approximate", [(64 * 340 - 21, True), (64 * 322, True), (64 * 340 - 21, False)])
+def test_query_blocks_paired_in_long_calls(lib, L, approximate):
+    test_gpu_parity.test_query_blocks_paired_by_row_similarity(lib, L, approximate)
