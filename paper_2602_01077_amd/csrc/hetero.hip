@@ -296,9 +296,11 @@ __device__ inline void wave_lds_sync() {
 // (1 / beta_c is computed beforehand, a lane per row) and s_{m+1}(lambda) is the characteristic polynomial but for a
 // constant.
 // theta: kept between `lo` and `hi`, a pass looks at 64 points of the interval at once, one a lane.  The lowest of
-// them without a sign change along s is still above the spectrum; the next one below is the new lo, and Laguerre's step
-// from it (monotone from above, with cubic convergence where the root is simple; first and second derivative along
-// the same recurrence) the new hi.
+// them without a sign change along s is still above the spectrum (`above_root`); the next one below is the new lo, and
+// Laguerre's step from it (monotone from above, with cubic convergence where the root is simple; first and second
+// derivative along the same recurrence) the new hi.  Where rounding carries that step below the root (a dominant
+// root: the step is exact, whatever the distance, and lands an ulp to either side), no point of the next pass is above the
+// spectrum: the root then lies between hi and `above_root`, and the passes go on in there.
 // residual: s satisfies all rows of T - theta above the one it is cut at, so the Krylov vector with the
 // coefficients s_1 .. s_c has |A x - theta x|^2 = beta_c^2 (s_c^2 + s_{c+1}^2) / (s_1^2 + .. + s_c^2); the least over
 // c is taken (past convergence rounding makes the later entries grow again).
@@ -325,6 +327,7 @@ __device__ inline RitzPair largest_ritz_pair(const double* alpha, const double* 
   wave_lds_sync();
   if (!(hi < bound)) hi = bound;                 // no estimate given, or no better one
   const double n = (double)m;
+  double above_root = INFINITY;                  // lowest point known to be above the spectrum
   for (int it = 0; it < 100; ++it) {
     const double lam = hi - (hi - lo) * (0.015625 * (double)lane);
     double s0 = 0.0, s1 = 1.0, p0 = 0.0, p1 = 0.0, q0 = 0.0, q1 = 0.0;     // s, s', s'' of the last two rows
@@ -346,11 +349,17 @@ __device__ inline RitzPair largest_ritz_pair(const double* alpha, const double* 
     const unsigned long long not_above = ~__ballot(above);
     const int n_above = not_above ? __builtin_ctzll(not_above) : 64;       // lanes 0 .. n_above - 1
     if (n_above == 0) {
-      if (hi < bound) {                          // the estimate was no upper bound
+      if (above_root < INFINITY) {               // Laguerre's step fell below the root by rounding
+        lo = fmax(lo, hi);
+        hi = above_root;
+        if (hi - lo < 1e-15 * hi) break;
+        continue;
+      }
+      if (hi < bound) {                          // the estimate handed in was no upper bound
         hi = bound;
         continue;
       }
-      break;                                     // on the root to rounding (or not a number)
+      break;                                     // no point above the spectrum at all: not a number, or a zero matrix
     }
     const double inv = reciprocal(s1), g = p1 * inv, h = fma(g, g, -q1 * inv);
     const double disc = fmax(1e-300, (n - 1.0) * fma(n, h, -g * g));
@@ -359,7 +368,11 @@ __device__ inline RitzPair largest_ritz_pair(const double* alpha, const double* 
     // how far the other roots are: 0: the root alone; 1: as if it were double
     const double crowd = read_lane(g * g * reciprocal(h), n_above - 1) - 1.0;
     if (n_above < 64) lo = fmax(lo, read_lane(lam, n_above));
-    if (!(step > 0.0)) break;
+    above_root = from;
+    if (!(step > 0.0)) {
+      hi = from;
+      break;
+    }
     hi = fmax(lo, from - step);
     // the distance left after a Laguerre step is about step * crowd^2
     if (step * crowd * crowd < 1e-15 * hi || hi - lo < 1e-15 * hi) break;

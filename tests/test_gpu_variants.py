@@ -144,3 +144,30 @@ def test_bf16_all_blocks_selected_is_bitwise_dense(lib, L, H, B, d):
 @pytest.mark.parametrize("L,approximate", [(64 * 340 - 21, True), (64 * 322, True), (64 * 340 - 21, False)])
 def test_query_blocks_paired_in_long_calls(lib, L, approximate):
     test_gpu_parity.test_query_blocks_paired_by_row_similarity(lib, L, approximate)
+
+
+def _heterogeneity_against_svd(lib, k, v, B):
+    """Spectral M_j of one head, each within 1e-9 of its own value (numpy SVD in fp64): the fp64 products and a Ritz value
+    with a 1e-7 residual (its error is quadratic in the residual) leave room for that."""
+    import numpy as np
+    st = lib.block_stats(k, k, v, B)
+    log_m = lib.block_heterogeneity(lib.make_shape(k, B), k, v, st["kbar64"], lib.PISA_NORM_SPECTRAL, 0.0)
+    H = _centred_products(k[0, 0].cpu(), v[0, 0].cpu(), B).numpy()
+    M = np.array([np.linalg.norm(h - H.mean(0), 2) for h in H])
+    got = np.exp(log_m[0, 0].cpu().numpy())
+    assert np.all(np.abs(got - M) <= 1e-9 * M), np.abs(got / M - 1.0).max()
+
+
+# one singular value of H_j - H_bar far above the others: the Krylov space ends after one or two steps
+@pytest.mark.parametrize("d,dtype", [(128, "bf16"), (64, "bf16"), (128, "fp32"), (64, "fp32")])
+@pytest.mark.parametrize("B", [64, 128])
+@pytest.mark.parametrize("factor", [float("inf"), 1e4, 3e3])     # the value channel over the others
+def test_spectral_heterogeneity_with_a_dominant_channel(lib, d, dtype, B, factor):
+    g = torch.Generator().manual_seed(d + B)
+    k, v = (torch.randn(1, 1, 24 * B, d, generator=g) for _ in range(2))
+    v[..., 5] *= min(factor, 1e4)
+    if factor == float("inf"):
+        v[..., :5] = 0.0
+        v[..., 6:] = 0.0                         # every H_j - H_bar has rank one
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    _heterogeneity_against_svd(lib, k.to(dt).to(DEV), v.to(dt).to(DEV), B)
