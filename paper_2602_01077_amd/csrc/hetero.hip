@@ -316,7 +316,8 @@ __device__ inline RitzPair largest_ritz_pair(const double* alpha, const double* 
   const int lane = threadIdx.x & 63;
   double bound = 0.0;
   for (int c = lane; c < m; c += 64) {
-    const double inv = reciprocal_sqrt(beta2[c]), b = beta2[c] * inv;
+    // beta = 0 (the last one, an exact end of the Krylov space): s_{m+1} is a multiple of the polynomial with any factor
+    const double inv = beta2[c] > 0.0 ? reciprocal_sqrt(beta2[c]) : 1.0, b = beta2[c] * inv;
     const double a = c > 0 ? beta2[c - 1] * reciprocal_sqrt(beta2[c - 1]) : 0.0;
     rows[c].alpha = alpha[c];
     rows[c].inv_beta = inv;

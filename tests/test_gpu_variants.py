@@ -171,3 +171,18 @@ def test_spectral_heterogeneity_with_a_dominant_channel(lib, d, dtype, B, factor
         v[..., 6:] = 0.0                         # every H_j - H_bar has rank one
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     _heterogeneity_against_svd(lib, k.to(dt).to(DEV), v.to(dt).to(DEV), B)
+
+
+@pytest.mark.parametrize("B,d", [(64, 64), (128, 64), (128, 128)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("c", [1.0, 0.25, 8.0])
+def test_spectral_heterogeneity_of_multiples_of_the_identity(lib, B, d, dtype, c):
+    """D_0 = c I = -D_1: A = D^T D maps the start vector to a multiple of itself without rounding, so that the first
+    off-diagonal of the Lanczos matrix can be exactly zero."""
+    k, v = torch.zeros(2, B, d), torch.zeros(2, B, d)
+    n = torch.arange(B)
+    for j in range(2):                           # tokens +-e_i: sum over the block of k^T v = +-2 on half of the channels
+        ch, used = (n // 2 + j * (d // 2)) % d, n < d
+        k[j, n[used], ch[used]] = 1.0 - 2.0 * (n[used] % 2)
+        v[j] = k[j] * (c if j == 0 else -c)
+    _heterogeneity_against_svd(lib, k.view(1, 1, -1, d).to(dtype).to(DEV), v.view(1, 1, -1, d).to(dtype).to(DEV), B)
