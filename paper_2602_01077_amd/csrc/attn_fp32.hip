@@ -304,14 +304,16 @@ __global__ __launch_bounds__(64 * kWaves, NBUF * KG * D > 512 ? 2 : 4) void attn
 #pragma unroll
   for (int u = 0; u < KG; ++u) m_all = fmaxf(m_all, part_s[0][u][16 * rg + i]);
   float l_all = 0.f, tail_all = 0.f;
+  // a group that met no key at all (maximum still -inf) holds zeros
+  auto weight = [&](float m_part) { return m_part == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_part - m_all); };
 #pragma unroll
   for (int u = 0; u < KG; ++u) {
-    const float f = __builtin_amdgcn_exp2f(part_s[0][u][16 * rg + i] - m_all);
+    const float f = weight(part_s[0][u][16 * rg + i]);
     l_all += part_s[1][u][16 * rg + i] * f;
     tail_all += part_s[2][u][16 * rg + i] * f;
   }
   {
-    const float f = __builtin_amdgcn_exp2f(m - m_all);
+    const float f = weight(m);
 #pragma unroll
     for (int t = 0; t < NT; ++t) o[t] *= f;
   }

@@ -186,3 +186,18 @@ def test_spectral_heterogeneity_of_multiples_of_the_identity(lib, B, d, dtype, c
         k[j, n[used], ch[used]] = 1.0 - 2.0 * (n[used] % 2)
         v[j] = k[j] * (c if j == 0 else -c)
     _heterogeneity_against_svd(lib, k.view(1, 1, -1, d).to(dtype).to(DEV), v.view(1, 1, -1, d).to(dtype).to(DEV), B)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d", [64, 128])
+def test_rows_that_attend_nothing(lib, dtype, d):
+    """Keep-or-drop with every index entry out of range: log of an empty sum, and 0 / 0."""
+    q, k, v = (torch.randn(1, 2, 300, d, device=DEV).to(dtype) for _ in range(3))
+    shape = lib.make_shape(q, 64)
+    idx = torch.full((1, 2, 5, 2), 9, dtype=torch.int32, device=DEV)
+    idx[:, :, 1] = torch.tensor([0, 3], dtype=torch.int32, device=DEV)
+    out, lse = lib.attention(shape, q, k, v, None, None, None, idx, 2, want_lse=True)
+    empty = torch.ones(300, dtype=torch.bool, device=DEV)
+    empty[64:128] = False
+    assert bool((lse[:, :, empty] == -float("inf")).all()) and bool(out[:, :, empty].isnan().all())
+    assert bool(lse[:, :, ~empty].isfinite().all()) and bool(out[:, :, ~empty].isfinite().all())
