@@ -163,9 +163,12 @@ __global__ __launch_bounds__(64 * kWaves, NBUF * KG * D > 512 ? 2 : 4) void attn
 #pragma unroll
   for (int t = 0; t < NT; ++t) o[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
   float m = -INFINITY, l = 0.f, l_tail = 0.f;     // log2 domain; l, l_tail: this lane's keys only
-  // scale * log2(e) in two fp32 parts, so that the base-2 logit is the scaled product to fp32 rounding
-  const float c_hi = p.scale * 1.44269504088896340736f;
-  const float c_lo = (float)((double)p.scale * 1.4426950408889634074 - (double)c_hi);
+  // scale * log2(e) in two fp32 parts, so that the base-2 logit is the scaled product to fp32 rounding; both
+  // positive, so that an infinite product stays what it is
+  const double c = (double)p.scale * 1.4426950408889634074;
+  float c_hi = (float)c;
+  if ((double)c_hi >= c) c_hi = __uint_as_float(__float_as_uint(c_hi) - 1u);
+  const float c_lo = (float)(c - (double)c_hi);
 
   // S^T of this wave's staged piece: element r = key 4 g + r.
   auto scores = [&](int buf) -> f32x4 {
@@ -200,6 +203,7 @@ __global__ __launch_bounds__(64 * kWaves, NBUF * KG * D > 512 ? 2 : 4) void attn
   };
   // Running maximum takes in the logits x (bias included, log2 domain up to the bias); returns the
   // probabilities and adds their sum to l.
+  bool far = false;                          // uniform: some row's maximum lies beyond +-2^20
   auto softmax = [&](const f32x4 s, const f32x4 bias) -> f32x4 {
     f32x4 z;
 #pragma unroll
@@ -214,10 +218,19 @@ __global__ __launch_bounds__(64 * kWaves, NBUF * KG * D > 512 ? 2 : 4) void attn
 #pragma unroll
       for (int t2 = 0; t2 < NT; ++t2) o[t2] *= corr;
       m = m_new;
+      far = __any(!(fabsf(m_new) <= 0x1p20f));
     }
     f32x4 e;
+    if (!far) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) e[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c_hi, fmaf(s[r], c_lo, bias[r] - m_safe)));
+      for (int r = 0; r < 4; ++r) e[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c_hi, fmaf(s[r], c_lo, bias[r] - m_safe)));
+    } else {
+      // There the rounding of the maximum itself is no longer small against 1 (keys masked by a huge negative
+      // channel, for one): the same rounded product is subtracted from it, so that the largest key keeps weight 1.
+#pragma clang fp contract(off)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) e[r] = __builtin_amdgcn_exp2f(s[r] * c_hi - (m_safe - bias[r]));
+    }
     l += (e[0] + e[1]) + (e[2] + e[3]);
     return e;
   };

@@ -201,3 +201,33 @@ def test_rows_that_attend_nothing(lib, dtype, d):
     empty[64:128] = False
     assert bool((lse[:, :, empty] == -float("inf")).all()) and bool(out[:, :, empty].isnan().all())
     assert bool(lse[:, :, ~empty].isfinite().all()) and bool(out[:, :, ~empty].isfinite().all())
+
+
+# a mask in a channel of its own: q = 1, k = a huge negative number or -inf, as finite as the type's lowest value
+@pytest.mark.parametrize("low", [-float("inf"), -3e38, -1e12])
+@pytest.mark.parametrize("masked", [(0, 32), (0, 16), (32, 64), (16, 48), (130, 470), (460, 520)])
+@pytest.mark.parametrize("d,scale", [(64, None), (128, None), (128, 1.0), (64, 0.3)])
+@pytest.mark.parametrize("dtype", [torch.float32])
+def test_keys_masked_by_a_channel(lib, dtype, d, scale, masked, low):
+    """Keys whose logits are lowest or -inf get no weight, wherever they fall among the pieces that a wave takes; the same
+    keys by a plain softmax over the others in fp64.  Tolerances: those of the oracle comparisons."""
+    g = torch.Generator().manual_seed(d)
+    L, H = 520, 2
+    q, k, v = (torch.randn(1, H, L, d, generator=g).to(dtype) for _ in range(3))
+    q[..., 0] = 1.0
+    k[..., 0] = 0.0
+    k[:, :, masked[0]:masked[1], 0] = low
+    out, lse = lib.dense_attention(q.to(DEV), k.to(DEV), v.to(DEV), 64, scale=scale, want_lse=True)
+    idx = torch.arange(9, dtype=torch.int32, device=DEV).repeat(1, H, 9, 1)[..., :8].contiguous()
+    part, _ = lib.attention(lib.make_shape(q, 64, scale), q.to(DEV), k.to(DEV), v.to(DEV), None, None, None, idx, 8)
+    keep = torch.ones(L, dtype=torch.bool)
+    keep[masked[0]:masked[1]] = False
+    s = lib.resolved_scale(d, scale)
+    for got, n in ((out, L), (part, 512)):
+        on = keep[:n].nonzero()[:, 0]
+        z = (q.double() @ k[:, :, on].double().transpose(-1, -2)) * s
+        ref = z.softmax(-1) @ v[:, :, on].double()
+        err = (got.double().cpu() - ref).abs().amax(-1) / ref.abs().amax(-1)
+        assert float(err.max()) <= test_gpu_parity.TOL[dtype], n       # (NaN fails)
+        if n == L:
+            assert float((lse.double().cpu() - z.logsumexp(-1)).abs().max()) <= (1e-4 if dtype == torch.float32 else 2e-2)
