@@ -143,7 +143,7 @@ __global__ __launch_bounds__(64 * kWaves, NBUF * KG * D > 512 ? 2 : 4) void attn
   };
 
   // This wave's share of a stage (K or V of buffer `buf`): 1 KB loads NLD wave .. NLD wave + NLD - 1, RPL
-  // rows each.  Rows past the end of the source repeat its last row (finite; the reader masks them).
+  // rows each.  Rows past the end of the source repeat its last row (the reader masks them).
   auto load_stage = [&](const float* src, int first_pc, int n_rows, bool kfmt, bool by_list, int buf) {
 #pragma unroll
     for (int u = 0; u < NLD; ++u) {
@@ -201,6 +201,20 @@ __global__ __launch_bounds__(64 * kWaves, NBUF * KG * D > 512 ? 2 : 4) void attn
         o[4 * hf + t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[t], b[r], o[4 * hf + t], 0, 0, 0);
     }
   };
+  // Clears what add_values would read of a piece's rows from `rows` on: copies of the last row there is, whose
+  // probability of 0 would make a NaN of an infinity.  (Waves that share the piece write the same zeros.)
+  auto clear_absent = [&](int rows, int buf) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));               // the addresses are made here, not kept in registers all along
+    LDS_PTR(float) v0 = ks + (2 * buf + 1) * STAGE_F + (kPiece * kg + 4 * (ln >> 4)) * D + 4 * (ln & 15);
+#pragma unroll 1
+    for (int r = 0; r < 4; ++r) {
+      if (4 * (ln >> 4) + r >= rows)
+#pragma unroll
+        for (int hf = 0; hf < NT / 4; ++hf)
+          *reinterpret_cast<LDS_PTR(f32x4)>(v0 + r * D + 64 * hf) = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+  };
   // Running maximum takes in the logits x (bias included, log2 domain up to the bias); returns the
   // probabilities and adds their sum to l.
   bool far = false;                          // uniform: some row's maximum lies beyond +-2^20
@@ -235,8 +249,8 @@ __global__ __launch_bounds__(64 * kWaves, NBUF * KG * D > 512 ? 2 : 4) void attn
     return e;
   };
 
-  // The walk over `n` pieces of (src_k, src_v): `absorb(pc, buf)` turns this wave's staged K piece into
-  // the B operand of the second product, or returns false if the wave has nothing in this trip.
+  // The walk over `n` pieces of (src_k, src_v): `absorb(pc, buf, e)` turns this wave's staged K piece into the B
+  // operand e of the second product and returns the rows the piece has, 0 if the wave has nothing in this trip.
   auto walk = [&](const float* src_k, const float* src_v, int n, int n_rows, bool by_list, auto absorb) {
     load_stage(src_k, 0, n_rows, true, by_list, 0);
     if (NBUF == 2) load_stage(src_v, 0, n_rows, false, by_list, 0);
@@ -250,29 +264,36 @@ __global__ __launch_bounds__(64 * kWaves, NBUF * KG * D > 512 ? 2 : 4) void attn
           load_stage(src_k, pc + KG, n_rows, true, by_list, buf ^ 1);
           load_stage(src_v, pc + KG, n_rows, false, by_list, buf ^ 1);
         }
-        if (absorb(pc + kg, buf, e)) add_values(e, buf);
+        const int rows = absorb(pc + kg, buf, e);
+        if (rows > 0) {
+          if (rows < kPiece) clear_absent(rows, buf);
+          add_values(e, buf);
+        }
         buf ^= 1;
       } else {
         load_stage(src_v, pc, n_rows, false, by_list, 0);
-        const bool mine = absorb(pc + kg, 0, e);
+        const int rows = absorb(pc + kg, 0, e);
         wait_async_loads();
         __syncthreads();                     // V has landed; K is used up
         if (pc + KG < n) load_stage(src_k, pc + KG, n_rows, true, by_list, 0);
-        if (mine) add_values(e, 0);
+        if (rows > 0) {
+          if (rows < kPiece) clear_absent(rows, 0);
+          add_values(e, 0);
+        }
       }
     }
   };
 
   // ---- Phase 1: exact pieces ----
   if (n_exact > 0)
-    walk(kh, vh, n_exact, L, true, [&](int pc, int buf, f32x4& e) -> bool {
+    walk(kh, vh, n_exact, L, true, [&](int pc, int buf, f32x4& e) -> int {
       const int first = exact_row(pc);
-      if (first < 0) return false;
+      if (first < 0) return 0;
       f32x4 bias;
 #pragma unroll
       for (int r = 0; r < 4; ++r) bias[r] = first + 4 * g + r < L ? 0.f : -INFINITY;
       e = softmax(scores(buf), bias);
-      return true;
+      return L - first;
     });
 
   // ---- Phase 2: centroid pieces ----
@@ -284,8 +305,8 @@ __global__ __launch_bounds__(64 * kWaves, NBUF * KG * D > 512 ? 2 : 4) void attn
     const int n_cen = (N + kPiece - 1) / kPiece;
     __syncthreads();                         // every wave is done with the stages
     walk(p.kbar + bh * (size_t)N * D, p.vsum + bh * (size_t)N * D, n_cen, N, false,
-         [&](int pc, int buf, f32x4& e) -> bool {
-           if (pc >= n_cen) return false;
+         [&](int pc, int buf, f32x4& e) -> int {
+           if (pc >= n_cen) return 0;
            const int j0 = pc * kPiece + 4 * g;          // this lane's first centroid
            const unsigned bits = chosen[j0 >> 5] >> (j0 & 31);
            f32x4 bias;
@@ -296,7 +317,7 @@ __global__ __launch_bounds__(64 * kWaves, NBUF * KG * D > 512 ? 2 : 4) void attn
            l_tail += (e[0] + e[1]) + (e[2] + e[3]);
 #pragma unroll
            for (int r = 0; r < 4; ++r) e[r] *= j0 + r == N - 1 ? inv_last : inv_full;
-           return true;
+           return N - pc * kPiece;
          });
   }
 

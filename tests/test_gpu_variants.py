@@ -231,3 +231,21 @@ def test_keys_masked_by_a_channel(lib, dtype, d, scale, masked, low):
         assert float(err.max()) <= test_gpu_parity.TOL[dtype], n       # (NaN fails)
         if n == L:
             assert float((lse.double().cpu() - z.logsumexp(-1)).abs().max()) <= (1e-4 if dtype == torch.float32 else 2e-2)
+
+
+@pytest.mark.parametrize("d,L,H", [(64, 70, 1), (128, 1000, 2), (128, 64 * 22 + 9, 10), (64, 64 * 40 + 17, 20)])
+def test_fp32_infinite_value_in_the_last_row(lib, d, L, H):
+    """The rows a ragged tile lacks must add nothing: with an infinite value in the last row that is there, its channel is
+    infinite and the others stay what they were; the same for the last block's value sum among the centroids."""
+    g = torch.Generator().manual_seed(L)
+    q, k, v = (torch.randn(1, H, L, d, generator=g).to(DEV) for _ in range(3))
+    w = v.clone()
+    w[:, :, -1, 3] = float("inf")
+    others = [c for c in range(d) if c != 3]
+    a, b = lib.dense_attention(q, k, v)[0], lib.dense_attention(q, k, w)[0]
+    assert bool((b[..., 3] == float("inf")).all()) and torch.equal(a[..., others], b[..., others])
+    n, shape = lib.num_blocks(L, 64), lib.make_shape(q, 64)
+    idx = torch.zeros(1, H, n, 1, dtype=torch.int32, device=DEV)       # block 0 exactly, the rest by their centroids
+    a, b = ((lib.attention(shape, q, k, x, st["kbar"], st["vsum"], None, idx, 1)[0])
+            for x in (v, w) for st in (lib.block_stats(q, k, x, 64),))
+    assert bool((b[..., 3] == float("inf")).all()) and torch.equal(a[..., others], b[..., others])
