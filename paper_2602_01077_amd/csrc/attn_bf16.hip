@@ -1031,10 +1031,35 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
 // a row (each with a running maximum of its own) meet in LDS once, before Phase 3, and each wave of the
 // pair finishes half of the channels.  The tiles of one index row are walked straight from its bitmask.
 
+// exp_rows against a maximum that has just taken these keys in: the same rounded product is subtracted from it, so
+// that the largest key has weight 1 whatever its size.  (With 32 keys to a wave's step, a step can consist of nothing but
+// keys that a channel of their own masks by the lowest value or -inf; against the unrounded product such a step
+// sums up to anything between 0 and inf.)
+__device__ inline void exp_rows_at_max(const f32x16& s, float c, float m, bf16x8& p0, bf16x8& p1, float& pa, float& pc) {
+#pragma clang fp contract(off)
+  const float m_safe = m == -INFINITY ? 0.f : m;
+#pragma unroll
+  for (int step = 0; step < 2; ++step) {
+    u32x4 pw;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 8 * step + 2 * i;
+      const float x0 = __builtin_amdgcn_exp2f(s[r] * c - m_safe);
+      const float x1 = __builtin_amdgcn_exp2f(s[r + 1] * c - m_safe);
+      pw[i] = pack_bf16(x0, x1);
+      if (i & 1) pc += x0 + x1;
+      else pa += x0 + x1;
+    }
+    if (step == 0) p0 = __builtin_bit_cast(bf16x8, pw);
+    else p1 = __builtin_bit_cast(bf16x8, pw);
+  }
+}
+
 // 32 staged keys, start to finish, with the exact softmax step (ragged tile, centroid tiles); see absorb_tile.
 template <int D, bool TAIL, bool RAGGED, int KOFF, int VOFF>
 __device__ inline void absorb_rows(State<D>& st, const bf16x8 (&qreg)[D / 16], const LaneCtx& lc,
                                    LDS_PTR(const float) bias, int nvalid, float c) {
+#pragma clang fp contract(off)
   f32x16 s;
   bf16x8 pb[2];
   qk_rows<D, KOFF, 0>(s, qreg, lc);
@@ -1060,7 +1085,7 @@ __device__ inline void absorb_rows(State<D>& st, const bf16x8 (&qreg)[D / 16], c
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const int r = 8 * step + 2 * i + u;
-        x[u] = __builtin_amdgcn_exp2f(TAIL ? s[r] + nm : fmaf(s[r], c, nm));
+        x[u] = __builtin_amdgcn_exp2f(TAIL ? s[r] + nm : s[r] * c + nm);      // two roundings: see exp_rows_at_max
         if (RAGGED && (r / 4) * 8 + 4 * h + (r % 4) >= nvalid) x[u] = 0.f;
         psum += x[u];
       }
@@ -1202,7 +1227,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_short_kernel(PB p) {
       if (__any(!(pa + pc < kStaleLimit))) {           // first keys of this wave, or a maximum that ran away
         raise_max<D>(st, max_rows(sc) * c);
         pa = pc = 0.f;
-        exp_rows(sc, c, -st.m, p0, p1, pa, pc);
+        exp_rows_at_max(sc, c, st.m, p0, p1, pa, pc);
       }
       st.l += pa + pc;
       pv_rows<D, V_CUR, 0>(st, p0, p1, lc);

@@ -207,7 +207,7 @@ def test_rows_that_attend_nothing(lib, dtype, d):
 @pytest.mark.parametrize("low", [-float("inf"), -3e38, -1e12])
 @pytest.mark.parametrize("masked", [(0, 32), (0, 16), (32, 64), (16, 48), (130, 470), (460, 520)])
 @pytest.mark.parametrize("d,scale", [(64, None), (128, None), (128, 1.0), (64, 0.3)])
-@pytest.mark.parametrize("dtype", [torch.float32])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_keys_masked_by_a_channel(lib, dtype, d, scale, masked, low):
     """Keys whose logits are lowest or -inf get no weight, wherever they fall among the pieces that a wave takes; the same
     keys by a plain softmax over the others in fp64.  Tolerances: those of the oracle comparisons."""
