@@ -1110,7 +1110,7 @@ __global__ __launch_bounds__(256, 2) void attn_bf16_short_kernel(PB p) {
 
   // Each XCD gets a contiguous range of (head, query tile) items, so that its L2 fetches the K, V and hsum of few heads.
   // Dealt round robin every XCD fetched all of them, and many short heads ran slower than on the 128-row kernel
-  // (attention of 64 heads of 512 tokens, 4 of 8 blocks: main kernel 26.0 us, short 31.6, now 23.0; 32 heads of 1 024,
+  // (attention of 64 heads of 512 tokens, 4 of 8 blocks: main kernel 26.1 us, short 31.6, now 23.5; 32 heads of 1 024,
   // 8 of 16: 29.5, 31.4, now 25.0; dense, 44 heads of 512: 15.2, 19.8, now 15.9).
   const int per_xcd = (p.total + 7) / 8;
   const int item = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
@@ -1408,6 +1408,30 @@ void attention_workspace_carve(const Dims& dm, void* workspace, void** kcen, voi
   *hpack = kc + 2 * tile_elems;
 }
 
+// Which kernel: up to how many 128-row workgroups of the main kernel the short one takes a call (us for the attention
+// step, main / short, head_dim 128 unless noted).  Up to 128 every 64-row workgroup has a CU to itself and the short
+// kernel is ahead everywhere (2 heads of 1 000 tokens 18.5 / 11.0, 16 heads of 1 024 with 1 of 16 blocks 16.0 / 13.5);
+// above, two share a CU that one main workgroup had, and it depends on what the call walks:
+//  - dense and block 128, where the main kernel walks one list: 176 (dense, 44 heads of 512 15.3 / 15.9, 7 of 3 000
+//    54.5 / 50.1, 12 of 2 048 (192 workgroups) 39.0 / 40.2; block 128, 11 heads of 2 048 with 5 of 16 blocks 25.6 / 23.9);
+//  - block 64, where it walks the union of two index rows: 320 (10 heads of 4 096 with 12 of 64 blocks 46.2 / 41.6,
+//    with 40 93.8 / 87; 384 workgroups 64.2 / 64.8);
+//  - where the union is hardly more than one row, past three quarters of the blocks at head_dim 128: 256 (1 head of 34 816
+//    with 490 of 544 blocks, 272 workgroups, 790 / 847; 5 of 8 192 with 116 of 128 207 / 214; 256 workgroups with 248 of 256
+//    blocks 336 / 275; at head_dim 64 the short kernel stays ahead, 701 / 558);
+//  - with no exact block, or one of 128 tokens, little is left but what every workgroup does once: 128 (11 heads of
+//    2 048, block 128, no block 13.0 / 14.3, one 16.4 / 17.0; block 64, no block 13.7 / 14.3; head_dim 64 and block 64, 320
+//    workgroups, 11.5 / 10.7).
+// With every block selected a call takes the line of the dense one, whose bits it has to give.
+static int short_call_limit(const Dims& dm, const AttnArgs& a) {
+  constexpr int kAlone = 128, kOneList = 176, kTwoPerCu = 256, kTwoLists = 320;
+  if (a.dense || a.k_top == dm.N) return kOneList;
+  if (dm.B != kTile) return a.k_top <= 1 ? kAlone : kOneList;
+  if (dm.d == 64) return kTwoLists;
+  if (a.k_top == 0) return kAlone;
+  return 4 * a.k_top > 3 * dm.N ? kTwoPerCu : kTwoLists;
+}
+
 template <int D>
 static hipError_t launch_attention_bf16_d(const Dims& dm, const AttnArgs& a, hipStream_t stream) {
   PB p{};
@@ -1427,15 +1451,7 @@ static hipError_t launch_attention_bf16_d(const Dims& dm, const AttnArgs& a, hip
   p.scale = dm.scale;
   p.first_order = a.hsum != nullptr;
 
-  // Which kernel: by the number of 128-row workgroups the main kernel would have on the 256 CUs (us per
-  // call, main / short kernel, head_dim 128 unless noted).  Dense: 16 workgroups 22.4 / 15.4, 144 79.2 / 72.2,
-  // 180 85.6 / 83.6, 192 39.0 / 40.2, 256 43.6 / 45.3, 432 131 / 158.  Block 128: 128 workgroups
-  // 40.8 / 35.8, 160 41.9 / 41.2, 192 42.6 / 42.3, 256 44.2 / 47.1.  Block 64, where the main kernel walks the
-  // union of two index rows: 16 31.6 / 24.7, 96 37.5 / 29.3, 256 (2 heads of 16 384) 133.9 / 94.8, 288
-  // 66.7 / 65.8, 320 57.3 / 56.9, 384 64.2 / 64.8, 432 71.4 / 75.9 (head_dim 64 48.7 / 46.1).  With every
-  // block selected a call takes the line of the dense one, whose bits it has to give.
-  constexpr int kShortDense = 176, kShortBlock64 = 320;
-  const bool short_call = p.total <= (a.dense || a.k_top == dm.N || dm.B != kTile ? kShortDense : kShortBlock64);
+  const bool short_call = p.total <= short_call_limit(dm, a);
   if (short_call) {
     p.n_super = (dm.L + kTile - 1) / kTile;
     p.total = p.n_super * dm.bh();

@@ -112,14 +112,17 @@ def test_sums_over_chunks(lib, dtype, H, L, d, B):
 
 
 # bf16 attention: the kernel with 64 rows per workgroup (few workgroups) on both sides of its lines: 176 workgroups of
-# 128 rows for block 128, 320 for block 64; ragged tiles of 1, 9, 33 and 63 rows, one and two centroid tiles, no full
-# tile, no selected block
+# 128 rows for block 128, 320 for block 64, 256 for block 64 past three quarters of the blocks, 128 without an exact block or
+# with one of 128 tokens; ragged tiles of 1, 9, 33 and 63 rows, one and two centroid tiles, no full tile, no selected block
 @pytest.mark.parametrize("L,H,d,B,r,check", [
     (40, 2, 128, 64, 0.0, [0, 1]), (65, 1, 64, 64, 0.5, [0]), (1000, 2, 128, 64, 0.8, [0, 1]),
     (64 * 3 + 33, 3, 128, 128, 0.5, [0, 2]), (64 * 5 + 63, 2, 64, 128, 1.0, [0, 1]), (64 * 9 + 9, 2, 128, 64, 1.0, [1]),
     (64 * 70 + 1, 2, 128, 64, 0.9, [0, 1]), (64 * 129, 1, 64, 64, 0.95, [0]),
     (1400, 16, 128, 128, 0.7, [0, 15]), (1409, 16, 128, 128, 0.7, [0, 15]),
     (2048, 20, 128, 64, 0.85, [0, 19]), (2049, 20, 128, 64, 0.85, [0, 19]),
+    (2048, 16, 128, 64, 0.1, [0, 15]), (2049, 16, 128, 64, 0.1, [0, 15]),
+    (1024, 16, 128, 64, 1.0, [0, 15]), (1025, 16, 128, 64, 1.0, [0, 15]),
+    (1024, 16, 64, 128, 0.9, [0, 15]), (1025, 16, 64, 128, 0.9, [0, 15]),
 ])
 def test_bf16_short_calls(lib, L, H, d, B, r, check):
     w = WORKLOADS["flux"].with_(name=f"short-{L}-{H}", heads=H, seq_len=L, head_dim=d, block=B, sparsity=r, grid=None,
