@@ -179,10 +179,10 @@ __global__ __launch_bounds__(64 * stats_waves(D), D == 128 ? 4 : 2) void stats_b
       const int rows = min(kTile, L - row0);
       if (rows <= 0) break;                       // uniform: the block ends inside its first half
       n_sub = sub + 1;
-      // LDS addresses are made again per sub-block from this copy: hoisted, they cost more registers
-      // than eight waves a workgroup leave.
+      // Head_dim 128: LDS addresses are made again per sub-block from this copy; hoisted, they cost more
+      // registers than eight waves a workgroup leave.
       int ln = lane;
-      asm volatile("" : "+v"(ln));
+      if (D == 128) asm volatile("" : "+v"(ln));
       const int cpn = ln % LPR, rpn = ln / LPR;
       int next_row0, next_rows;
       {
@@ -327,7 +327,8 @@ __global__ __launch_bounds__(64 * stats_waves(D), D == 128 ? 4 : 2) void stats_b
       double ss = 0.0;
       const float* hp = hs_head;
       unsigned hoff = 4 * h * D + lam;
-      asm volatile("" : "+s"(hp), "+v"(hoff));    // keeps the loads below inside the block loop (hoisted, they spill)
+      asm volatile("" : "+s"(hp));    // keeps the loads below inside the block loop (hoisted, they spill), and at
+      if (D == 128) asm volatile("" : "+v"(hoff));    // head_dim 128 their addresses as well
 #pragma unroll
       for (int bt = 0; bt < NB; ++bt) {
         float hb[16];                 // the elements of hsum at this lane's accumulator positions (see the store below)
