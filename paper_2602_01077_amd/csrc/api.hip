@@ -77,8 +77,10 @@ StatsPlan matrix_bound_plan(const Dims& dm) {
   if (!few_blocks(dm)) return stats_plan(dm);
   int best = 1;
   double best_cost = 1e300;
-  for (int c = 1; c <= dm.N; ++c) {
-    const long long groups = (long long)dm.bh() * ((dm.N + c - 1) / c);
+  // every number of chunks there is, with the shortest chunk that gives it (at most 2 sqrt(N) of them)
+  for (int c = 1, chunks = 0; chunks != 1; c = (dm.N + chunks - 2) / std::max(chunks - 1, 1)) {
+    chunks = (dm.N + c - 1) / c;
+    const long long groups = (long long)dm.bh() * chunks;
     const double cost = (double)((groups + 255) / 256) * c + 0.25 * (double)groups / 256.0;
     if (cost <= best_cost) {
       best = c;

@@ -183,3 +183,19 @@ def test_binding_refuses_host_tensors():
     q = torch.zeros(1, 2, 128, 64)
     with pytest.raises(ValueError):
         pisa.dense_attention(q, q, q)
+
+
+def test_chunk_plan_of_the_matrix_bound_sums(lib):
+    """pisa_workspace_bytes holds the fp64 partial sums and Hbar of pisa_block_heterogeneity: their number is that of the cheapest
+    chunk length over all lengths 1 .. N (blocks on the fullest of 256 compute units plus a quarter of a block per partial sum)."""
+    d = 128
+    for n in list(range(1, 130)) + [255, 256, 257, 1000, 4096]:
+        for bh in sorted({1, 2, 7, 24, max(1, 4096 // n)}):
+            if n * bh > 4096:
+                continue
+            cost = lambda c: (-(-bh * -(-n // c) // 256) * c + 0.25 * (bh * -(-n // c)) / 256.0, -c)
+            chunks = -(-n // min(range(1, n + 1), key=cost))
+            need = bh * (chunks + 1) * d * d * 8
+            logits = 8 * bh * n * n                                   # what pisa_select needs
+            got = lib.workspace_bytes(lib.PisaShape(1, bh, n * 64, d, 64, lib.PISA_FP32, 0.0))
+            assert got == max(need, logits), (n, bh)
