@@ -1,10 +1,13 @@
 """GPU parity at the edges of the kernels' dispatch rules: sizes on both sides of every line at which
 another build of a kernel takes over, with remainders in every tile dimension.  Oracle, checks and
 tolerances are those of test_gpu_parity.py."""
+import numpy as np
 import pytest
 import torch
 
 import test_gpu_parity
+from oracle import pisa_oracle as po
+from parity_util import COS_MIN, TOL, head_np, row_errors, rows_of_blocks
 from test_gpu_parity import DEV, run_full_case
 from workloads import WORKLOADS, make_qkv
 
@@ -36,7 +39,8 @@ def test_fp32_all_blocks_selected_is_bitwise_dense(lib, L, H):
     assert torch.equal(res["out"], dense) and torch.equal(res["lse"], lse)
 
 
-# Spectral norm of the block heterogeneity: matrices whose Krylov space ends early, and clustered singular values
+# Spectral norm of the block heterogeneity: blocks whose H_j has a low rank or clustered singular values.  (H_j - H_bar, which
+# the norm is taken of, has full rank all the same; the tests with a dominant channel have matrices of rank one.)
 @pytest.mark.parametrize("d,dtype", [(128, "bf16"), (64, "bf16"), (128, "fp32"), (64, "fp32")])
 @pytest.mark.parametrize("B", [64, 128])
 def test_spectral_heterogeneity_of_special_blocks(lib, d, dtype, B):
@@ -44,7 +48,6 @@ def test_spectral_heterogeneity_of_special_blocks(lib, d, dtype, B):
     rows, 1 or 2 or 5 distinct tokens (rank 0, 1, 4), pairs of tokens with equal weight in orthogonal channels (repeated
     singular values), a ragged last block of 3 tokens.  1e-9 of the largest norm is what the fp64 products and a Ritz
     value with a 1e-7 residual leave room for (its error is quadratic in the residual)."""
-    import numpy as np
     g = torch.Generator().manual_seed(d + B)
     n, rows = 9, []
     for j in range(n):
@@ -152,7 +155,6 @@ def test_query_blocks_paired_in_long_calls(lib, L, approximate):
 def _heterogeneity_against_svd(lib, k, v, B):
     """Spectral M_j of one head, each within 1e-9 of its own value (numpy SVD in fp64): the fp64 products and a Ritz value
     with a 1e-7 residual (its error is quadratic in the residual) leave room for that."""
-    import numpy as np
     st = lib.block_stats(k, k, v, B)
     log_m = lib.block_heterogeneity(lib.make_shape(k, B), k, v, st["kbar64"], lib.PISA_NORM_SPECTRAL, 0.0)
     H = _centred_products(k[0, 0].cpu(), v[0, 0].cpu(), B).numpy()
@@ -231,7 +233,7 @@ def test_keys_masked_by_a_channel(lib, dtype, d, scale, masked, low):
         z = (q.double() @ k[:, :, on].double().transpose(-1, -2)) * s
         ref = z.softmax(-1) @ v[:, :, on].double()
         err = (got.double().cpu() - ref).abs().amax(-1) / ref.abs().amax(-1)
-        assert float(err.max()) <= test_gpu_parity.TOL[dtype], n       # (NaN fails)
+        assert float(err.max()) <= TOL[dtype], n       # (NaN fails)
         if n == L:
             assert float((lse.double().cpu() - z.logsumexp(-1)).abs().max()) <= (1e-4 if dtype == torch.float32 else 2e-2)
 
@@ -252,3 +254,106 @@ def test_fp32_infinite_value_in_the_last_row(lib, d, L, H):
     a, b = ((lib.attention(shape, q, k, x, st["kbar"], st["vsum"], None, idx, 1)[0])
             for x in (v, w) for st in (lib.block_stats(q, k, x, 64),))
     assert bool((b[..., 3] == float("inf")).all()) and torch.equal(a[..., others], b[..., others])
+
+
+# The 128-row bf16 kernel past the short kernel's lines (12 workgroups a head at 1 409 and 1 500 tokens): what most of the small
+# shapes of test_gpu_parity.py no longer reach
+@pytest.mark.parametrize("L,H,d,B,r,mode", [
+    (1409, 29, 64, 64, 1.0, "hybrid"),           # no selected block
+    (1409, 12, 64, 128, 1.0, "hybrid"),
+    (1409, 29, 128, 64, 0.8, "pisa0"), (1409, 29, 64, 128, 0.8, "pisa0"),
+    (1409, 29, 64, 64, 0.7, "sparse"), (1409, 29, 128, 64, 0.7, "sparse"),      # 23 blocks: the last workgroup holds one
+    (1409, 29, 128, 128, 0.7, "sparse"),
+    (64 * 17 + 1, 40, 128, 64, 0.5, "hybrid"),
+])
+def test_bf16_long_calls(lib, L, H, d, B, r, mode):
+    w = WORKLOADS["flux"].with_(name=f"long-{L}-{H}-{mode}", heads=H, seq_len=L, head_dim=d, block=B, sparsity=r, grid=None,
+                                block_offset_std=0.5, seed=L + H)
+    n = -(-L // B)
+    run_full_case(lib, w, blocks_per_head=sorted({0, 1, n // 2, n - 2, n - 1}), heads=[0, H - 1],
+                  first_order=mode == "hybrid", approximate=mode != "sparse")
+
+
+def _check_heads(lib, q, k, v, B, idx, out, heads, blocks, scale, mode="hybrid", what=""):
+    """Rows of the listed blocks and heads against the oracle; idx[h]: the head's index rows."""
+    rows = rows_of_blocks(blocks, B, q.shape[2])
+    for h in heads:
+        Q, K, V = head_np(q, 0, h), head_np(k, 0, h), head_np(v, 0, h)
+        st = po.block_stats(Q, K, V, B)
+        ref, _ = po.attention_head(Q, K, V, B, None if idx is None else idx[h], scale, mode, blocks=blocks, stats=st)
+        rel, cos = row_errors(out[0, h].float().cpu().numpy()[rows], ref)
+        assert rel <= TOL[q.dtype] and cos >= COS_MIN, (what, h, rel, cos)
+
+
+@pytest.mark.parametrize("direction", ["rising", "falling", "spike"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_runaway_maximum_in_long_calls(lib, direction, d):
+    """test_runaway_maximum past the short kernel's lines (18 workgroups a head: 324 in all), so that the 128-row kernel, whose
+    maximum is refreshed only when a tile sum nears overflow, takes the dense and the sparse call."""
+    L, H, B = 2304, 18, 64
+    w = WORKLOADS["flux"].with_(name=f"runaway-{direction}", heads=H, seq_len=L, head_dim=d, grid=None, sparsity=0.5)
+    q, k, v = make_qkv(w, device="cpu")
+    u = torch.zeros(d)
+    u[:8] = 1.0
+    pos = torch.arange(L, dtype=torch.float32) / L
+    ramp = {"rising": pos - 0.5, "falling": 0.5 - pos, "spike": torch.zeros(L)}[direction]
+    if direction == "spike":
+        ramp[L // 2 + 5] = 1.0
+    q = (q.float() * 0.25 + 24.0 * u).to(torch.bfloat16)
+    k = (k.float() * 0.25 + (35.0 * ramp)[:, None] * u).to(torch.bfloat16)
+    qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
+    scale = lib.resolved_scale(d)
+    dense, _ = lib.dense_attention(qd, kd, vd, B)
+    res = lib.forward_in_steps(qd, kd, vd, B, w.sparsity)
+    blocks = [0, 1, 17, 35]
+    _check_heads(lib, q, k, v, B, None, dense, [0, H - 1], blocks, scale, "dense", direction)
+    _check_heads(lib, q, k, v, B, res["idx"][0].cpu().numpy(), res["out"], [0, H - 1], blocks, scale, "hybrid", direction)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_out_of_range_index_entries_in_long_calls(lib, d):
+    """Entries outside [0, N) at different places of the two rows of a 128-row workgroup: their lists differ in length, so
+    that some tiles of either are left without a partner."""
+    L, H, B = 1500, 28, 64
+    w = WORKLOADS["flux"].with_(name="badidx", heads=H, seq_len=L, head_dim=d, grid=None, sparsity=0.6)
+    q, k, v = make_qkv(w, device="cpu")
+    qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
+    shape, scale = lib.make_shape(qd, B), lib.resolved_scale(d)
+    ws = lib.alloc_workspace(shape, DEV)
+    st = lib.block_stats(qd, kd, vd, B, ws)
+    n, k_top = lib.num_blocks(L, B), lib.topk_count(lib.num_blocks(L, B), w.sparsity)
+    idx, _ = lib.select(shape, st["qbar64"], st["kbar64"], k_top, ws)
+    bad = idx.clone()
+    for i in range(n):                                        # neighbours lose 0 to 4 entries, at the front or at the back
+        lost = (0, 3, 4, 1, 0, 2)[i % 6]
+        for t in range(lost):
+            bad[:, :, i, t if i % 2 else -1 - t] = (n + 7, -3, 2 ** 31 - 1, -2 ** 31)[t]
+    out, _ = lib.attention(shape, qd, kd, vd, st["kbar"], st["vsum"], st["hsum"], bad, k_top, workspace=ws)
+    kept = [[r[(r >= 0) & (r < n)] for r in bad[0, h].cpu().numpy()] for h in range(H)]
+    _check_heads(lib, q, k, v, B, kept, out, [0, H - 1], list(range(n)), scale)
+
+
+@pytest.mark.parametrize("d,scale", [(128, 0.2), (64, 0.01)])
+def test_custom_softmax_scale_in_long_calls(lib, d, scale):
+    L, H, B = 1409, 29, 64
+    w = WORKLOADS["flux"].with_(name=f"scale-{scale}", heads=H, seq_len=L, head_dim=d, grid=None, sparsity=0.75)
+    q, k, v = make_qkv(w, device="cpu")
+    qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
+    s32 = lib.resolved_scale(d, scale)
+    res = lib.forward_in_steps(qd, kd, vd, B, w.sparsity, scale=scale)
+    dense, _ = lib.dense_attention(qd, kd, vd, B, scale=scale)
+    blocks = [0, 1, 11, 21, 22]
+    _check_heads(lib, q, k, v, B, res["idx"][0].cpu().numpy(), res["out"], [0, H - 1], blocks, s32)
+    _check_heads(lib, q, k, v, B, None, dense, [0, H - 1], blocks, s32, "dense")
+
+
+def test_static_scratch_in_long_calls(lib):
+    """pisa_attention_static with the pairing tables in the built-in scratch (340 workgroups, 340 blocks): the bits of the call
+    with a workspace."""
+    w = WORKLOADS["flux"].with_(heads=2, seq_len=64 * 340 - 21, grid=None, sparsity=0.85)
+    q, k, v = (x.to(DEV) for x in make_qkv(w, device="cpu"))
+    res = lib.forward_in_steps(q, k, v, w.block, w.sparsity, want_lse=True)
+    st, out, lse = res["stats"], torch.full_like(q, float("nan")), torch.full_like(res["lse"], float("nan"))
+    lib.attention_static(lib.make_shape(q, w.block), q, k, v, st["kbar"], st["vsum"], st["hsum"], res["idx"], res["k_top"],
+                         out=out, lse=lse)
+    assert torch.equal(out, res["out"]) and torch.equal(lse, res["lse"])
