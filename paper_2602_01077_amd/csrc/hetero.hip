@@ -39,11 +39,10 @@ template <int D> struct Geo {
   // tid at pair_at: every store of a wave is 1 KB in one piece.  (As rows and columns a lane's 16 bytes lay 64 apart: sum
   // over 19 heads of 10 blocks 21.7 us in bf16 and 22.4 in fp32, now 15.6 and 16.3.)
   __device__ static inline int pair_at(int a, int e, int b, int tid) { return ((a * 4 + e) * (TB / 2) + b / 2) * 256 + tid; }
-  // Its inverse for one element: place n of a matrix in memory -> place in row-major order.
-  __device__ static inline int row_major(int n) {
-    const int tid = (n / 2) % 256, slot = n / 512, b = 2 * (slot % (TB / 2)) + (n & 1), ae = slot / (TB / 2);
-    const int i = tid & 15, kk = (tid >> 4) & 3, w = tid >> 6;
-    return ((D / 4) * w + TA * (4 * (ae % 4) + kk) + ae / 4) * D + TB * i + b;
+  // The same place by row (key channel) and even column (value channel).
+  __device__ static inline int pair_of(int row, int col) {
+    const int w = row / (D / 4), r = row % (D / 4), a = r % TA, kk = r / TA % 4, e = r / TA / 4;
+    return pair_at(a, e, col % TB, 64 * w + 16 * kk + col / TB);
   }
 };
 
@@ -201,18 +200,20 @@ __global__ __launch_bounds__(256) void hbar_from_hsum_kernel(const float* __rest
   if (e < total) hbar64[e] = (double)hsum[e] / (double)N;
 }
 
-// hbar64[bh] = (sum over chunks, in chunk order, of partial[bh][chunk]) / N, row-major
+// hbar64[bh] = (sum over chunks, in chunk order, of partial[bh][chunk]) / N, row-major: a thread per pair of columns (a
+// wave writes 1 KB in one piece and reads pieces of 256 bytes).
 template <int D>
 __global__ __launch_bounds__(256) void hbar64_kernel(const double* __restrict__ partial,
                                                      double* __restrict__ hbar64, int n_chunks, int N) {
-  constexpr int dd = D * D;
+  constexpr int pairs = D * D / 2;
   const size_t bh = blockIdx.y;
-  const int n = blockIdx.x * 256 + threadIdx.x;              // the grid covers dd exactly
-  const double* p = partial + bh * n_chunks * (size_t)dd + n;
-  double acc = 0.0;
+  const int n = blockIdx.x * 256 + threadIdx.x;              // the grid covers them exactly
+  const f64x2* p = reinterpret_cast<const f64x2*>(partial) + bh * n_chunks * (size_t)pairs +
+                   Geo<D>::pair_of(n / (D / 2), n % (D / 2) * 2);
+  f64x2 acc = {0.0, 0.0};
 #pragma unroll 8
-  for (int c = 0; c < n_chunks; ++c) acc += p[(size_t)c * dd];
-  hbar64[bh * dd + Geo<D>::row_major(n)] = acc / (double)N;
+  for (int c = 0; c < n_chunks; ++c) acc += p[(size_t)c * pairs];
+  reinterpret_cast<f64x2*>(hbar64)[bh * pairs + n] = f64x2{acc[0] / (double)N, acc[1] / (double)N};
 }
 
 // ---- lane exchanges on the vector ALU ----
@@ -662,7 +663,7 @@ hipError_t launch_block_heterogeneity(const Dims& dm, const void* k, const void*
   const int dd = dm.d * dm.d;
   double* partial = workspace;
   double* hbar = workspace + (size_t)dm.bh() * plan.n_chunks * dd;
-  const dim3 g1(plan.n_chunks, dm.bh()), g2(dd / 256, dm.bh()), g3(dm.N, dm.bh());
+  const dim3 g1(plan.n_chunks, dm.bh()), g2(dd / 512, dm.bh()), g3(dm.N, dm.bh());
 #define PISA_HET(T, DD)                                                                                \
   do {                                                                                                  \
     if (hsum) {                                                                                         \
