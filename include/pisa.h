@@ -166,10 +166,13 @@ int32_t pisa_select(const pisa_shape* shape, const double* qbar64, const double*
  * k_top == N reproduces dense_attention; k_top == 0 is the pure approximation.
  * N up to 4096 blocks.  `workspace` must hold pisa_workspace_bytes(shape) when k_top < N and
  * kbar is given (it may be NULL otherwise); its contents are overwritten.
- * bf16, block 64, N >= 256, density k_top / N at most 20 %, workspace given: which two 64-row
+ * bf16, block 64, N >= 256, density k_top / N at most 20 %, more than 320 workgroups of 128 rows
+ * (batch * heads * ceil(seq_len / 128)), workspace given: which two 64-row
  * query blocks travel in one workgroup is decided from idx (blocks whose rows overlap most are
  * paired, three small launches ahead of the attention kernel), which changes the order of the
  * fp32 sums and nothing else; every entry point decides the same way for the same idx.
+ * Calls with few workgroups run a kernel of their own (64 rows a workgroup, no pairing); which one
+ * runs depends on the shape and k_top alone.
  * (PISA_NO_PAIRING=1 in the environment, read once per process, keeps neighbours together.)
  */
 int32_t pisa_attention(const pisa_shape* shape, const void* q, const void* k, const void* v,
@@ -209,7 +212,8 @@ int32_t pisa_attention_static(const pisa_shape* shape, const void* q, const void
  * What it saves is launches, which is what short sequences pay for (the paper's remark on
  * 4K-token inputs): on the bf16 path the statistics kernels write the attention kernel's
  * centroid tiles and packed hsum directly (no pre-pass), and for N <= 128 blocks the reduction
- * of the partial H sums shares the selection's launch: three launches instead of five.
+ * of the partial H sums shares the selection's launch, in bf16 and in fp32: three launches instead
+ * of five (bf16) or four (fp32).
  *   q, k, v    device, shape->dtype, [batch,heads,seq_len,head_dim]
  *   k_top      number of exact blocks per query block, 0 .. N (pisa_topk_count)
  *   out, lse   as for pisa_attention (lse may be NULL)

@@ -72,8 +72,8 @@ StatsPlan matrix_bound_plan(const Dims& dm) {
   // through, plus the partial sums, which cost about a quarter of a block each to write and read
   // again.  fp32, 8 heads of 4 500 tokens: 288 workgroups of two blocks (four on the fullest unit)
   // 33.0 us, 192 of three 25.7 us.  fp64 sums of 24 heads of 4 608: 432 workgroups of four blocks or
-  // 216 of eight, eight on the fullest unit either way, 84 us both; half the partial sums take their
-  // reduction from 10.0 to 5.9 us.
+  // 216 of eight, eight on the fullest unit either way, took the same (78 us now); half the partial sums
+  // take their reduction from 10.0 to 6.3 us.
   if (!few_blocks(dm)) return stats_plan(dm);
   int best = 1;
   double best_cost = 1e300;

@@ -1025,7 +1025,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
 // its time is one workgroup's: a chain of tiles, each a load, a softmax and two products.  Here a workgroup has
 // half the rows and a wave half the keys: a tile takes half as long, a sparse workgroup walks its own index
 // row instead of the union of two, and twice as many CUs work.  The price is that every tile is loaded
-// for 64 rows instead of 128.  2 heads of 1 000 tokens, r = 0.8: one call 31.6 -> 24.7 us.
+// for 64 rows instead of 128.  2 heads of 1 000 tokens, r = 0.8: one call 31.6 -> 24.0 us.
 // Wave w owns rows 32 (w >> 1) .. + 31 of the query tile and half e = w & 1 of the keys of every staged
 // tile; staging, operand layouts and the trip pipeline are the main kernel's.  The two partial results of
 // a row (each with a running maximum of its own) meet in LDS once, before Phase 3, and each wave of the

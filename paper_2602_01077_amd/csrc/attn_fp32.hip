@@ -19,7 +19,7 @@
 //
 // Bound by the fp32 matrix instruction (256 flop per clock and CU) and, on sequences of a few thousand
 // tokens, by how evenly the workgroups divide over the CUs.  8 heads of 4 500 tokens, head_dim 128, r = 0.85:
-// 1 080 us as a vector-ALU kernel (four threads per row, keys and probabilities through LDS), 217 us now;
+// 1 080 us as a vector-ALU kernel (four threads per row, keys and probabilities through LDS), 221 us now;
 // 2 heads of 1 024, head_dim 64, r = 0.75: 69 us, now 12 us.
 //
 // The three phases of Alg. 1 run inside one running-max softmax:

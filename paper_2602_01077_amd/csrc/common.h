@@ -41,9 +41,9 @@ StatsPlan stats_plan(const Dims& dm);
 StatsPlan matrix_bound_plan(const Dims& dm);
 
 // What the fused forward call asks of the statistics launches beyond the plain outputs (all
-// optional; bf16 only): the centroid tiles and the packed hsum in the form the attention kernel
-// reads (they replace its pre-pass), and leaving the reduction of the partial H sums to a later
-// launch.
+// optional): the centroid tiles and the packed hsum in the form the bf16 attention kernel
+// reads (they replace its pre-pass; bf16 only), and leaving the reduction of the partial H sums to a
+// later launch (either type).
 struct StatsExtras {
   void* kcen = nullptr;          // bf16 [bh][npad][d]: kbar_j
   void* vbar = nullptr;          // bf16 [bh][npad][d]: vsum_j / B_j

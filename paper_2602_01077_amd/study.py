@@ -157,7 +157,7 @@ def l2_miss_cost_study(args):
     of the all-hit lists together), so both launches walk neighbour pairs."""
     os.environ["PISA_NO_PAIRING"] = "1"            # read by the library at its first attention call
     dev = torch.device("cuda:0")
-    w = WORKLOADS["wan"]
+    w = WORKLOADS["wan"].with_(block=args.block)
     q, k, v = make_qkv(w, device=dev)
     shape = pisa.make_shape(q, w.block)
     ws = pisa.alloc_workspace(shape, dev)
@@ -169,7 +169,7 @@ def l2_miss_cost_study(args):
     a, b = idx[0, :, 0:n - 1:2].long(), idx[0, :, 1:n:2].long()
     hit = torch.zeros(a.shape[0], a.shape[1], n, dtype=torch.bool, device=dev).scatter_(2, a, True)
     shared = hit.gather(2, b).float().sum(dim=2).mean().item()
-    pairs = int(round(k_top - shared))
+    pairs = int(round(k_top - shared)) if w.block == 64 else 0      # a block-128 workgroup walks one row
     g = torch.Generator(device="cpu")
     g.manual_seed(0)
     perm = torch.randperm(n - 1, generator=g)
@@ -229,6 +229,7 @@ def main():
     s.add_argument("--graph", action="store_true", help="also time the path replayed from a captured HIP graph")
     m = sub.add_parser("l2-miss-cost")
     m.add_argument("--reps", type=int, default=6)
+    m.add_argument("--block", type=int, choices=[64, 128], default=64)
     args = ap.parse_args()
     {"error": error_study, "speed": speed_study, "l2-miss-cost": l2_miss_cost_study}[args.cmd](args)
 
