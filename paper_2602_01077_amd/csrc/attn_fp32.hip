@@ -1,26 +1,26 @@
 // fp32 attention path (dense and PISA) on the fp32 matrix instruction v_mfma_f32_16x16x4_f32.
 //
-// Workgroup = 8 wavefronts = RG row groups of 16 query rows x KG key groups.  Keys are walked in
-// pieces of 16 rows; a trip stages KG consecutive pieces of K and V in LDS and each wave takes its
-// row group against its own piece, with a running maximum, row sum and output of its own; the KG
+// Workgroup = 4 or 8 wavefronts on 32 (or 16) query rows.  Keys are walked in pieces of 16 rows: wave w takes pieces
+// w, w + KG, ... against all of the workgroup's rows, with a running maximum, row sum and output of its own; the KG
 // partial results of a row meet in LDS at the end.  As in the bf16 kernels everything is transposed:
 //     S^T (keys x queries) = K_piece (keys x d) * Q^T,    O^T (d x queries) = V_piece^T * P^T
-// so that a lane owns one query column and the S^T accumulator is already the B operand of the
+// so that a lane owns one query column per 16 rows and the S^T accumulator is already the B operand of the
 // second product: lane (i = lane % 16, g = lane / 16) holds keys 4 g .. 4 g + 3 of query i, and
 // contraction step r of the second product takes key 4 g + r of every g.  Both A operands come from
-// ds_read_b128: four channels of K feed four contraction steps (K rows XOR their 16-byte chunk index
-// with the row, so the 16 rows of a read hit different banks), four channels of V feed four 16-channel
-// tiles of O^T (tile t <-> channels 4 i + t; a row is read in one contiguous line).
+// ds_read_b128, each read serving both 16-row tiles: four channels of K feed four contraction steps (K rows XOR their
+// 16-byte chunk index with the row, so the 16 rows of a read hit different banks), four channels of V feed four
+// 16-channel tiles of O^T (tile t <-> channels 4 i + t; a row is read in one contiguous line).
 //
-// Stages are filled global -> LDS without registers.  Double buffered (NBUF = 2) the loads of trip t + 1
-// are in flight during all of trip t, one barrier a trip; where two buffers do not fit (NBUF = 1) K and V
-// take turns: V of trip t is in flight while S^T of trip t is computed, K of trip t + 1 while O^T is, two
-// barriers a trip.
+// A wave fills its stages (one K piece, one V piece) itself, global -> LDS without registers, and nobody else reads them:
+// the walk has no barriers, a wave waits for its own loads only.  V of a piece is in flight while S^T is computed, the
+// next K while O^T is.  The centroids' pieces follow the exact ones in the same walk.
 //
-// Bound by the fp32 matrix instruction (256 flop per clock and CU) and, on sequences of a few thousand
-// tokens, by how evenly the workgroups divide over the CUs.  8 heads of 4 500 tokens, head_dim 128, r = 0.85:
-// 1 080 us as a vector-ALU kernel (four threads per row, keys and probabilities through LDS), 221 us now;
-// 2 heads of 1 024, head_dim 64, r = 0.75: 69 us, now 12 us.
+// Bound by the fp32 matrix instruction (256 flop per clock and CU), by what a workgroup does once (index row, first
+// loads, merge: 9 us) and by how evenly the workgroups divide over the CUs.  8 heads of 4 500 tokens, head_dim 128,
+// r = 0.85, us for the attention step: 201 with stages shared by eight waves (two barriers a trip, 16 rows to a wave), 184
+// with stages of a wave's own, 170 with the last row groups in halves (dense 899, 820, 749); 2 heads of 1 024, head_dim 64,
+// r = 0.75: 11.8, now 11.3, at head_dim 128 19.1, now 14.5.  With the loads taken out the first takes 167 instead of
+// 184, without the softmax 170.
 //
 // The three phases of Alg. 1 run inside one running-max softmax:
 //   Phase 1  pieces of the selected blocks S_i (all of the sequence for dense attention)
@@ -28,6 +28,8 @@
 //            masked; values vsum_j, whose 1 / B_j goes into the probability; the same mass is l_tail
 //   Phase 3  O^T += hsum^T (w Q)^T, the second product with hsum's rows in the place of V's and Q's
 //            registers in the place of P's
+#include <type_traits>
+
 #include "common.h"
 
 namespace pisa {
@@ -37,7 +39,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
 
 constexpr int kPiece = 16;      // keys per piece
-constexpr int kWaves = 8;       // wavefronts per workgroup
+constexpr int kCusPerXcd = 32;
+typedef __attribute__((address_space(4))) int32_t ConstInt;
+
+// Wavefronts per SIMD: what registers allow at 32 rows a workgroup, in workgroups that fit the LDS.
+constexpr int waves_per_simd(int d, int kg) { return d == 128 || kg == 8 ? 2 : 3; }
 
 struct P32 {
   const float* q;
@@ -49,12 +55,24 @@ struct P32 {
   const int32_t* idx;
   float* out;
   float* lse;
-  int L, B, N, k_top, n_groups, total;    // n_groups: row groups of a head per workgroup; total: workgroups with work
+  int L, B, N, k_top, n_groups, total;    // n_groups: row groups of a head; total: of all heads
+  int per_xcd, n_whole;                   // groups per XCD; how many of them a workgroup takes whole
   float scale;
   int dense;
 };
 
-__device__ inline void wait_async_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
+// s_waitcnt vmcnt(N) / lgkmcnt(0) with the other counters left alone (gfx9 encoding).
+template <int N> __device__ inline void wait_loads() {
+  static_assert(N >= 0 && N < 16, "low four bits of vmcnt");
+  asm volatile("" : : : "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | N);
+  asm volatile("" : : : "memory");
+}
+__device__ inline void wait_lds() {
+  asm volatile("" : : : "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+  asm volatile("" : : : "memory");
+}
 
 // Largest of the four lanes that share lane % 16 (row swaps on the vector ALU instead of LDS shuffles).
 __device__ inline float max_over_g(float x) {
@@ -64,105 +82,142 @@ __device__ inline float max_over_g(float x) {
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
-// One LDS-DMA instruction: 64 lanes x 16 bytes from per-lane addresses to 1 KB at `lds` (wave-uniform).
-// Inline asm keeps the compiler from waiting on it before unrelated LDS reads; a stage is read only
-// after wait_async_loads() + barrier.  (M0 needs one wait state before the instruction reads it.)
-__device__ inline void dma_1kb(const float* src, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-               :
-               : "s"(lds), "v"(src)
-               : "memory", "m0");
+// One LDS-DMA instruction: 64 lanes x 16 bytes, global (base + voff + IMM) -> LDS (M0 + IMM + 16 lane).
+// Inline asm keeps the compiler from waiting on it before unrelated LDS reads; a stage is read only after wait_loads().
+// (M0 needs one wait state before the instruction reads it.)
+__device__ inline void set_dma_lds_base(unsigned lds /* wave-uniform */) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" : : "s"(lds) : "memory", "m0");
+}
+template <int IMM> __device__ inline void dma_1kb(unsigned voff, const float* base /* wave-uniform */) {
+  asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" : : "v"(voff), "s"(base), "n"(IMM) : "memory");
+}
+__device__ inline void dma_1kb_far(const float* src) {
+  asm volatile("global_load_lds_dwordx4 %0, off" : : "v"(src) : "memory");
 }
 
-template <int D, int RG, int KG, int NBUF>
-__global__ __launch_bounds__(64 * kWaves, NBUF * KG * D > 512 ? 2 : 4) void attn_fp32_kernel(P32 p) {
-  static_assert(RG * KG == kWaves, "eight wavefronts");
+// One workgroup's work: RT * 16 query rows from row0 of head bh.
+template <int D, int RT, int KG>
+__device__ __forceinline__ void attend_rows(const P32& p, const size_t bh, const int row0, float* stage_mem,
+                                            unsigned int* chosen, float (*part_s)[KG][32]) {
   constexpr int NS = D / 16;              // 16-channel slices
   constexpr int NT = D / 16;              // O^T tiles of 16 channels
   constexpr int PIECE_F = kPiece * D;     // floats per piece
-  constexpr int STAGE_F = KG * PIECE_F;   // floats per stage (K or V)
-  constexpr int NLD = STAGE_F * 4 / 1024 / kWaves;   // 1 KB loads per wave and stage
+  constexpr int NLD = PIECE_F * 4 / 1024; // 1 KB loads per piece
   constexpr int RPL = 1024 / (D * 4);     // rows per load
-  __shared__ __attribute__((aligned(1024))) float stage[2 * NBUF * STAGE_F];    // (K | V) x NBUF
-  __shared__ unsigned short list[kMaxBlocks];
-  __shared__ unsigned int chosen[kMaxBlocks / 32];
-  __shared__ float part_s[3][KG][RG * 16];   // m, l, l_tail of every key group
-
-  // Each XCD gets a contiguous range of (head, row group) items, so that its L2 serves one head.
-  const int per_xcd = (p.total + 7) / 8;
-  if ((int)blockIdx.x / 8 >= per_xcd) return;
-  const int item = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (item >= p.total) return;
-  const size_t bh = item / p.n_groups;
-  const int row0 = (item % p.n_groups) * (RG * 16);
-
+  constexpr int LPR = 64 / RPL;           // lanes (16-byte chunks) per row
+  constexpr int WAVE_F = 2 * PIECE_F;     // a wave's own stages: K | V
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rg = wave % RG, kg = wave / RG;
+  const int kg = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, g = lane >> 4;
   const int L = p.L, N = p.N;
-  const float* kh = p.k + bh * (size_t)L * D;
-  const float* vh = p.v + bh * (size_t)L * D;
-  const int q_row = row0 + 16 * rg + i;
-  const int tpb = p.B / kTile;
-  LDS_PTR(float) ks = (LDS_PTR(float)) & stage[0];
-  const unsigned lds_addr = (unsigned)(unsigned long long)ks;
+  const bool approx = !p.dense && p.k_top < N && p.kbar != nullptr;
+  const bool first_order = approx && p.hsum != nullptr;
+  LDS_PTR(float) ks = (LDS_PTR(float))stage_mem + kg * WAVE_F;
+  const unsigned lds_addr = __builtin_amdgcn_readfirstlane((unsigned)(unsigned long long)ks);
 
-  // ---- Q^T operand: channels 16 s + 4 g + u of this lane's row ----
-  f32x4 q[NS];
-#pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    q[s] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    if (q_row < L) q[s] = *reinterpret_cast<const f32x4*>(p.q + (bh * (size_t)L + q_row) * D + 16 * s + 4 * g);
-  }
-
-  // ---- index row: list in LDS, bitmask for Phase 2 ----
+  // The index row is read through the scalar cache, an entry at a time, by the wave that needs it.
+  const ConstInt* idx_row = nullptr;
+  int j_mine = -1;
   if (!p.dense) {
     const int32_t* row = p.idx + (bh * N + row0 / p.B) * (size_t)p.k_top;
-    if (tid < kMaxBlocks / 32) chosen[tid] = 0u;
+    idx_row = (const ConstInt*)(unsigned long long)row;
+    if (tid < p.k_top) j_mine = row[tid];
+  }
+
+  // ---- Q^T operand: channels 16 s + 4 g + u of this lane's rows ----
+  f32x4 q[RT][NS];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int q_row = row0 + 16 * rt + i;
+      q[rt][s] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      if (q_row < L) q[rt][s] = *reinterpret_cast<const f32x4*>(p.q + (bh * (size_t)L + q_row) * D + 16 * s + 4 * g);
+    }
+
+  // ---- the pieces of the walk: those of the exact blocks, then those of the centroids; wave kg takes kg, kg + KG, ... ----
+  const int shift = p.B == kTile ? 2 : 3;                         // pieces per block: 4 or 8
+  const int n_exact = p.dense ? (L + kPiece - 1) / kPiece : p.k_top << shift;
+  const int n_all = n_exact + (approx ? (N + kPiece - 1) / kPiece : 0);
+  // First row of piece pc in its source (keys or centroids), or -1: an ignored entry, or rows past the end.
+  auto first_row = [&](int pc) -> int {
+    if (pc >= n_exact) return (pc - n_exact) * kPiece;
+    if (p.dense) return pc * kPiece;
+    const int j = idx_row[pc >> shift];
+    const int r = j * p.B + (pc & ((1 << shift) - 1)) * kPiece;
+    return (unsigned)j < (unsigned)N && r < L ? r : -1;
+  };
+  // Loads of one piece (16 rows from `row` of a matrix of n_rows) to `dst` in LDS: K format if KF.  Rows past the
+  // end repeat the last one (the reader masks them).
+  const unsigned voff_v = (unsigned)lane * 16, voff_k = (unsigned)(lane / LPR * LPR + ((lane % LPR) ^ (lane / LPR))) * 16;
+  auto load_rows = [&](const float* src, int row, int n_rows, auto kf_tag, unsigned dst) {
+    constexpr bool KF = decltype(kf_tag)::value;
+    row = __builtin_amdgcn_readfirstlane(max(row, 0));
+    if (row + kPiece <= n_rows) {
+      const float* base = src + (size_t)row * D;
+      unsigned vo = KF ? voff_k : voff_v;
+      asm volatile("" : "+v"(vo));           // the variants below are made here, not kept in registers all along
+#pragma unroll
+      for (int u0 = 0; u0 < NLD; u0 += 4) {                       // the immediate offset reaches 4 KB
+        set_dma_lds_base(dst + u0 * 1024);
+        const float* b = base + u0 * 256;
+        dma_1kb<0>(KF ? vo ^ (u0 * RPL * 16) : vo, b);
+        dma_1kb<1024>(KF ? vo ^ ((u0 + 1) * RPL * 16) : vo, b);
+        dma_1kb<2048>(KF ? vo ^ ((u0 + 2) * RPL * 16) : vo, b);
+        dma_1kb<3072>(KF ? vo ^ ((u0 + 3) * RPL * 16) : vo, b);
+      }
+    } else {
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+#pragma unroll 1
+      for (int u = 0; u < NLD; ++u) {
+        const int r_in = u * RPL + ln / LPR, ch = ln % LPR;
+        set_dma_lds_base(dst + u * 1024);
+        dma_1kb_far(src + (size_t)min(row + r_in, n_rows - 1) * D + 4 * (KF ? ch ^ r_in : ch));
+      }
+    }
+  };
+  const float* kh = p.k + bh * (size_t)L * D;
+  const float* vh = p.v + bh * (size_t)L * D;
+  const float* kc = p.kbar + (approx ? bh * (size_t)N * D : 0);
+  const float* vc = p.vsum + (approx ? bh * (size_t)N * D : 0);
+  auto load_k = [&](int pc, int row) {
+    if (pc < n_exact) load_rows(kh, row, L, std::true_type{}, lds_addr);
+    else load_rows(kc, row, N, std::true_type{}, lds_addr);
+  };
+  auto load_v = [&](int pc, int row) {
+    if (pc < n_exact) load_rows(vh, row, L, std::false_type{}, lds_addr + PIECE_F * 4);
+    else load_rows(vc, row, N, std::false_type{}, lds_addr + PIECE_F * 4);
+  };
+  int pc = kg, row = -1;
+  if (pc < n_all) {
+    row = first_row(pc);
+    load_k(pc, row);
+    load_v(pc, row);
+  }
+
+  // ---- bitmask of the index row, for the centroids ----
+  if (approx) {
+    for (int w = tid; w < kMaxBlocks / 32; w += 64 * KG) chosen[w] = 0u;
     __syncthreads();
-    for (int t = tid; t < p.k_top; t += 64 * kWaves) {
-      const int j = row[t];
-      const bool ok = (unsigned)j < (unsigned)N;        // entries outside [0, N) are ignored
-      list[t] = ok ? (unsigned short)j : (unsigned short)0xffff;
-      if (ok) atomicOr(&chosen[j >> 5], 1u << (j & 31));
+    for (int t = tid, j = j_mine; t < p.k_top; t += 64 * KG) {
+      if (t != tid) j = p.idx[(bh * N + row0 / p.B) * (size_t)p.k_top + t];
+      if ((unsigned)j < (unsigned)N) atomicOr(&chosen[j >> 5], 1u << (j & 31));   // entries outside [0, N) are ignored
     }
     __syncthreads();
   }
 
-  // Key row at which piece `pc` of Phase 1 starts, or -1 (an ignored entry, or past the end).
-  const int n_exact = (p.dense ? (L + kTile - 1) / kTile : p.k_top * tpb) * (kTile / kPiece);
-  const int block_shift = tpb == 1 ? 2 : 3;                       // pieces per block: 4 or 8
-  auto exact_row = [&](int pc) -> int {
-    if (pc >= n_exact) return -1;
-    if (p.dense) return pc * kPiece < L ? pc * kPiece : -1;
-    const int j = __builtin_amdgcn_readfirstlane((int)list[pc >> block_shift]);
-    if (j == 0xffff) return -1;
-    const int r = j * p.B + (pc & ((1 << block_shift) - 1)) * kPiece;
-    return r < L ? r : -1;
-  };
-
-  // This wave's share of a stage (K or V of buffer `buf`): 1 KB loads NLD wave .. NLD wave + NLD - 1, RPL
-  // rows each.  Rows past the end of the source repeat its last row (the reader masks them).
-  auto load_stage = [&](const float* src, int first_pc, int n_rows, bool kfmt, bool by_list, int buf) {
+  f32x4 o[RT][NT];
+  float m[RT], l[RT], l_tail[RT];            // log2 domain; l, l_tail: this lane's keys only
+  bool far[RT];                              // uniform: some row's maximum lies beyond +-2^20
 #pragma unroll
-    for (int u = 0; u < NLD; ++u) {
-      const int srow = (wave * NLD + u) * RPL;                    // first stage row of this load
-      const int pc = first_pc + srow / kPiece;
-      const int base = by_list ? exact_row(pc) : pc * kPiece;
-      const int r_in = srow % kPiece + lane / (64 / RPL);         // row inside the piece
-      const int ch = lane % (64 / RPL);                           // 16-byte chunk of the row in LDS
-      const int row = min(max(base, 0) + r_in, n_rows - 1);
-      const int src_ch = kfmt ? ch ^ r_in : ch;
-      dma_1kb(src + (size_t)row * D + 4 * src_ch,
-              lds_addr + ((2 * buf + (kfmt ? 0 : 1)) * STAGE_F + srow * D) * 4);
-    }
-  };
-
-  f32x4 o[NT];
+  for (int rt = 0; rt < RT; ++rt) {
 #pragma unroll
-  for (int t = 0; t < NT; ++t) o[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY, l = 0.f, l_tail = 0.f;     // log2 domain; l, l_tail: this lane's keys only
+    for (int t = 0; t < NT; ++t) o[rt][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    m[rt] = -INFINITY;
+    l[rt] = l_tail[rt] = 0.f;
+    far[rt] = false;
+  }
   // scale * log2(e) in two fp32 parts, so that the base-2 logit is the scaled product to fp32 rounding; both
   // positive, so that an infinite product stays what it is
   const double c = (double)p.scale * 1.4426950408889634074;
@@ -170,24 +225,28 @@ __global__ __launch_bounds__(64 * kWaves, NBUF * KG * D > 512 ? 2 : 4) void attn
   if ((double)c_hi >= c) c_hi = __uint_as_float(__float_as_uint(c_hi) - 1u);
   const float c_lo = (float)(c - (double)c_hi);
 
-  // S^T of this wave's staged piece: element r = key 4 g + r.
-  auto scores = [&](int buf) -> f32x4 {
-    LDS_PTR(const float) kr = ks + 2 * buf * STAGE_F + (kPiece * kg + i) * D;
-    f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0, kv, kn = *reinterpret_cast<LDS_PTR(const f32x4)>(kr + 4 * (g ^ i));
+  // S^T of the staged piece: element r = key 4 g + r.
+  auto scores = [&](f32x4 (&sc)[RT]) {
+    LDS_PTR(const float) kr = ks + i * D;
+    f32x4 a[RT][2], kv, kn = *reinterpret_cast<LDS_PTR(const f32x4)>(kr + 4 * (g ^ i));
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) a[rt][0] = a[rt][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       kv = kn;                               // one read ahead of the products
       if (s + 1 < NS) kn = *reinterpret_cast<LDS_PTR(const f32x4)>(kr + 4 * ((4 * (s + 1) + g) ^ i));
-      a0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[0], q[s][0], a0, 0, 0, 0);
-      a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[1], q[s][1], a1, 0, 0, 0);
-      a0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[2], q[s][2], a0, 0, 0, 0);
-      a1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[3], q[s][3], a1, 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+          a[rt][u & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[u], q[rt][s][u], a[rt][u & 1], 0, 0, 0);
     }
-    return a0 + a1;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) sc[rt] = a[rt][0] + a[rt][1];
   };
   // O^T += (staged rows)^T b, b = B operand of the piece's 16 rows.
-  auto add_values = [&](const f32x4 b, int buf) {
-    LDS_PTR(const float) v0 = ks + (2 * buf + 1) * STAGE_F + (kPiece * kg + 4 * g) * D + 4 * i;
+  auto add_values = [&](const f32x4 (&b)[RT], LDS_PTR(const float) piece) {
+    LDS_PTR(const float) v0 = piece + 4 * g * D + 4 * i;
     constexpr int NR = NT;                   // reads: row r of the four, half hf of its channels
     f32x4 vv, vn = *reinterpret_cast<LDS_PTR(const f32x4)>(v0);
 #pragma unroll
@@ -198,15 +257,17 @@ __global__ __launch_bounds__(64 * kWaves, NBUF * KG * D > 512 ? 2 : 4) void attn
         vn = *reinterpret_cast<LDS_PTR(const f32x4)>(v0 + (n + 1) / (NT / 4) * D + 64 * ((n + 1) % (NT / 4)));
 #pragma unroll
       for (int t = 0; t < 4; ++t)
-        o[4 * hf + t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[t], b[r], o[4 * hf + t], 0, 0, 0);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+          o[rt][4 * hf + t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[t], b[rt][r], o[rt][4 * hf + t], 0, 0, 0);
     }
   };
   // Clears what add_values would read of a piece's rows from `rows` on: copies of the last row there is, whose
-  // probability of 0 would make a NaN of an infinity.  (Waves that share the piece write the same zeros.)
-  auto clear_absent = [&](int rows, int buf) {
+  // probability of 0 would make a NaN of an infinity.
+  auto clear_absent = [&](int rows) {
     int ln = lane;
     asm volatile("" : "+v"(ln));               // the addresses are made here, not kept in registers all along
-    LDS_PTR(float) v0 = ks + (2 * buf + 1) * STAGE_F + (kPiece * kg + 4 * (ln >> 4)) * D + 4 * (ln & 15);
+    LDS_PTR(float) v0 = ks + PIECE_F + 4 * (ln >> 4) * D + 4 * (ln & 15);
 #pragma unroll 1
     for (int r = 0; r < 4; ++r) {
       if (4 * (ln >> 4) + r >= rows)
@@ -215,27 +276,25 @@ __global__ __launch_bounds__(64 * kWaves, NBUF * KG * D > 512 ? 2 : 4) void attn
           *reinterpret_cast<LDS_PTR(f32x4)>(v0 + r * D + 64 * hf) = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
   };
-  // Running maximum takes in the logits x (bias included, log2 domain up to the bias); returns the
-  // probabilities and adds their sum to l.
-  bool far = false;                          // uniform: some row's maximum lies beyond +-2^20
-  auto softmax = [&](const f32x4 s, const f32x4 bias) -> f32x4 {
+  // Running maximum of row tile rt takes in the logits s * c + bias (log2 domain); returns the probabilities.
+  auto softmax = [&](int rt, const f32x4 s, const f32x4 bias) -> f32x4 {
     f32x4 z;
 #pragma unroll
     for (int r = 0; r < 4; ++r) z[r] = fmaf(s[r], c_hi, bias[r]);
     const float t = max_over_g(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])));
-    const float m_new = fmaxf(m, t);
+    const float m_new = fmaxf(m[rt], t);
     const float m_safe = m_new == -INFINITY ? 0.f : m_new;
-    if (__any(m_new != m)) {
-      const float corr = __builtin_amdgcn_exp2f(m - m_safe);
-      l *= corr;
-      l_tail *= corr;
+    if (__any(m_new != m[rt])) {
+      const float corr = __builtin_amdgcn_exp2f(m[rt] - m_safe);
+      l[rt] *= corr;
+      l_tail[rt] *= corr;
 #pragma unroll
-      for (int t2 = 0; t2 < NT; ++t2) o[t2] *= corr;
-      m = m_new;
-      far = __any(!(fabsf(m_new) <= 0x1p20f));
+      for (int t2 = 0; t2 < NT; ++t2) o[rt][t2] *= corr;
+      m[rt] = m_new;
+      far[rt] = __any(!(fabsf(m_new) <= 0x1p20f));
     }
     f32x4 e;
-    if (!far) {
+    if (!far[rt]) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) e[r] = __builtin_amdgcn_exp2f(fmaf(s[r], c_hi, fmaf(s[r], c_lo, bias[r] - m_safe)));
     } else {
@@ -245,176 +304,198 @@ __global__ __launch_bounds__(64 * kWaves, NBUF * KG * D > 512 ? 2 : 4) void attn
 #pragma unroll
       for (int r = 0; r < 4; ++r) e[r] = __builtin_amdgcn_exp2f(s[r] * c_hi - (m_safe - bias[r]));
     }
-    l += (e[0] + e[1]) + (e[2] + e[3]);
     return e;
   };
 
-  // The walk over `n` pieces of (src_k, src_v): `absorb(pc, buf, e)` turns this wave's staged K piece into the B
-  // operand e of the second product and returns the rows the piece has, 0 if the wave has nothing in this trip.
-  auto walk = [&](const float* src_k, const float* src_v, int n, int n_rows, bool by_list, auto absorb) {
-    load_stage(src_k, 0, n_rows, true, by_list, 0);
-    if (NBUF == 2) load_stage(src_v, 0, n_rows, false, by_list, 0);
-    int buf = 0;
-    for (int pc = 0; pc < n; pc += KG) {
-      wait_async_loads();
-      __syncthreads();                       // this trip's K (and V, if double buffered) has landed
-      f32x4 e = {0.f, 0.f, 0.f, 0.f};
-      if (NBUF == 2) {
-        if (pc + KG < n) {                   // the other buffer was used up before the barrier
-          load_stage(src_k, pc + KG, n_rows, true, by_list, buf ^ 1);
-          load_stage(src_v, pc + KG, n_rows, false, by_list, buf ^ 1);
-        }
-        const int rows = absorb(pc + kg, buf, e);
-        if (rows > 0) {
-          if (rows < kPiece) clear_absent(rows, buf);
-          add_values(e, buf);
-        }
-        buf ^= 1;
+  const int last_rows = L - (N - 1) * p.B;
+  const float b_full = log2f((float)p.B), b_last = log2f((float)last_rows);
+  const float inv_full = 1.f / (float)p.B, inv_last = 1.f / (float)last_rows;
+
+  // ---- Phases 1 and 2 ----
+  // No barriers: the stages are the wave's own.  A load may overwrite a stage once this wave's reads of it have returned.
+  wait_loads<0>();                           // Q, and the first piece
+  while (pc < n_all) {
+    const int pc_n = pc + KG;
+    const bool more = pc_n < n_all;
+    const int row_n = more ? first_row(pc_n) : -1;
+    if (row < 0) {                           // nothing to attend here
+      wait_loads<0>();
+      if (more) {
+        load_k(pc_n, row_n);
+        load_v(pc_n, row_n);
+      }
+    } else {
+      f32x4 e[RT], bias, wt = {1.f, 1.f, 1.f, 1.f};
+      wait_loads<NLD>();                     // K has landed; V may be on its way
+      scores(e);
+      wait_lds();
+      if (more) load_k(pc_n, row_n);
+      const bool cen = pc >= n_exact;
+      const int rows = (cen ? N : L) - row;
+      if (!cen) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bias[r] = 4 * g + r < rows ? 0.f : -INFINITY;
       } else {
-        load_stage(src_v, pc, n_rows, false, by_list, 0);
-        const int rows = absorb(pc + kg, 0, e);
-        wait_async_loads();
-        __syncthreads();                     // V has landed; K is used up
-        if (pc + KG < n) load_stage(src_k, pc + KG, n_rows, true, by_list, 0);
-        if (rows > 0) {
-          if (rows < kPiece) clear_absent(rows, 0);
-          add_values(e, 0);
+        const int j0 = row + 4 * g;          // this lane's first centroid
+        const unsigned bits = chosen[j0 >> 5] >> (j0 & 31);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          bias[r] = (j0 + r >= N || ((bits >> r) & 1u)) ? -INFINITY : (j0 + r == N - 1 ? b_last : b_full);
+          wt[r] = j0 + r == N - 1 ? inv_last : inv_full;
         }
       }
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        e[rt] = softmax(rt, e[rt], bias);
+        const float sum = (e[rt][0] + e[rt][1]) + (e[rt][2] + e[rt][3]);
+        l[rt] += sum;
+        l_tail[rt] += cen ? sum : 0.f;
+        e[rt] *= wt;
+      }
+      if (more) wait_loads<NLD>();           // V has landed; the next K may be on its way
+      else wait_loads<0>();
+      if (rows < kPiece) clear_absent(rows);
+      add_values(e, ks + PIECE_F);
+      wait_lds();
+      if (more) load_v(pc_n, row_n);
     }
-  };
-
-  // ---- Phase 1: exact pieces ----
-  if (n_exact > 0)
-    walk(kh, vh, n_exact, L, true, [&](int pc, int buf, f32x4& e) -> int {
-      const int first = exact_row(pc);
-      if (first < 0) return 0;
-      f32x4 bias;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) bias[r] = first + 4 * g + r < L ? 0.f : -INFINITY;
-      e = softmax(scores(buf), bias);
-      return L - first;
-    });
-
-  // ---- Phase 2: centroid pieces ----
-  const bool approx = !p.dense && p.k_top < N && p.kbar != nullptr;
-  if (approx) {
-    const int last_rows = L - (N - 1) * p.B;
-    const float b_full = log2f((float)p.B), b_last = log2f((float)last_rows);
-    const float inv_full = 1.f / (float)p.B, inv_last = 1.f / (float)last_rows;
-    const int n_cen = (N + kPiece - 1) / kPiece;
-    __syncthreads();                         // every wave is done with the stages
-    walk(p.kbar + bh * (size_t)N * D, p.vsum + bh * (size_t)N * D, n_cen, N, false,
-         [&](int pc, int buf, f32x4& e) -> int {
-           if (pc >= n_cen) return 0;
-           const int j0 = pc * kPiece + 4 * g;          // this lane's first centroid
-           const unsigned bits = chosen[j0 >> 5] >> (j0 & 31);
-           f32x4 bias;
-#pragma unroll
-           for (int r = 0; r < 4; ++r)
-             bias[r] = (j0 + r >= N || ((bits >> r) & 1u)) ? -INFINITY : (j0 + r == N - 1 ? b_last : b_full);
-           e = softmax(scores(buf), bias);
-           l_tail += (e[0] + e[1]) + (e[2] + e[3]);
-#pragma unroll
-           for (int r = 0; r < 4; ++r) e[r] *= j0 + r == N - 1 ? inv_last : inv_full;
-           return N - pc * kPiece;
-         });
+    pc = pc_n;
+    row = row_n;
   }
 
-  // ---- the key groups of a row agree on one maximum ----
-  const bool first_order = approx && p.hsum != nullptr;
-  l += __shfl_xor(l, 16);
-  l += __shfl_xor(l, 32);
-  l_tail += __shfl_xor(l_tail, 16);
-  l_tail += __shfl_xor(l_tail, 32);
-  if (g == 0) {
-    part_s[0][kg][16 * rg + i] = m;
-    part_s[1][kg][16 * rg + i] = l;
-    part_s[2][kg][16 * rg + i] = l_tail;
+  // ---- the waves of a row agree on one maximum ----
+  // This wave's pieces of hsum are on their way meanwhile
+  const float* hs = p.hsum + bh * (size_t)D * D;
+  // (where a wave has two, the second goes where its K pieces went)
+  constexpr int HP = (NS + KG - 1) / KG;       // pieces of hsum per wave
+  static_assert(HP <= 2, "two stages hold a wave's pieces of hsum");
+  if (first_order) {
+    if (kg < NS) load_rows(hs, kPiece * kg, D, std::false_type{}, lds_addr + PIECE_F * 4);
+    if (HP == 2) load_rows(hs, kPiece * (KG + kg), D, std::false_type{}, lds_addr);
   }
-  __syncthreads();                           // also: every wave is done with the stages
-  if (first_order) load_stage(p.hsum + bh * (size_t)D * D, 0, D, false, false, 0);
-  float m_all = -INFINITY;
 #pragma unroll
-  for (int u = 0; u < KG; ++u) m_all = fmaxf(m_all, part_s[0][u][16 * rg + i]);
-  float l_all = 0.f, tail_all = 0.f;
-  // a group that met no key at all (maximum still -inf) holds zeros
-  auto weight = [&](float m_part) { return m_part == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_part - m_all); };
-#pragma unroll
-  for (int u = 0; u < KG; ++u) {
-    const float f = weight(part_s[0][u][16 * rg + i]);
-    l_all += part_s[1][u][16 * rg + i] * f;
-    tail_all += part_s[2][u][16 * rg + i] * f;
+  for (int rt = 0; rt < RT; ++rt) {
+    l[rt] += __shfl_xor(l[rt], 16);
+    l[rt] += __shfl_xor(l[rt], 32);
+    l_tail[rt] += __shfl_xor(l_tail[rt], 16);
+    l_tail[rt] += __shfl_xor(l_tail[rt], 32);
+    if (g == 0) {
+      part_s[0][kg][16 * rt + i] = m[rt];
+      part_s[1][kg][16 * rt + i] = l[rt];
+      part_s[2][kg][16 * rt + i] = l_tail[rt];
+    }
   }
-  {
-    const float f = weight(m);
+  __syncthreads();
+  float m_all[RT], l_all[RT], tail_all[RT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) o[t] *= f;
+  for (int rt = 0; rt < RT; ++rt) {
+    m_all[rt] = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < KG; ++u) m_all[rt] = fmaxf(m_all[rt], part_s[0][u][16 * rt + i]);
+    l_all[rt] = tail_all[rt] = 0.f;
+    // a wave that met no key at all (maximum still -inf) holds zeros
+    auto weight = [&](float m_part) { return m_part == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_part - m_all[rt]); };
+#pragma unroll
+    for (int u = 0; u < KG; ++u) {
+      const float f = weight(part_s[0][u][16 * rt + i]);
+      l_all[rt] += part_s[1][u][16 * rt + i] * f;
+      tail_all[rt] += part_s[2][u][16 * rt + i] * f;
+    }
+    const float f = weight(m[rt]);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) o[rt][t] *= f;
   }
 
   // ---- Phase 3: hsum's rows as values, w Q as probabilities ----
   if (first_order) {
-    const float w = tail_all / (float)L * p.scale;
+    wait_loads<0>();
 #pragma unroll
-    for (int s0 = 0; s0 < NS; s0 += KG) {
-      wait_async_loads();
-      __syncthreads();
+    for (int s1 = 0; s1 < NS; ++s1)
+      if (kg == s1 % KG) {                              // uniform over the wave
+        f32x4 b[RT];
 #pragma unroll
-      for (int u = 0; u < KG && s0 + u < NS; ++u)
-        if (kg == u) add_values(q[s0 + u] * w, 0);        // uniform over the wave
-      if (s0 + KG < NS) {
-        __syncthreads();
-        load_stage(p.hsum + bh * (size_t)D * D, s0 + KG, D, false, false, 0);
+        for (int rt = 0; rt < RT; ++rt) b[rt] = q[rt][s1] * (tail_all[rt] / (float)L * p.scale);
+        add_values(b, s1 < KG ? ks + PIECE_F : ks);
       }
-    }
   }
 
-  // ---- sum over the key groups, normalise, store ----
-  __syncthreads();
-  LDS_PTR(f32x4) board = (LDS_PTR(f32x4))ks;
-  static_assert((KG - 1) * RG * NT * 64 * 16 <= 2 * NBUF * STAGE_F * 4, "the partial outputs must fit the stages");
-  if (kg > 0) {
+  // ---- sum over the waves, normalise, store ----
+  // o[rt][4 hf + t][r] = channel 64 hf + 4 (4 g + r) + t: unit (rt, hf, r) is 16 bytes a lane, and a wave sums up the units
+  // kg, kg + KG, ... over all waves.  Each wave lays its own out in its own stages, which nobody else reads before the barrier.
+  constexpr int UNITS = RT * NT;
+  static_assert(UNITS * 256 <= WAVE_F, "a wave's output must fit its stages");
+  wait_loads<0>();
+  wait_lds();
+  LDS_PTR(f32x4) board = (LDS_PTR(f32x4))stage_mem;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) board[(((kg - 1) * RG + rg) * NT + t) * 64 + lane] = o[t];
-  }
-  __syncthreads();
-  if (kg > 0) return;
-#pragma unroll
-  for (int u = 0; u < KG - 1; ++u)
-#pragma unroll
-    for (int t = 0; t < NT; ++t) o[t] += board[((u * RG + rg) * NT + t) * 64 + lane];
-  if (q_row < L) {
-    // o[4 hf + t][r] = channel 64 hf + 4 (4 g + r) + t
-    const float inv_l = 1.f / l_all;
-    float* orow = p.out + (bh * (size_t)L + q_row) * D;
+  for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int hf = 0; hf < NT / 4; ++hf)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const f32x4 w = {o[4 * hf][r] * inv_l, o[4 * hf + 1][r] * inv_l, o[4 * hf + 2][r] * inv_l,
-                         o[4 * hf + 3][r] * inv_l};
-        *reinterpret_cast<f32x4*>(orow + 64 * hf + 16 * g + 4 * r) = w;
-      }
-    if (p.lse && g == 0) p.lse[bh * (size_t)L + q_row] = (m_all + log2f(l_all)) * 0.69314718055994530942f;
+      for (int r = 0; r < 4; ++r)
+        board[kg * (WAVE_F / 4) + ((rt * (NT / 4) + hf) * 4 + r) * 64 + lane] =
+            (f32x4){o[rt][4 * hf][r], o[rt][4 * hf + 1][r], o[rt][4 * hf + 2][r], o[rt][4 * hf + 3][r]};
+  __syncthreads();
+  for (int n = kg; n < UNITS; n += KG) {
+    f32x4 sum = board[n * 64 + lane];
+#pragma unroll
+    for (int u = 1; u < KG; ++u) sum += board[u * (WAVE_F / 4) + n * 64 + lane];
+    const int r = n % 4, hf = n / 4 % (NT / 4), rt = n / NT;
+    const int q_row = row0 + 16 * rt + i;
+    const float lr = RT == 2 && rt == 1 ? l_all[RT - 1] : l_all[0];
+    if (q_row < L)
+      *reinterpret_cast<f32x4*>(p.out + (bh * (size_t)L + q_row) * D + 64 * hf + 16 * g + 4 * r) = sum * (1.f / lr);
+  }
+  if (p.lse && g == 0 && kg == 0)
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      const int q_row = row0 + 16 * rt + i;
+      if (q_row < L) p.lse[bh * (size_t)L + q_row] = (m_all[rt] + log2f(l_all[rt])) * 0.69314718055994530942f;
+    }
+}
+
+template <int D, int KG>
+__global__ __launch_bounds__(64 * KG, waves_per_simd(D, KG)) void attn_fp32_kernel(P32 p) {
+  __shared__ __attribute__((aligned(1024))) float stage[KG * 2 * kPiece * D];
+  __shared__ unsigned int chosen[kMaxBlocks / 32];
+  __shared__ float part_s[3][KG][32];        // m, l, l_tail of every wave
+  // Each XCD gets a contiguous range of (head, row group) items, so that its L2 serves one head; the first n_whole are
+  // taken by a workgroup each, the rest by two.
+  const int xcd = blockIdx.x % 8, j = blockIdx.x / 8;
+  const int nth = j < p.n_whole ? j : p.n_whole + (j - p.n_whole) / 2;
+  const int item = xcd * p.per_xcd + nth;
+  if (nth >= p.per_xcd || item >= p.total) return;
+  const int row0 = item % p.n_groups * 32;
+  if (j < p.n_whole) {
+    attend_rows<D, 2, KG>(p, item / p.n_groups, row0, stage, chosen, part_s);
+  } else {
+    const int half0 = row0 + 16 * ((j - p.n_whole) & 1);
+    if (half0 < p.L) attend_rows<D, 1, KG>(p, item / p.n_groups, half0, stage, chosen, part_s);
   }
 }
 
-template <int D, int RG, int KG, int NBUF> void launch(P32& p, const Dims& dm, hipStream_t stream) {
-  p.n_groups = (dm.L + 16 * RG - 1) / (16 * RG);
-  p.total = p.n_groups * dm.bh();
-  hipLaunchKernelGGL((attn_fp32_kernel<D, RG, KG, NBUF>), dim3(8 * ((p.total + 7) / 8)), dim3(64 * kWaves), 0, stream, p);
-}
-
 template <int D> void launch_d(P32& p, const Dims& dm, hipStream_t stream) {
-  // Query rows per workgroup.  Fewer rows per workgroup fill more of the chip and balance it better, more
-  // rows read K and V less often (a 16-row workgroup asks L2 for 8.4 TB/s, which is what it gives).
-  // Measured, us per call (statistics and selection included), 16 / 32 / 64 rows: 32 tiles at head_dim 64
-  // 29.7 / 32.3 / 38.5; at head_dim 128 128 tiles 71.7 / 59.5 / 67.2, 568 tiles 388 / 278 / 283, 1136 tiles
-  // 732 / 465 / 448.
-  const long long tiles = (long long)((dm.L + kTile - 1) / kTile) * dm.bh();
-  if (tiles <= 64) launch<D, 1, 8, D == 128 ? 1 : 2>(p, dm, stream);
-  else if (tiles <= 768) launch<D, 2, 4, D == 128 ? 1 : 2>(p, dm, stream);
-  else launch<D, 4, 2, 2>(p, dm, stream);
+  p.n_groups = (dm.L + 31) / 32;
+  p.total = p.n_groups * dm.bh();
+  p.per_xcd = (p.total + 7) / 8;
+  // Row groups per XCD, of 32 CUs.  Up to one a CU, eight waves share a group's keys; up to half of that, each half of a
+  // group has a CU of its own.  Above, two (head_dim 128) or three workgroups of four waves share a CU, and the groups past
+  // the last full round of CUs are taken in halves where both halves of all of them find a CU, because the dispatcher puts
+  // the last workgroups on whatever CU is free first, two on one and none on another.  Measured over 110 sizes from 4 to 24
+  // heads of 700 to 4 000 rows: with halves 9-13 % faster (r = 0.85) and 11-16 % (dense) where up to 16 groups are left over,
+  // slower from there on.  At head_dim 128 all of up to 32 groups past a round of 64 workgroups are halved: 17 .. 32 groups
+  // 5 % faster (at head_dim 64, where a CU holds three workgroups, 13 % slower).
+  // Eight waves against four, us for the attention step: 2 heads of 2 200 rows 28.6 / 30.4 (dense 88 / 103), 8 of 1 000
+  // 22.0 / 21.1 (47.5 / 52.2); past one group a CU 8 of 1 500 38.7 / 31.6 (102 / 94).
+  if (p.per_xcd <= kCusPerXcd) {
+    p.n_whole = 2 * p.per_xcd <= kCusPerXcd ? 0 : p.per_xcd;
+    hipLaunchKernelGGL((attn_fp32_kernel<D, 8>), dim3(8 * (2 * p.per_xcd - p.n_whole)), dim3(512), 0, stream, p);
+  } else {
+    int over = p.per_xcd % kCusPerXcd;
+    if (D == 128 && 2 * over > kCusPerXcd) over = p.per_xcd % (2 * kCusPerXcd);
+    p.n_whole = over <= (D == 128 ? kCusPerXcd : kCusPerXcd / 2) ? p.per_xcd - over : p.per_xcd;
+    hipLaunchKernelGGL((attn_fp32_kernel<D, 4>), dim3(8 * (2 * p.per_xcd - p.n_whole)), dim3(256), 0, stream, p);
+  }
 }
 
 }  // namespace

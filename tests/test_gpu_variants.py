@@ -14,17 +14,37 @@ from workloads import WORKLOADS, make_qkv
 pytestmark = pytest.mark.gpu
 
 
-# fp32 attention: 16, 32 and 64 query rows per workgroup (up to 64, up to 768, more 64-row tiles in all)
+# fp32 attention: calls of 64 to 792 64-row tiles
 @pytest.mark.parametrize("L,H,d,B,r,check", [
-    (64 * 32, 2, 128, 64, 0.8, [0, 1]),           # 64 tiles: the last size with 16 rows
-    (64 * 21 + 1, 3, 128, 64, 0.9, [0, 2]),       # 66 tiles, one row in the last: 32 rows
+    (64 * 32, 2, 128, 64, 0.8, [0, 1]),           # 64 tiles
+    (64 * 21 + 1, 3, 128, 64, 0.9, [0, 2]),       # 66 tiles, one row in the last
     (64 * 21 + 50, 3, 64, 128, 0.5, [1]),         # the same at head_dim 64, block 128
-    (64 * 32, 24, 128, 128, 0.9, [0, 23]),        # 768 tiles: the last size with 32 rows
-    (64 * 32 + 17, 24, 128, 64, 0.95, [0, 23]),   # 792 tiles: 64 rows
+    (64 * 32, 24, 128, 128, 0.9, [0, 23]),        # 768 tiles
+    (64 * 32 + 17, 24, 128, 64, 0.95, [0, 23]),   # 792 tiles
     (64 * 32 + 63, 24, 64, 64, 0.8, [7]),
 ])
 def test_fp32_rows_per_workgroup(lib, L, H, d, B, r, check):
     w = WORKLOADS["tiny"].with_(name=f"fp32-rows-{L}-{H}", heads=H, seq_len=L, head_dim=d, block=B, sparsity=r,
+                                seed=L + H)
+    n = -(-L // B)
+    run_full_case(lib, w, blocks_per_head=sorted({0, 1, n // 2, n - 2, n - 1}), heads=check)
+
+
+# fp32 attention: the lines of the split, in groups of 32 rows per XCD (an eighth of all): eight waves up to 32, 16 rows
+# to a workgroup up to 16; above, the groups past a round of 32 CUs (at head_dim 128 also up to half a round of 64
+# workgroups) are halved
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("L,H,B,check", [
+    (1024, 4, 64, [0, 3]),              # 16: all in halves
+    (32 * 33 - 20, 4, 128, [0, 3]),     # 17: none, the last half of 12 rows
+    (1024, 8, 64, [0, 7]),              # 32
+    (32 * 33 - 16, 8, 64, [0, 7]),      # 33: one in halves, of which one has no row
+    (32 * 49, 8, 128, [7]),             # 49: none
+    (32 * 27 - 31, 24, 64, [0, 23]),    # 81: 17 in halves at head_dim 128, none at 64; one row in the last group
+    (32 * 21 + 5, 37, 64, [0, 36]),     # 102, six in halves; fewer in the last XCD
+])
+def test_fp32_split(lib, L, H, B, check, d):
+    w = WORKLOADS["tiny"].with_(name=f"fp32-split-{L}-{H}", heads=H, seq_len=L, head_dim=d, block=B, sparsity=0.8,
                                 seed=L + H)
     n = -(-L // B)
     run_full_case(lib, w, blocks_per_head=sorted({0, 1, n // 2, n - 2, n - 1}), heads=check)
