@@ -88,6 +88,7 @@ struct PB {
   int L, B, N, k_top, npad, n_super, total;
   float scale;
   int first_order;
+  int by_xcd;             // see the launch
   const int32_t* pair;    // block 64 only, may be null: [bh][2 * n_super] query blocks of each workgroup (-1: none)
 };
 
@@ -533,17 +534,12 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
   __shared__ unsigned short pre_s[DENSE || TPB == 2 ? 1 : MASK_WORDS + 1], pre_a[DENSE || TPB == 2 ? 1 : MASK_WORDS + 1],
       pre_b[DENSE || TPB == 2 ? 1 : MASK_WORDS + 1];                                   // tiles below each mask word, by class
 
-  // Workgroup ids are dealt round-robin to the 8 XCDs.  Dense attention gives each XCD a
-  // contiguous range of (head, query tile) items, so one XCD's L2 serves one head whose tiles
-  // all its workgroups walk in the same order.  PISA workgroups walk different tile lists and
-  // mostly miss L2, so there all XCDs work on the same head at the same time instead: the
-  // misses of all 8 XCDs then fall on one or two heads' K/V (39 MB each), which the 256 MB
-  // Infinity Cache holds, rather than on eight heads at once.
+  // Workgroup ids are dealt round-robin to the 8 XCDs.  With p.by_xcd each XCD gets a contiguous range of (head, query
+  // tile) items, so that one XCD's L2 serves one head; otherwise all XCDs work on the same head, 8 neighbouring items each
+  // (the rule stands at the launch).  The grid is rounded up: ids past an XCD's range leave.
   const int wg = blockIdx.x;
-  int item = ((wg >> 6) << 6) + ((wg & 7) << 3) + ((wg >> 3) & 7);   // 8 neighbours per XCD
-  if (DENSE) {
-    // The grid is rounded up, so ids with wg / 8 >= per_xcd would spill into the next XCD's
-    // range and redo its first items: they leave.
+  int item = ((wg >> 6) << 6) + ((wg & 7) << 3) + ((wg >> 3) & 7);
+  if (DENSE || p.by_xcd) {
     const int per_xcd = (p.total + 7) / 8;
     if (wg / 8 >= per_xcd) return;
     item = (wg % 8) * per_xcd + wg / 8;
@@ -1432,6 +1428,16 @@ static int short_call_limit(const Dims& dm, const AttnArgs& a) {
   return 4 * a.k_top > 3 * dm.N ? kTwoPerCu : kTwoLists;
 }
 
+// Which items an XCD takes.  Dense attention walks the same tiles in every workgroup of a head, so a head goes to one XCD.
+// PISA workgroups walk different lists: while K and V of a head are not much larger than an XCD's L2 (4 MB), most of their
+// tiles are found there if one XCD has the head to itself (us for the attention step, all XCDs on one head / one head
+// each, r = 0.85: 12 heads of 8 192 125 / 107, 24 of 8 192 212 / 187, 24 of 4 608 85 / 82, 24 of 16 384 713 / 688, at block 128
+// 580 / 549, head_dim 64, 40 of 8 192 184 / 171).  Longer heads mostly miss L2 either way (24 of 32 768 2 599 / 2 592,
+// 40 000 3 803 / 3 818, 48 000 5 497 / 5 512), and from where the K and V of eight heads at once outgrow the 256 MB Infinity
+// Cache they are better taken one at a time (12 of 65 536 3 591 / 3 625, 40 of 75 600 23.1 / 24.7 ms).  The line: 12 MiB
+// each for K and V of a head, 192 MiB for eight.
+static bool heads_by_xcd(const Dims& dm) { return (size_t)dm.L * dm.d * 2 <= ((size_t)12 << 20); }
+
 template <int D>
 static hipError_t launch_attention_bf16_d(const Dims& dm, const AttnArgs& a, hipStream_t stream) {
   PB p{};
@@ -1450,6 +1456,7 @@ static hipError_t launch_attention_bf16_d(const Dims& dm, const AttnArgs& a, hip
   p.total = p.n_super * dm.bh();
   p.scale = dm.scale;
   p.first_order = a.hsum != nullptr;
+  p.by_xcd = heads_by_xcd(dm);
 
   const bool short_call = p.total <= short_call_limit(dm, a);
   if (short_call) {
