@@ -39,8 +39,8 @@
 // point, by the statistics kernels; Phase 3 multiplies by the pre-packed hi/lo split of hsum,
 // staged through LDS once per workgroup.
 //
-// Calls with few workgroups take attn_bf16_short_kernel (64 rows per workgroup, keys split over wave
-// pairs); the rule and both kernels' times stand at the launch.
+// Calls of few items, and the items past the last full round of CUs, are taken by workgroups of 64 rows with the keys split
+// over wave pairs (attend_64_rows); the rule stands at the launch.
 #include <mutex>
 #include <type_traits>
 
@@ -89,6 +89,7 @@ struct PB {
   float scale;
   int first_order;
   int by_xcd;             // see the launch
+  int per_xcd, n_whole;   // items per XCD; how many of them a workgroup takes whole (the rest: two, 64 rows each)
   const int32_t* pair;    // block 64 only, may be null: [bh][2 * n_super] query blocks of each workgroup (-1: none)
 };
 
@@ -517,6 +518,365 @@ __device__ inline void absorb_tile(State<D>& st, const bf16x8 (&qreg)[D / 16], c
   pv_tile<D, VOFF>(st, pb, lc);
 }
 
+// ---------------------------------------------------------------------------------
+// Half an item: 64 query rows per workgroup, keys split over wave pairs
+// ---------------------------------------------------------------------------------
+// A workgroup has half the rows and a wave half the keys: a tile takes half as long, a sparse workgroup walks its own
+// index row instead of the union of two, and where there are fewer items than CUs twice as many CUs work.  The price is
+// that every tile is loaded for 64 rows instead of 128.
+// Wave w owns rows 32 (w >> 1) .. + 31 of the query tile and half e = w & 1 of the keys of every staged
+// tile; staging, operand layouts and the trip pipeline are the main kernel's.  The two partial results of
+// a row (each with a running maximum of its own) meet in LDS once, before Phase 3, and each wave of the
+// pair finishes half of the channels.  The tiles of one index row are walked straight from its bitmask.
+
+// exp_rows against a maximum that has just taken these keys in: the same rounded product is subtracted from it, so
+// that the largest key has weight 1 whatever its size.  (With 32 keys to a wave's step, a step can consist of nothing but
+// keys that a channel of their own masks by the lowest value or -inf; against the unrounded product such a step
+// sums up to anything between 0 and inf.)
+__device__ inline void exp_rows_at_max(const f32x16& s, float c, float m, bf16x8& p0, bf16x8& p1, float& pa, float& pc) {
+#pragma clang fp contract(off)
+  const float m_safe = m == -INFINITY ? 0.f : m;
+#pragma unroll
+  for (int step = 0; step < 2; ++step) {
+    u32x4 pw;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 8 * step + 2 * i;
+      const float x0 = __builtin_amdgcn_exp2f(s[r] * c - m_safe);
+      const float x1 = __builtin_amdgcn_exp2f(s[r + 1] * c - m_safe);
+      pw[i] = pack_bf16(x0, x1);
+      if (i & 1) pc += x0 + x1;
+      else pa += x0 + x1;
+    }
+    if (step == 0) p0 = __builtin_bit_cast(bf16x8, pw);
+    else p1 = __builtin_bit_cast(bf16x8, pw);
+  }
+}
+
+// 32 staged keys, start to finish, with the exact softmax step (ragged tile, centroid tiles); see absorb_tile.
+template <int D, bool TAIL, bool RAGGED, int KOFF, int VOFF>
+__device__ inline void absorb_rows(State<D>& st, const bf16x8 (&qreg)[D / 16], const LaneCtx& lc,
+                                   LDS_PTR(const float) bias, int nvalid, float c) {
+#pragma clang fp contract(off)
+  f32x16 s;
+  bf16x8 pb[2];
+  qk_rows<D, KOFF, 0>(s, qreg, lc);
+  const int h = lc.h;
+  if (TAIL) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f32x4 b = *reinterpret_cast<LDS_PTR(const f32x4)>(bias + 8 * g + 4 * h);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[4 * g + i] = fmaf(s[4 * g + i], c, b[i]);
+    }
+  }
+  const float tmax = max_rows(s);
+  raise_max<D>(st, TAIL ? tmax : tmax * c);
+  const float nm = st.m == -INFINITY ? 0.f : -st.m;
+  float psum = 0.f;
+#pragma unroll
+  for (int step = 0; step < 2; ++step) {
+    u32x4 pw;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float x[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int r = 8 * step + 2 * i + u;
+        x[u] = __builtin_amdgcn_exp2f(TAIL ? s[r] + nm : s[r] * c + nm);      // two roundings: see exp_rows_at_max
+        if (RAGGED && (r / 4) * 8 + 4 * h + (r % 4) >= nvalid) x[u] = 0.f;
+        psum += x[u];
+      }
+      pw[i] = pack_bf16(x[0], x[1]);
+    }
+    pb[step] = __builtin_bit_cast(bf16x8, pw);
+  }
+  st.l += psum;
+  if (TAIL) st.l_tail += psum;
+  pv_rows<D, VOFF, 0>(st, pb[0], pb[1], lc);
+}
+
+// LDS of a 64-row workgroup, inside that of the kernel it runs in.
+struct ShortLds {
+  LDS_PTR(unsigned char) stage;      // K0 | K1 | V0 | V1
+  LDS_PTR(unsigned int) chosen;      // [MASK_WORDS]
+  LDS_PTR(float) bias;               // [stage parity][centroid]
+  LDS_PTR(float) merge;              // [wave][max, sum, tail sum][32]
+};
+
+// One 64-row query tile qt of head bh.
+template <int D, bool DENSE, int TPB>
+__device__ __forceinline__ void attend_64_rows(const PB& p, const size_t bh, const int qt, const ShortLds& sl) {
+  constexpr int ROWB = Geo<D>::ROWB, TILEB = Geo<D>::TILEB, NKS = Geo<D>::NKS, NDT = Geo<D>::NDT;
+  constexpr int CPR = Geo<D>::CPR, RPL = Geo<D>::RPL, HDT = NDT / 2, HALFB = TILEB / 2;
+  constexpr int KST0 = 0, KST1 = TILEB, VST0 = 2 * TILEB, VST1 = 3 * TILEB;
+  LDS_PTR(unsigned int) chosen = sl.chosen;
+  const int blk = qt / TPB;                          // its block (PISA)
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lam = lane & 31, h = lane >> 5, e = wave & 1;
+  const int L = p.L, N = p.N;
+  const unsigned char* kg = reinterpret_cast<const unsigned char*>(p.k + bh * (size_t)L * D);
+  const unsigned char* vg = reinterpret_cast<const unsigned char*>(p.v + bh * (size_t)L * D);
+  const float c = p.scale * 1.44269504088896340736f;
+  LDS_PTR(unsigned char) lds = sl.stage;
+  const unsigned lds_addr = (unsigned)(unsigned long long)lds;
+
+  LaneCtx lc;
+  lc.h = h;
+  lc.wave = wave;
+  {
+    const int pos = lane % CPR;
+    lc.dma_r0 = RPL * Geo<D>::NLD * wave + lane / CPR;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = lc.dma_r0 + RPL * i;
+      const int in_piece = (lane / CPR) * ROWB;
+      lc.dma_k[i] = in_piece + ((pos ^ kswz<D>(r)) << 4);
+      lc.dma_v[i] = in_piece + (((((pos >> 1) ^ vswz<D>(r)) << 1) | (pos & 1)) << 4);
+    }
+    const int j16 = lane & 15, kq = 4 * h + (j16 >> 2), lhalf = (lane >> 4) & 1;
+    // this wave's 32 rows of a stage (32 is a multiple of both swizzles' periods)
+    lc.kbase = lds + (32 * e + lam) * ROWB + ((kswz<D>(lam) ^ h) << 4);
+    lc.vbase = lds + (32 * e + kq) * ROWB + 8 * (j16 & 3) + ((lhalf ^ vswz<D>(kq)) << 5);
+  }
+
+  const int32_t* row = DENSE ? nullptr : p.idx + (bh * N + blk) * (size_t)p.k_top;
+  int j_first = -1;
+  if (!DENSE && tid < p.k_top) j_first = row[tid];
+  const int q_row = qt * kTile + 32 * (wave >> 1) + lam;
+  bf16x8 qreg[NKS];
+  {
+    const __bf16* qg = p.q + bh * (size_t)L * D;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+      u32x4 w = {0, 0, 0, 0};
+      if (q_row < L) w = *reinterpret_cast<const u32x4*>(qg + (size_t)q_row * D + 16 * ks + 8 * h);
+      qreg[ks] = __builtin_bit_cast(bf16x8, w);
+    }
+  }
+  State<D> st;
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt) st.ot[dt] = (f32x16){0};
+  st.m = -INFINITY;
+  st.l = 0.f;
+  st.l_tail = 0.f;
+
+  const int nwords = (N + 31) / 32;
+  if (!DENSE) {
+    for (int w = tid; w < MASK_WORDS; w += 256) chosen[w] = 0u;
+    __syncthreads();
+    int j = j_first;
+    for (int t = tid; t < p.k_top; t += 256) {
+      if (t != tid) j = row[t];
+      if ((unsigned)j < (unsigned)N) atomicOr((unsigned int*)(chosen + (j >> 5)), 1u << (j & 31));   // entries outside [0, N) are ignored
+    }
+    __syncthreads();
+  }
+
+  // ---- Phase 1 ----
+  const int n_tiles = L / kTile;
+  int w_word = -1, pend = -1, dense_t = 0;
+  unsigned int w_bits = 0u;
+  auto next_tile = [&](int& off) -> bool {            // byte offset of the next full exact tile
+    int tile;
+    if (DENSE) {
+      tile = dense_t++;
+    } else if (pend >= 0) {
+      tile = pend;
+      pend = -1;
+    } else {
+      while (w_bits == 0u) {
+        if (++w_word >= nwords) return false;
+        w_bits = __builtin_amdgcn_readfirstlane(chosen[w_word]);
+      }
+      tile = TPB * (w_word * 32 + __builtin_ctz(w_bits));
+      w_bits &= w_bits - 1u;
+      if (TPB == 2 && tile + 1 < n_tiles) pend = tile + 1;
+    }
+    if (tile >= n_tiles) return false;                // only the ragged tile is left
+    off = tile * TILEB;
+    return true;
+  };
+  {
+    f32x16 sc;
+    int off0 = 0, off1 = 0, off2 = 0;
+    bool have0 = next_tile(off0), have1 = false, have2 = false;
+    if (have0) {
+      load_stage<D, true>(lc, kg, Trip{off0, off0 + HALFB}, lds_addr + KST0);
+      have1 = next_tile(off1);
+      wait_async_loads();
+      __syncthreads();
+      if (have1) load_stage<D, true>(lc, kg, Trip{off1, off1 + HALFB}, lds_addr + KST1);
+      load_stage<D, false>(lc, vg, Trip{off0, off0 + HALFB}, lds_addr + VST0);
+      qk_rows<D, KST0, 0>(sc, qreg, lc);
+    }
+    auto trip = [&](auto parity_tag) {
+      constexpr int P = decltype(parity_tag)::value;
+      constexpr int K_NEXT = P ? KST0 : KST1, K_FREE = P ? KST1 : KST0;
+      constexpr int V_CUR = P ? VST1 : VST0, V_FREE = P ? VST0 : VST1;
+      have2 = have1 && next_tile(off2);
+      wait_async_loads();
+      __syncthreads();
+      if (have2) load_stage<D, true>(lc, kg, Trip{off2, off2 + HALFB}, lds_addr + K_FREE);
+      if (have1) load_stage<D, false>(lc, vg, Trip{off1, off1 + HALFB}, lds_addr + V_FREE);
+      bf16x8 p0, p1;
+      float pa = 0.f, pc = 0.f;
+      exp_rows(sc, c, -st.m, p0, p1, pa, pc);
+      if (__any(!(pa + pc < kStaleLimit))) {           // first keys of this wave, or a maximum that ran away
+        raise_max<D>(st, max_rows(sc) * c);
+        pa = pc = 0.f;
+        exp_rows_at_max(sc, c, st.m, p0, p1, pa, pc);
+      }
+      st.l += pa + pc;
+      pv_rows<D, V_CUR, 0>(st, p0, p1, lc);
+      if (have1) qk_rows<D, K_NEXT, 0>(sc, qreg, lc);
+      off0 = off1;
+      have0 = have1;
+      off1 = off2;
+      have1 = have2;
+    };
+    while (have0) {
+      trip(std::integral_constant<int, 0>{});
+      if (!have0) break;
+      trip(std::integral_constant<int, 1>{});
+    }
+  }
+
+  // ---- ragged last tile ----
+  if (L % kTile != 0) {
+    const int jb = n_tiles / TPB;
+    if (DENSE || ((chosen[jb >> 5] >> (jb & 31)) & 1u)) {            // uniform over the workgroup
+      __syncthreads();
+      load_tile_async<D, true>(lc, kg + (size_t)n_tiles * TILEB, L - n_tiles * kTile, lds_addr + KST0);
+      load_tile_async<D, false>(lc, vg + (size_t)n_tiles * TILEB, L - n_tiles * kTile, lds_addr + VST0);
+      wait_async_loads();
+      __syncthreads();
+      absorb_rows<D, false, true, KST0, VST0>(st, qreg, lc, nullptr, L - n_tiles * kTile - 32 * e, c);
+    }
+  }
+
+  // ---- Phase 2: centroid tiles ----
+  const bool approx = !DENSE && p.k_top < N && p.kcen != nullptr;
+  if (approx) {
+    const unsigned char* kcg = reinterpret_cast<const unsigned char*>(p.kcen + bh * (size_t)p.npad * D);
+    const unsigned char* vbg = reinterpret_cast<const unsigned char*>(p.vbar + bh * (size_t)p.npad * D);
+    const float log2_full = __builtin_amdgcn_logf((float)p.B);
+    const float log2_last = __builtin_amdgcn_logf((float)(L - (N - 1) * p.B));
+    auto fetch = [&](int g0, auto parity_tag) {
+      constexpr int P = decltype(parity_tag)::value;
+      load_tile_async<D, true>(lc, kcg + (size_t)g0 * ROWB, kTile, lds_addr + (P ? KST1 : KST0));
+      load_tile_async<D, false>(lc, vbg + (size_t)g0 * ROWB, kTile, lds_addr + (P ? VST1 : VST0));
+      if (tid < kTile) {
+        const int j = g0 + tid;
+        const bool masked = j >= N || ((chosen[(j >> 5) & (MASK_WORDS - 1)] >> (j & 31)) & 1u);
+        sl.bias[P * kTile + tid] = masked ? -INFINITY : (j == N - 1 ? log2_last : log2_full);
+      }
+    };
+    auto absorb = [&](int g0, auto parity_tag) {
+      constexpr int P = decltype(parity_tag)::value;
+      wait_async_loads();
+      __syncthreads();
+      if (g0 + kTile < N) fetch(g0 + kTile, std::integral_constant<int, 1 - P>{});
+      absorb_rows<D, true, false, (P ? KST1 : KST0), (P ? VST1 : VST0)>(
+          st, qreg, lc, (LDS_PTR(const float))(sl.bias + P * kTile + 32 * e), kTile, c);
+    };
+    __syncthreads();
+    fetch(0, std::integral_constant<int, 0>{});
+    for (int g0 = 0; g0 < N; g0 += 2 * kTile) {
+      absorb(g0, std::integral_constant<int, 0>{});
+      if (g0 + kTile < N) absorb(g0 + kTile, std::integral_constant<int, 1>{});
+    }
+  }
+
+  // ---- merge: lane halves, then the two waves of a pair; a wave keeps channel tiles e HDT .. + HDT - 1 ----
+  {
+    st.l += __shfl_xor(st.l, 32);
+    st.l_tail += __shfl_xor(st.l_tail, 32);
+    LDS_PTR(unsigned char) mine = lds + wave * (HDT * 4096) + lane * 16;
+    LDS_PTR(const unsigned char) theirs = lds + (wave ^ 1) * (HDT * 4096) + lane * 16;
+    __syncthreads();                            // the stages are free
+#pragma unroll
+    for (int dt = 0; dt < HDT; ++dt) {
+      const f32x16 give = e ? st.ot[dt] : st.ot[HDT + dt];
+      if (e) st.ot[dt] = st.ot[HDT + dt];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 w = {give[4 * g], give[4 * g + 1], give[4 * g + 2], give[4 * g + 3]};
+        *reinterpret_cast<LDS_PTR(f32x4)>(mine + (dt * 4 + g) * 1024) = w;
+      }
+    }
+    if (h == 0) {
+      sl.merge[(wave * 3 + 0) * 32 + lam] = st.m;
+      sl.merge[(wave * 3 + 1) * 32 + lam] = st.l;
+      sl.merge[(wave * 3 + 2) * 32 + lam] = st.l_tail;
+    }
+    __syncthreads();
+    const float om = sl.merge[((wave ^ 1) * 3 + 0) * 32 + lam];
+    const float m = fmaxf(st.m, om);
+    // a wave that met no key at all (maximum still -inf) holds zeros
+    const float f0 = st.m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(st.m - m);
+    const float f1 = om == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(om - m);
+    st.m = m;
+    st.l = st.l * f0 + sl.merge[((wave ^ 1) * 3 + 1) * 32 + lam] * f1;
+    st.l_tail = st.l_tail * f0 + sl.merge[((wave ^ 1) * 3 + 2) * 32 + lam] * f1;
+#pragma unroll
+    for (int dt = 0; dt < HDT; ++dt)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 w = *reinterpret_cast<LDS_PTR(const f32x4)>(theirs + (dt * 4 + g) * 1024);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) st.ot[dt][4 * g + i] = fmaf(st.ot[dt][4 * g + i], f0, w[i] * f1);
+      }
+  }
+
+  // ---- Phase 3, as in the main kernel, for this wave's channels ----
+  if (approx && p.first_order) {
+    const unsigned char* hp = reinterpret_cast<const unsigned char*>(p.hpack + bh * (size_t)(2 * D * D));
+    constexpr int HP_LOADS = 4 * D * D / (4 * 1024);
+    __syncthreads();                            // the merge has been read
+#pragma unroll
+    for (int i = 0; i < HP_LOADS; ++i) {
+      const unsigned off = (unsigned)__builtin_amdgcn_readfirstlane((int)((lc.wave * HP_LOADS + i) * 1024));
+      set_dma_lds_base(lds_addr + off);
+      dma_1kb<0>((unsigned)(lane * 16), hp + off);
+    }
+    wait_async_loads();
+    __syncthreads();
+    LDS_PTR(const unsigned char) hl = lds + lane * 16 + e * HDT * 1024;
+    f32x16 rt[HDT];
+#pragma unroll
+    for (int dt = 0; dt < HDT; ++dt) rt[dt] = (f32x16){0};
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+      for (int dt = 0; dt < HDT; ++dt) {
+        const bf16x8 ahi = *reinterpret_cast<LDS_PTR(const bf16x8)>(hl + (ks * NDT + dt) * 1024);
+        const bf16x8 alo = *reinterpret_cast<LDS_PTR(const bf16x8)>(hl + 2 * D * D + (ks * NDT + dt) * 1024);
+        rt[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi, qreg[ks], rt[dt], 0, 0, 0);
+        rt[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo, qreg[ks], rt[dt], 0, 0, 0);
+      }
+    const float w = st.l_tail / (float)L * p.scale;
+#pragma unroll
+    for (int dt = 0; dt < HDT; ++dt) st.ot[dt] += rt[dt] * w;
+  }
+
+  if (q_row < L) {
+    const float inv_l = 1.f / st.l;
+    __bf16* orow = p.out + (bh * (size_t)L + q_row) * D + 32 * HDT * e;
+#pragma unroll
+    for (int dt = 0; dt < HDT; ++dt)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const u32x2 w = {pack_bf16(st.ot[dt][4 * g] * inv_l, st.ot[dt][4 * g + 1] * inv_l),
+                         pack_bf16(st.ot[dt][4 * g + 2] * inv_l, st.ot[dt][4 * g + 3] * inv_l)};
+        *reinterpret_cast<u32x2*>(orow + 32 * dt + 8 * g + 4 * h) = w;
+      }
+    if (p.lse && h == 0 && e == 0)
+      p.lse[bh * (size_t)L + q_row] = (st.m + __builtin_amdgcn_logf(st.l)) * 0.69314718055994530942f;
+  }
+}
+
 // LDS map of the staging area (byte offsets): K stages | V stages; Phase 2 reuses it as
 // centroid keys (K stage 0) and centroid values (V stage 0).
 // Three workgroups per CU at head_dim 64 (168 VGPRs, 33 KB LDS each), two at 128.
@@ -530,6 +890,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
   __shared__ __attribute__((aligned(1024))) unsigned char stage[4 * TILEB];   // K0 | K1 | V0 | V1
   __shared__ unsigned int chosen[2][MASK_WORDS];
   __shared__ __attribute__((aligned(16))) float bias_s[2][2][kTile];          // [stage parity][query block][centroid]
+  __shared__ float merge_s[4 * 3 * 32];
   __shared__ unsigned short trip_list[DENSE || TPB == 2 ? 2 : kMaxBlocks + 2];          // Phase-1 walk of a block-64 workgroup
   __shared__ unsigned short pre_s[DENSE || TPB == 2 ? 1 : MASK_WORDS + 1], pre_a[DENSE || TPB == 2 ? 1 : MASK_WORDS + 1],
       pre_b[DENSE || TPB == 2 ? 1 : MASK_WORDS + 1];                                   // tiles below each mask word, by class
@@ -537,16 +898,21 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
   // Workgroup ids are dealt round-robin to the 8 XCDs.  With p.by_xcd each XCD gets a contiguous range of (head, query
   // tile) items, so that one XCD's L2 serves one head; otherwise all XCDs work on the same head, 8 neighbouring items each
   // (the rule stands at the launch).  The grid is rounded up: ids past an XCD's range leave.
-  const int wg = blockIdx.x;
-  int item = ((wg >> 6) << 6) + ((wg & 7) << 3) + ((wg >> 3) & 7);
-  if (DENSE || p.by_xcd) {
-    const int per_xcd = (p.total + 7) / 8;
-    if (wg / 8 >= per_xcd) return;
-    item = (wg % 8) * per_xcd + wg / 8;
-  }
-  if (item >= p.total) return;
+  const int xcd = blockIdx.x % 8, j = blockIdx.x / 8;
+  const int nth = j < p.n_whole ? j : p.n_whole + (j - p.n_whole) / 2;
+  const int item = p.by_xcd ? xcd * p.per_xcd + nth : (nth >> 3) * 64 + xcd * 8 + (nth & 7);
+  if (nth >= p.per_xcd || item >= p.total) return;
   const size_t bh = item / p.n_super;
   const int sg = item % p.n_super;
+  if (j >= p.n_whole) {
+    const int half = (j - p.n_whole) & 1;
+    int qt = 2 * sg + half;
+    if (!DENSE && TPB == 1 && p.pair) qt = __builtin_amdgcn_readfirstlane(p.pair[(bh * p.n_super + sg) * 2 + half]);
+    if (qt >= 0 && qt * kTile < p.L)
+      attend_64_rows<D, DENSE, TPB>(p, bh, qt, ShortLds{(LDS_PTR(unsigned char)) & stage[0], (LDS_PTR(unsigned int)) & chosen[0][0],
+                                                        (LDS_PTR(float)) & bias_s[0][0][0], (LDS_PTR(float)) & merge_s[0]});
+    return;
+  }
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -1014,371 +1380,6 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
   }
 }
 
-// ---------------------------------------------------------------------------------
-// Short calls: 64 query rows per workgroup, keys split over wave pairs
-// ---------------------------------------------------------------------------------
-// A call of a few heads of a few thousand tokens has fewer 128-row workgroups than the chip has CUs, and
-// its time is one workgroup's: a chain of tiles, each a load, a softmax and two products.  Here a workgroup has
-// half the rows and a wave half the keys: a tile takes half as long, a sparse workgroup walks its own index
-// row instead of the union of two, and twice as many CUs work.  The price is that every tile is loaded
-// for 64 rows instead of 128.  2 heads of 1 000 tokens, r = 0.8: one call 31.6 -> 24.0 us.
-// Wave w owns rows 32 (w >> 1) .. + 31 of the query tile and half e = w & 1 of the keys of every staged
-// tile; staging, operand layouts and the trip pipeline are the main kernel's.  The two partial results of
-// a row (each with a running maximum of its own) meet in LDS once, before Phase 3, and each wave of the
-// pair finishes half of the channels.  The tiles of one index row are walked straight from its bitmask.
-
-// exp_rows against a maximum that has just taken these keys in: the same rounded product is subtracted from it, so
-// that the largest key has weight 1 whatever its size.  (With 32 keys to a wave's step, a step can consist of nothing but
-// keys that a channel of their own masks by the lowest value or -inf; against the unrounded product such a step
-// sums up to anything between 0 and inf.)
-__device__ inline void exp_rows_at_max(const f32x16& s, float c, float m, bf16x8& p0, bf16x8& p1, float& pa, float& pc) {
-#pragma clang fp contract(off)
-  const float m_safe = m == -INFINITY ? 0.f : m;
-#pragma unroll
-  for (int step = 0; step < 2; ++step) {
-    u32x4 pw;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = 8 * step + 2 * i;
-      const float x0 = __builtin_amdgcn_exp2f(s[r] * c - m_safe);
-      const float x1 = __builtin_amdgcn_exp2f(s[r + 1] * c - m_safe);
-      pw[i] = pack_bf16(x0, x1);
-      if (i & 1) pc += x0 + x1;
-      else pa += x0 + x1;
-    }
-    if (step == 0) p0 = __builtin_bit_cast(bf16x8, pw);
-    else p1 = __builtin_bit_cast(bf16x8, pw);
-  }
-}
-
-// 32 staged keys, start to finish, with the exact softmax step (ragged tile, centroid tiles); see absorb_tile.
-template <int D, bool TAIL, bool RAGGED, int KOFF, int VOFF>
-__device__ inline void absorb_rows(State<D>& st, const bf16x8 (&qreg)[D / 16], const LaneCtx& lc,
-                                   LDS_PTR(const float) bias, int nvalid, float c) {
-#pragma clang fp contract(off)
-  f32x16 s;
-  bf16x8 pb[2];
-  qk_rows<D, KOFF, 0>(s, qreg, lc);
-  const int h = lc.h;
-  if (TAIL) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const f32x4 b = *reinterpret_cast<LDS_PTR(const f32x4)>(bias + 8 * g + 4 * h);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) s[4 * g + i] = fmaf(s[4 * g + i], c, b[i]);
-    }
-  }
-  const float tmax = max_rows(s);
-  raise_max<D>(st, TAIL ? tmax : tmax * c);
-  const float nm = st.m == -INFINITY ? 0.f : -st.m;
-  float psum = 0.f;
-#pragma unroll
-  for (int step = 0; step < 2; ++step) {
-    u32x4 pw;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float x[2];
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int r = 8 * step + 2 * i + u;
-        x[u] = __builtin_amdgcn_exp2f(TAIL ? s[r] + nm : s[r] * c + nm);      // two roundings: see exp_rows_at_max
-        if (RAGGED && (r / 4) * 8 + 4 * h + (r % 4) >= nvalid) x[u] = 0.f;
-        psum += x[u];
-      }
-      pw[i] = pack_bf16(x[0], x[1]);
-    }
-    pb[step] = __builtin_bit_cast(bf16x8, pw);
-  }
-  st.l += psum;
-  if (TAIL) st.l_tail += psum;
-  pv_rows<D, VOFF, 0>(st, pb[0], pb[1], lc);
-}
-
-template <int D, bool DENSE, int TPB>
-__global__ __launch_bounds__(256, 2) void attn_bf16_short_kernel(PB p) {
-  constexpr int ROWB = Geo<D>::ROWB, TILEB = Geo<D>::TILEB, NKS = Geo<D>::NKS, NDT = Geo<D>::NDT;
-  constexpr int CPR = Geo<D>::CPR, RPL = Geo<D>::RPL, HDT = NDT / 2, HALFB = TILEB / 2;
-  constexpr int KST0 = 0, KST1 = TILEB, VST0 = 2 * TILEB, VST1 = 3 * TILEB;
-  __shared__ __attribute__((aligned(1024))) unsigned char stage[4 * TILEB];   // K0 | K1 | V0 | V1
-  __shared__ unsigned int chosen[MASK_WORDS];
-  __shared__ __attribute__((aligned(16))) float bias_s[2][kTile];             // [stage parity][centroid]
-  __shared__ float merge_s[4][3][32];                                         // [wave]: max, sum, tail sum
-
-  // Each XCD gets a contiguous range of (head, query tile) items, so that its L2 fetches the K, V and hsum of few heads.
-  // Dealt round robin every XCD fetched all of them, and many short heads ran slower than on the 128-row kernel
-  // (attention of 64 heads of 512 tokens, 4 of 8 blocks: main kernel 26.1 us, short 31.6, now 23.5; 32 heads of 1 024,
-  // 8 of 16: 29.5, 31.4, now 25.0; dense, 44 heads of 512: 15.2, 19.8, now 15.9).
-  const int per_xcd = (p.total + 7) / 8;
-  const int item = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if ((int)blockIdx.x / 8 >= per_xcd || item >= p.total) return;
-  const size_t bh = item / p.n_super;
-  const int qt = item % p.n_super;                   // 64-row query tile
-  const int blk = qt / TPB;                          // its block (PISA)
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lam = lane & 31, h = lane >> 5, e = wave & 1;
-  const int L = p.L, N = p.N;
-  const unsigned char* kg = reinterpret_cast<const unsigned char*>(p.k + bh * (size_t)L * D);
-  const unsigned char* vg = reinterpret_cast<const unsigned char*>(p.v + bh * (size_t)L * D);
-  const float c = p.scale * 1.44269504088896340736f;
-  LDS_PTR(unsigned char) lds = (LDS_PTR(unsigned char)) & stage[0];
-  const unsigned lds_addr = (unsigned)(unsigned long long)lds;
-
-  LaneCtx lc;
-  lc.h = h;
-  lc.wave = wave;
-  {
-    const int pos = lane % CPR;
-    lc.dma_r0 = RPL * Geo<D>::NLD * wave + lane / CPR;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = lc.dma_r0 + RPL * i;
-      const int in_piece = (lane / CPR) * ROWB;
-      lc.dma_k[i] = in_piece + ((pos ^ kswz<D>(r)) << 4);
-      lc.dma_v[i] = in_piece + (((((pos >> 1) ^ vswz<D>(r)) << 1) | (pos & 1)) << 4);
-    }
-    const int j16 = lane & 15, kq = 4 * h + (j16 >> 2), lhalf = (lane >> 4) & 1;
-    // this wave's 32 rows of a stage (32 is a multiple of both swizzles' periods)
-    lc.kbase = lds + (32 * e + lam) * ROWB + ((kswz<D>(lam) ^ h) << 4);
-    lc.vbase = lds + (32 * e + kq) * ROWB + 8 * (j16 & 3) + ((lhalf ^ vswz<D>(kq)) << 5);
-  }
-
-  const int32_t* row = DENSE ? nullptr : p.idx + (bh * N + blk) * (size_t)p.k_top;
-  int j_first = -1;
-  if (!DENSE && tid < p.k_top) j_first = row[tid];
-  const int q_row = qt * kTile + 32 * (wave >> 1) + lam;
-  bf16x8 qreg[NKS];
-  {
-    const __bf16* qg = p.q + bh * (size_t)L * D;
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-      u32x4 w = {0, 0, 0, 0};
-      if (q_row < L) w = *reinterpret_cast<const u32x4*>(qg + (size_t)q_row * D + 16 * ks + 8 * h);
-      qreg[ks] = __builtin_bit_cast(bf16x8, w);
-    }
-  }
-  State<D> st;
-#pragma unroll
-  for (int dt = 0; dt < NDT; ++dt) st.ot[dt] = (f32x16){0};
-  st.m = -INFINITY;
-  st.l = 0.f;
-  st.l_tail = 0.f;
-
-  const int nwords = (N + 31) / 32;
-  if (!DENSE) {
-    for (int w = tid; w < MASK_WORDS; w += 256) chosen[w] = 0u;
-    __syncthreads();
-    int j = j_first;
-    for (int t = tid; t < p.k_top; t += 256) {
-      if (t != tid) j = row[t];
-      if ((unsigned)j < (unsigned)N) atomicOr(&chosen[j >> 5], 1u << (j & 31));   // entries outside [0, N) are ignored
-    }
-    __syncthreads();
-  }
-
-  // ---- Phase 1 ----
-  const int n_tiles = L / kTile;
-  int w_word = -1, pend = -1, dense_t = 0;
-  unsigned int w_bits = 0u;
-  auto next_tile = [&](int& off) -> bool {            // byte offset of the next full exact tile
-    int tile;
-    if (DENSE) {
-      tile = dense_t++;
-    } else if (pend >= 0) {
-      tile = pend;
-      pend = -1;
-    } else {
-      while (w_bits == 0u) {
-        if (++w_word >= nwords) return false;
-        w_bits = __builtin_amdgcn_readfirstlane(chosen[w_word]);
-      }
-      tile = TPB * (w_word * 32 + __builtin_ctz(w_bits));
-      w_bits &= w_bits - 1u;
-      if (TPB == 2 && tile + 1 < n_tiles) pend = tile + 1;
-    }
-    if (tile >= n_tiles) return false;                // only the ragged tile is left
-    off = tile * TILEB;
-    return true;
-  };
-  {
-    f32x16 sc;
-    int off0 = 0, off1 = 0, off2 = 0;
-    bool have0 = next_tile(off0), have1 = false, have2 = false;
-    if (have0) {
-      load_stage<D, true>(lc, kg, Trip{off0, off0 + HALFB}, lds_addr + KST0);
-      have1 = next_tile(off1);
-      wait_async_loads();
-      __syncthreads();
-      if (have1) load_stage<D, true>(lc, kg, Trip{off1, off1 + HALFB}, lds_addr + KST1);
-      load_stage<D, false>(lc, vg, Trip{off0, off0 + HALFB}, lds_addr + VST0);
-      qk_rows<D, KST0, 0>(sc, qreg, lc);
-    }
-    auto trip = [&](auto parity_tag) {
-      constexpr int P = decltype(parity_tag)::value;
-      constexpr int K_NEXT = P ? KST0 : KST1, K_FREE = P ? KST1 : KST0;
-      constexpr int V_CUR = P ? VST1 : VST0, V_FREE = P ? VST0 : VST1;
-      have2 = have1 && next_tile(off2);
-      wait_async_loads();
-      __syncthreads();
-      if (have2) load_stage<D, true>(lc, kg, Trip{off2, off2 + HALFB}, lds_addr + K_FREE);
-      if (have1) load_stage<D, false>(lc, vg, Trip{off1, off1 + HALFB}, lds_addr + V_FREE);
-      bf16x8 p0, p1;
-      float pa = 0.f, pc = 0.f;
-      exp_rows(sc, c, -st.m, p0, p1, pa, pc);
-      if (__any(!(pa + pc < kStaleLimit))) {           // first keys of this wave, or a maximum that ran away
-        raise_max<D>(st, max_rows(sc) * c);
-        pa = pc = 0.f;
-        exp_rows_at_max(sc, c, st.m, p0, p1, pa, pc);
-      }
-      st.l += pa + pc;
-      pv_rows<D, V_CUR, 0>(st, p0, p1, lc);
-      if (have1) qk_rows<D, K_NEXT, 0>(sc, qreg, lc);
-      off0 = off1;
-      have0 = have1;
-      off1 = off2;
-      have1 = have2;
-    };
-    while (have0) {
-      trip(std::integral_constant<int, 0>{});
-      if (!have0) break;
-      trip(std::integral_constant<int, 1>{});
-    }
-  }
-
-  // ---- ragged last tile ----
-  if (L % kTile != 0) {
-    const int jb = n_tiles / TPB;
-    if (DENSE || ((chosen[jb >> 5] >> (jb & 31)) & 1u)) {            // uniform over the workgroup
-      __syncthreads();
-      load_tile_async<D, true>(lc, kg + (size_t)n_tiles * TILEB, L - n_tiles * kTile, lds_addr + KST0);
-      load_tile_async<D, false>(lc, vg + (size_t)n_tiles * TILEB, L - n_tiles * kTile, lds_addr + VST0);
-      wait_async_loads();
-      __syncthreads();
-      absorb_rows<D, false, true, KST0, VST0>(st, qreg, lc, nullptr, L - n_tiles * kTile - 32 * e, c);
-    }
-  }
-
-  // ---- Phase 2: centroid tiles ----
-  const bool approx = !DENSE && p.k_top < N && p.kcen != nullptr;
-  if (approx) {
-    const unsigned char* kcg = reinterpret_cast<const unsigned char*>(p.kcen + bh * (size_t)p.npad * D);
-    const unsigned char* vbg = reinterpret_cast<const unsigned char*>(p.vbar + bh * (size_t)p.npad * D);
-    const float log2_full = __builtin_amdgcn_logf((float)p.B);
-    const float log2_last = __builtin_amdgcn_logf((float)(L - (N - 1) * p.B));
-    auto fetch = [&](int g0, auto parity_tag) {
-      constexpr int P = decltype(parity_tag)::value;
-      load_tile_async<D, true>(lc, kcg + (size_t)g0 * ROWB, kTile, lds_addr + (P ? KST1 : KST0));
-      load_tile_async<D, false>(lc, vbg + (size_t)g0 * ROWB, kTile, lds_addr + (P ? VST1 : VST0));
-      if (tid < kTile) {
-        const int j = g0 + tid;
-        const bool masked = j >= N || ((chosen[(j >> 5) & (MASK_WORDS - 1)] >> (j & 31)) & 1u);
-        bias_s[P][tid] = masked ? -INFINITY : (j == N - 1 ? log2_last : log2_full);
-      }
-    };
-    auto absorb = [&](int g0, auto parity_tag) {
-      constexpr int P = decltype(parity_tag)::value;
-      wait_async_loads();
-      __syncthreads();
-      if (g0 + kTile < N) fetch(g0 + kTile, std::integral_constant<int, 1 - P>{});
-      absorb_rows<D, true, false, (P ? KST1 : KST0), (P ? VST1 : VST0)>(
-          st, qreg, lc, (LDS_PTR(const float)) & bias_s[P][32 * e], kTile, c);
-    };
-    __syncthreads();
-    fetch(0, std::integral_constant<int, 0>{});
-    for (int g0 = 0; g0 < N; g0 += 2 * kTile) {
-      absorb(g0, std::integral_constant<int, 0>{});
-      if (g0 + kTile < N) absorb(g0 + kTile, std::integral_constant<int, 1>{});
-    }
-  }
-
-  // ---- merge: lane halves, then the two waves of a pair; a wave keeps channel tiles e HDT .. + HDT - 1 ----
-  {
-    st.l += __shfl_xor(st.l, 32);
-    st.l_tail += __shfl_xor(st.l_tail, 32);
-    LDS_PTR(unsigned char) mine = lds + wave * (HDT * 4096) + lane * 16;
-    LDS_PTR(const unsigned char) theirs = lds + (wave ^ 1) * (HDT * 4096) + lane * 16;
-    __syncthreads();                            // the stages are free
-#pragma unroll
-    for (int dt = 0; dt < HDT; ++dt) {
-      const f32x16 give = e ? st.ot[dt] : st.ot[HDT + dt];
-      if (e) st.ot[dt] = st.ot[HDT + dt];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 w = {give[4 * g], give[4 * g + 1], give[4 * g + 2], give[4 * g + 3]};
-        *reinterpret_cast<LDS_PTR(f32x4)>(mine + (dt * 4 + g) * 1024) = w;
-      }
-    }
-    if (h == 0) {
-      merge_s[wave][0][lam] = st.m;
-      merge_s[wave][1][lam] = st.l;
-      merge_s[wave][2][lam] = st.l_tail;
-    }
-    __syncthreads();
-    const float om = merge_s[wave ^ 1][0][lam];
-    const float m = fmaxf(st.m, om);
-    // a wave that met no key at all (maximum still -inf) holds zeros
-    const float f0 = st.m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(st.m - m);
-    const float f1 = om == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(om - m);
-    st.m = m;
-    st.l = st.l * f0 + merge_s[wave ^ 1][1][lam] * f1;
-    st.l_tail = st.l_tail * f0 + merge_s[wave ^ 1][2][lam] * f1;
-#pragma unroll
-    for (int dt = 0; dt < HDT; ++dt)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 w = *reinterpret_cast<LDS_PTR(const f32x4)>(theirs + (dt * 4 + g) * 1024);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) st.ot[dt][4 * g + i] = fmaf(st.ot[dt][4 * g + i], f0, w[i] * f1);
-      }
-  }
-
-  // ---- Phase 3, as in the main kernel, for this wave's channels ----
-  if (approx && p.first_order) {
-    const unsigned char* hp = reinterpret_cast<const unsigned char*>(p.hpack + bh * (size_t)(2 * D * D));
-    constexpr int HP_LOADS = 4 * D * D / (4 * 1024);
-    __syncthreads();                            // the merge has been read
-#pragma unroll
-    for (int i = 0; i < HP_LOADS; ++i) {
-      const unsigned off = (unsigned)__builtin_amdgcn_readfirstlane((int)((lc.wave * HP_LOADS + i) * 1024));
-      set_dma_lds_base(lds_addr + off);
-      dma_1kb<0>((unsigned)(lane * 16), hp + off);
-    }
-    wait_async_loads();
-    __syncthreads();
-    LDS_PTR(const unsigned char) hl = lds + lane * 16 + e * HDT * 1024;
-    f32x16 rt[HDT];
-#pragma unroll
-    for (int dt = 0; dt < HDT; ++dt) rt[dt] = (f32x16){0};
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks)
-#pragma unroll
-      for (int dt = 0; dt < HDT; ++dt) {
-        const bf16x8 ahi = *reinterpret_cast<LDS_PTR(const bf16x8)>(hl + (ks * NDT + dt) * 1024);
-        const bf16x8 alo = *reinterpret_cast<LDS_PTR(const bf16x8)>(hl + 2 * D * D + (ks * NDT + dt) * 1024);
-        rt[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi, qreg[ks], rt[dt], 0, 0, 0);
-        rt[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo, qreg[ks], rt[dt], 0, 0, 0);
-      }
-    const float w = st.l_tail / (float)L * p.scale;
-#pragma unroll
-    for (int dt = 0; dt < HDT; ++dt) st.ot[dt] += rt[dt] * w;
-  }
-
-  if (q_row < L) {
-    const float inv_l = 1.f / st.l;
-    __bf16* orow = p.out + (bh * (size_t)L + q_row) * D + 32 * HDT * e;
-#pragma unroll
-    for (int dt = 0; dt < HDT; ++dt)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const u32x2 w = {pack_bf16(st.ot[dt][4 * g] * inv_l, st.ot[dt][4 * g + 1] * inv_l),
-                         pack_bf16(st.ot[dt][4 * g + 2] * inv_l, st.ot[dt][4 * g + 3] * inv_l)};
-        *reinterpret_cast<u32x2*>(orow + 32 * dt + 8 * g + 4 * h) = w;
-      }
-    if (p.lse && h == 0 && e == 0)
-      p.lse[bh * (size_t)L + q_row] = (st.m + __builtin_amdgcn_logf(st.l)) * 0.69314718055994530942f;
-  }
-}
-
 }  // namespace
 
 // The kernels that walk two tiles per block without a trip list: dense_attention and block 128.
@@ -1404,31 +1405,8 @@ void attention_workspace_carve(const Dims& dm, void* workspace, void** kcen, voi
   *hpack = kc + 2 * tile_elems;
 }
 
-// Which kernel: up to how many 128-row workgroups of the main kernel the short one takes a call (us for the attention
-// step, main / short, head_dim 128 unless noted).  Up to 128 every 64-row workgroup has a CU to itself and the short
-// kernel is ahead everywhere (2 heads of 1 000 tokens 18.5 / 11.0, 16 heads of 1 024 with 1 of 16 blocks 16.0 / 13.5);
-// above, two share a CU that one main workgroup had, and it depends on what the call walks:
-//  - dense and block 128, where the main kernel walks one list: 176 (dense, 44 heads of 512 15.3 / 15.9, 7 of 3 000
-//    54.5 / 50.1, 12 of 2 048 (192 workgroups) 39.0 / 40.2; block 128, 11 heads of 2 048 with 5 of 16 blocks 25.6 / 23.9);
-//  - block 64, where it walks the union of two index rows: 320 (10 heads of 4 096 with 12 of 64 blocks 46.2 / 41.6,
-//    with 40 93.8 / 87; 384 workgroups 64.2 / 64.8);
-//  - where the union is hardly more than one row, past three quarters of the blocks at head_dim 128: 256 (1 head of 34 816
-//    with 490 of 544 blocks, 272 workgroups, 790 / 847; 5 of 8 192 with 116 of 128 207 / 214; 256 workgroups with 248 of 256
-//    blocks 336 / 275; at head_dim 64 the short kernel stays ahead, 701 / 558);
-//  - with no exact block, or one of 128 tokens, little is left but what every workgroup does once: 128 (11 heads of
-//    2 048, block 128, no block 13.0 / 14.3, one 16.4 / 17.0; block 64, no block 13.7 / 14.3; head_dim 64 and block 64, 320
-//    workgroups, 11.5 / 10.7).
-// With every block selected a call takes the line of the dense one, whose bits it has to give.
-static int short_call_limit(const Dims& dm, const AttnArgs& a) {
-  constexpr int kAlone = 128, kOneList = 176, kTwoPerCu = 256, kTwoLists = 320;
-  if (a.dense || a.k_top == dm.N) return kOneList;
-  if (dm.B != kTile) return a.k_top <= 1 ? kAlone : kOneList;
-  if (dm.d == 64) return kTwoLists;
-  if (a.k_top == 0) return kAlone;
-  return 4 * a.k_top > 3 * dm.N ? kTwoPerCu : kTwoLists;
-}
-
-// Which items an XCD takes.  Dense attention walks the same tiles in every workgroup of a head, so a head goes to one XCD.
+// Which items an XCD takes.  Dense attention (and r = 0) walks the same tiles in every workgroup of a head, so a head goes to
+// one XCD.
 // PISA workgroups walk different lists: while K and V of a head are not much larger than an XCD's L2 (4 MB), most of their
 // tiles are found there if one XCD has the head to itself (us for the attention step, all XCDs on one head / one head
 // each, r = 0.85: 12 heads of 8 192 125 / 107, 24 of 8 192 212 / 187, 24 of 4 608 85 / 82, 24 of 16 384 713 / 688, at block 128
@@ -1436,7 +1414,39 @@ static int short_call_limit(const Dims& dm, const AttnArgs& a) {
 // 40 000 3 803 / 3 818, 48 000 5 497 / 5 512), and from where the K and V of eight heads at once outgrow the 256 MB Infinity
 // Cache they are better taken one at a time (12 of 65 536 3 591 / 3 625, 40 of 75 600 23.1 / 24.7 ms).  The line: 12 MiB
 // each for K and V of a head, 192 MiB for eight.
-static bool heads_by_xcd(const Dims& dm) { return (size_t)dm.L * dm.d * 2 <= ((size_t)12 << 20); }
+static bool heads_by_xcd(const Dims& dm, const AttnArgs& a) {
+  return a.dense || a.k_top == dm.N || (size_t)dm.L * dm.d * 2 <= ((size_t)12 << 20);
+}
+
+// How many of an XCD's last items are taken by two workgroups of 64 rows each (attend_64_rows).
+// A call of few items lasts as long as one workgroup's chain of tiles, and the items past the last full round of the XCD's
+// 32 CUs keep some CUs busy for a whole item while others have none, all the more as the dispatcher puts two on the CU that
+// is free first; in halves they spread out.  Whole / halved, as geometric means of the attention step over 134 calls of 7
+// to 40 heads of 900 to 14 000 tokens:
+//  - one index row to an item (dense, block 128, nearly every block selected): up to 16 items over 1.04-1.09; from 17 on
+//    the halves, which load every tile twice as often, cost what they gain (0.93-1.01);
+//  - the union of two rows (a half walks its own row only): up to 16 over 1.10-1.16; 17 to 31 over a round of 64 workgroups
+//    1.04-1.11, over 32 of them 0.98-1.01 at head_dim 128; at head_dim 64, with three workgroups on a CU, 1.03-1.10
+//    wherever they lie, and 33 to 48 over a round of 64 in halves altogether 1.16-1.20.
+// Calls that are halved altogether: every 64-row workgroup has a CU to itself up to 16 items per XCD (2 heads of 1 000 tokens
+// 18.5 / 11.0 us); above, two share a CU that one item had, which pays up to 32 where an item walks two rows (10 heads of
+// 3 300 46.2 / 41.6; 256 items in all of 248 of 256 blocks 336 / 275), up to 24 (head_dim 64: 32) where it walks one (dense,
+// 17 items per XCD 1.30, 20 1.11, 24 1.09, 26 1.00), and not where there is no exact block, or one of 128 tokens (11 heads
+// of 2 048, block 128, no block 13.0 / 14.3).
+// The rule goes by sizes and k_top alone, and with every block selected it is the dense one, so that r = 0 keeps the bits
+// of dense_attention.
+static int halved_items(const Dims& dm, const AttnArgs& a, int per_xcd) {
+  constexpr int kCus = 32;
+  const int over = per_xcd % kCus, over2 = per_xcd % (2 * kCus);
+  const bool dense = a.dense || a.k_top == dm.N;
+  const bool little = !dense && (dm.B == kTile ? a.k_top == 0 && dm.d == 128 : a.k_top <= 1);
+  const bool two_rows = !dense && !little && dm.B == kTile && 4 * a.k_top <= 3 * dm.N;
+  const int all = little ? kCus / 2 : dm.d == 64 || (!dense && dm.B == kTile) ? kCus : 24;    // up to here the whole call
+  if (per_xcd <= all) return per_xcd;
+  if (two_rows && dm.d == 64) return over2 <= 48 ? over2 : over;
+  if (two_rows && over2 < kCus) return over;
+  return over <= kCus / 2 ? over : 0;
+}
 
 template <int D>
 static hipError_t launch_attention_bf16_d(const Dims& dm, const AttnArgs& a, hipStream_t stream) {
@@ -1456,18 +1466,11 @@ static hipError_t launch_attention_bf16_d(const Dims& dm, const AttnArgs& a, hip
   p.total = p.n_super * dm.bh();
   p.scale = dm.scale;
   p.first_order = a.hsum != nullptr;
-  p.by_xcd = heads_by_xcd(dm);
+  p.by_xcd = heads_by_xcd(dm, a);
 
-  const bool short_call = p.total <= short_call_limit(dm, a);
-  if (short_call) {
-    p.n_super = (dm.L + kTile - 1) / kTile;
-    p.total = p.n_super * dm.bh();
-  }
-  const int grid = ((p.total + 63) / 64) * 64;
-  if (a.dense && short_call) {
-    hipLaunchKernelGGL((attn_bf16_short_kernel<D, true, 1>), dim3(8 * ((p.total + 7) / 8)), dim3(256), 0, stream, p);
-    return hipGetLastError();
-  }
+  p.per_xcd = p.by_xcd ? (p.total + 7) / 8 : (p.total + 63) / 64 * 8;
+  p.n_whole = p.per_xcd - halved_items(dm, a, p.per_xcd);
+  const int grid = 8 * (2 * p.per_xcd - p.n_whole);
   if (a.dense) return launch_attention_two_tiles<D>(p, true, grid, stream);
   if (a.k_top < dm.N && a.kbar) {
     void *kcen_v, *vbar_v, *hpack_v;                      // kcen | vbar | hpack
@@ -1485,12 +1488,7 @@ static hipError_t launch_attention_bf16_d(const Dims& dm, const AttnArgs& a, hip
     p.vbar = vbar;
     p.hpack = hpack;
   }
-  if (short_call) {
-    if (dm.B == kTile) hipLaunchKernelGGL((attn_bf16_short_kernel<D, false, 1>), dim3(8 * ((p.total + 7) / 8)), dim3(256), 0, stream, p);
-    else hipLaunchKernelGGL((attn_bf16_short_kernel<D, false, 2>), dim3(8 * ((p.total + 7) / 8)), dim3(256), 0, stream, p);
-    return hipGetLastError();
-  }
-  if (pairing_pays(dm, a.k_top) && a.workspace) {
+  if (pairing_pays(dm, a.k_top) && a.workspace && p.n_whole > 0) {
     // the pairing scratch follows the pre-pass results (whether or not those are in use)
     unsigned char* after = static_cast<unsigned char*>(a.workspace) +
                            (size_t)dm.bh() * (2 * (size_t)p.npad * D * 2 + 2 * D * D * 2);

@@ -134,9 +134,8 @@ def test_sums_over_chunks(lib, dtype, H, L, d, B):
             assert float((log_m[0, h].exp() - norms).abs().max() / norms.max()) < 1e-9
 
 
-# bf16 attention: the kernel with 64 rows per workgroup (few workgroups) on both sides of its lines: 176 workgroups of
-# 128 rows for block 128, 320 for block 64, 256 for block 64 past three quarters of the blocks, 128 without an exact block or
-# with one of 128 tokens; ragged tiles of 1, 9, 33 and 63 rows, one and two centroid tiles, no full tile, no selected block
+# bf16 attention: calls of few items (most of them in halves of 64 rows altogether); ragged tiles of 1, 9, 33 and 63 rows,
+# one and two centroid tiles, no full tile, no selected block
 @pytest.mark.parametrize("L,H,d,B,r,check", [
     (40, 2, 128, 64, 0.0, [0, 1]), (65, 1, 64, 64, 0.5, [0]), (1000, 2, 128, 64, 0.8, [0, 1]),
     (64 * 3 + 33, 3, 128, 128, 0.5, [0, 2]), (64 * 5 + 63, 2, 64, 128, 1.0, [0, 1]), (64 * 9 + 9, 2, 128, 64, 1.0, [1]),
@@ -154,10 +153,38 @@ def test_bf16_short_calls(lib, L, H, d, B, r, check):
     run_full_case(lib, w, blocks_per_head=sorted({x for x in (0, 1, n // 2, n - 2, n - 1) if 0 <= x < n}), heads=check)
 
 
-@pytest.mark.parametrize("L,H,B", [(1000, 2, 64), (1400, 16, 64), (1400, 16, 128), (1500, 16, 64), (2048, 20, 64), (63, 1, 128)])
+# bf16 attention: which items of 128 rows are taken in halves, in items per XCD (an eighth of all)
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("L,H,B,r,check", [
+    (128 * 16, 8, 128, 0.95, [0, 7]),             # 16, one block of 128 tokens: all
+    (128 * 17, 8, 128, 0.95, [0, 7]),             # 17: none
+    (128 * 25 - 70, 8, 128, 0.8, [0, 7]),         # 25, one row to an item: none at head_dim 128, all at 64 (the last has one half)
+    (128 * 33 - 3, 8, 128, 0.8, [7]),             # 33: one
+    (128 * 32, 8, 64, 0.2, [7]),                  # 32, more than three quarters of the blocks: all
+    (128 * 49, 8, 64, 0.2, [7]),                  # 49: none
+    (128 * 48 - 64, 8, 64, 0.85, [0, 7]),         # 48, two rows to an item: 16, at head_dim 64 all; an odd number of blocks
+    (128 * 27 + 9, 14, 64, 0.8, [0, 13]),         # 49: none, at head_dim 64 17
+    (128 * 27 + 9, 24, 64, 0.9, [0, 23]),         # 84: 20
+])
+def test_bf16_halved_items(lib, L, H, B, r, check, d):
+    w = WORKLOADS["flux"].with_(name=f"halved-{L}-{H}", heads=H, seq_len=L, head_dim=d, block=B, sparsity=r, grid=None,
+                                seed=L + H)
+    n = -(-L // B)
+    run_full_case(lib, w, blocks_per_head=sorted({0, 1, n // 2, n - 2, n - 1}), heads=check)
+
+
+def test_bf16_halved_items_with_all_xcds_on_a_head(lib):
+    """A head too long for an XCD of its own: its 547 items are dealt in groups of 8, the last 35 (from row 65 536 on)
+    in halves, with paired query blocks."""
+    w = WORKLOADS["flux"].with_(name="halved-long", heads=1, seq_len=70000, head_dim=128, sparsity=0.95, grid=None, seed=3)
+    run_full_case(lib, w, blocks_per_head=[0, 1000, 1023, 1024, 1025, 1060, 1092, 1093], heads=[0])
+
+
+@pytest.mark.parametrize("L,H,B", [(1000, 2, 64), (1400, 16, 64), (1400, 16, 128), (1500, 16, 64), (2048, 20, 64), (63, 1, 128),
+                                   (128 * 33, 8, 64), (128 * 24, 8, 64), (128 * 25, 8, 64), (128 * 43 - 3, 8, 128)])
 @pytest.mark.parametrize("d", [64, 128])
 def test_bf16_all_blocks_selected_is_bitwise_dense(lib, L, H, B, d):
-    """Past the short kernel's line the number of blocks is even: the 128-row kernel walks the last of an odd number
+    """Where items are taken whole the number of blocks is even: a 128-row workgroup walks the last of an odd number
     on its own, in half tiles, whose row sums add up in another order."""
     w = WORKLOADS["flux"].with_(heads=H, seq_len=L, head_dim=d, block=B, sparsity=0.0, grid=None)
     q, k, v = (x.to(DEV) for x in make_qkv(w))
@@ -166,7 +193,8 @@ def test_bf16_all_blocks_selected_is_bitwise_dense(lib, L, H, B, d):
     assert torch.equal(res["out"], dense) and torch.equal(res["lse"], lse)
 
 
-# the pairing belongs to the 128-row kernel: the same checks at sizes past the short kernel's line (340 and 322 workgroups)
+# the pairing decides which blocks make an item: the same checks at sizes where items are taken whole as well as in halves
+# (43 and 41 items per XCD)
 @pytest.mark.parametrize("L,approximate", [(64 * 340 - 21, True), (64 * 322, True), (64 * 340 - 21, False)])
 def test_query_blocks_paired_in_long_calls(lib, L, approximate):
     test_gpu_parity.test_query_blocks_paired_by_row_similarity(lib, L, approximate)
