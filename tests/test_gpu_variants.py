@@ -304,8 +304,8 @@ def test_fp32_infinite_value_in_the_last_row(lib, d, L, H):
     assert bool((b[..., 3] == float("inf")).all()) and torch.equal(a[..., others], b[..., others])
 
 
-# The 128-row bf16 kernel past the short kernel's lines (12 workgroups a head at 1 409 and 1 500 tokens): what most of the small
-# shapes of test_gpu_parity.py no longer reach
+# bf16 items taken whole (12 items a head at 1 409 and 1 500 tokens; at head_dim 64 and block 64 from 49 per XCD on): what most
+# of the small shapes of test_gpu_parity.py do not reach
 @pytest.mark.parametrize("L,H,d,B,r,mode", [
     (1409, 29, 64, 64, 1.0, "hybrid"),           # no selected block
     (1409, 12, 64, 128, 1.0, "hybrid"),
@@ -313,6 +313,7 @@ def test_fp32_infinite_value_in_the_last_row(lib, d, L, H):
     (1409, 29, 64, 64, 0.7, "sparse"), (1409, 29, 128, 64, 0.7, "sparse"),      # 23 blocks: the last workgroup holds one
     (1409, 29, 128, 128, 0.7, "sparse"),
     (64 * 17 + 1, 40, 128, 64, 0.5, "hybrid"),
+    (1409, 37, 64, 64, 1.0, "hybrid"), (1409, 37, 64, 64, 0.7, "sparse"), (64 * 17 + 1, 46, 64, 64, 0.5, "hybrid"),
 ])
 def test_bf16_long_calls(lib, L, H, d, B, r, mode):
     w = WORKLOADS["flux"].with_(name=f"long-{L}-{H}-{mode}", heads=H, seq_len=L, head_dim=d, block=B, sparsity=r, grid=None,
@@ -334,11 +335,11 @@ def _check_heads(lib, q, k, v, B, idx, out, heads, blocks, scale, mode="hybrid",
 
 
 @pytest.mark.parametrize("direction", ["rising", "falling", "spike"])
-@pytest.mark.parametrize("d", [64, 128])
-def test_runaway_maximum_in_long_calls(lib, direction, d):
-    """test_runaway_maximum past the short kernel's lines (18 workgroups a head: 324 in all), so that the 128-row kernel, whose
-    maximum is refreshed only when a tile sum nears overflow, takes the dense and the sparse call."""
-    L, H, B = 2304, 18, 64
+@pytest.mark.parametrize("d,H", [(64, 18), (128, 18), (64, 22)])
+def test_runaway_maximum_in_long_calls(lib, direction, d, H):
+    """test_runaway_maximum with items taken whole (18 a head; 64 channels, sparse: at 22 heads), where the
+    maximum is refreshed only when a tile sum nears overflow."""
+    L, B = 2304, 64
     w = WORKLOADS["flux"].with_(name=f"runaway-{direction}", heads=H, seq_len=L, head_dim=d, grid=None, sparsity=0.5)
     q, k, v = make_qkv(w, device="cpu")
     u = torch.zeros(d)
@@ -358,11 +359,11 @@ def test_runaway_maximum_in_long_calls(lib, direction, d):
     _check_heads(lib, q, k, v, B, res["idx"][0].cpu().numpy(), res["out"], [0, H - 1], blocks, scale, "hybrid", direction)
 
 
-@pytest.mark.parametrize("d", [64, 128])
-def test_out_of_range_index_entries_in_long_calls(lib, d):
+@pytest.mark.parametrize("d,H", [(64, 28), (128, 28), (64, 37)])
+def test_out_of_range_index_entries_in_long_calls(lib, d, H):
     """Entries outside [0, N) at different places of the two rows of a 128-row workgroup: their lists differ in length, so
     that some tiles of either are left without a partner."""
-    L, H, B = 1500, 28, 64
+    L, B = 1500, 64
     w = WORKLOADS["flux"].with_(name="badidx", heads=H, seq_len=L, head_dim=d, grid=None, sparsity=0.6)
     q, k, v = make_qkv(w, device="cpu")
     qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
@@ -381,9 +382,9 @@ def test_out_of_range_index_entries_in_long_calls(lib, d):
     _check_heads(lib, q, k, v, B, kept, out, [0, H - 1], list(range(n)), scale)
 
 
-@pytest.mark.parametrize("d,scale", [(128, 0.2), (64, 0.01)])
-def test_custom_softmax_scale_in_long_calls(lib, d, scale):
-    L, H, B = 1409, 29, 64
+@pytest.mark.parametrize("d,scale,H", [(128, 0.2, 29), (64, 0.01, 29), (64, 0.01, 37)])
+def test_custom_softmax_scale_in_long_calls(lib, d, scale, H):
+    L, B = 1409, 64
     w = WORKLOADS["flux"].with_(name=f"scale-{scale}", heads=H, seq_len=L, head_dim=d, grid=None, sparsity=0.75)
     q, k, v = make_qkv(w, device="cpu")
     qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
@@ -396,7 +397,7 @@ def test_custom_softmax_scale_in_long_calls(lib, d, scale):
 
 
 def test_static_scratch_in_long_calls(lib):
-    """pisa_attention_static with the pairing tables in the built-in scratch (340 workgroups, 340 blocks): the bits of the call
+    """pisa_attention_static with the pairing tables in the built-in scratch (340 items, 340 blocks): the bits of the call
     with a workspace."""
     w = WORKLOADS["flux"].with_(heads=2, seq_len=64 * 340 - 21, grid=None, sparsity=0.85)
     q, k, v = (x.to(DEV) for x in make_qkv(w, device="cpu"))
