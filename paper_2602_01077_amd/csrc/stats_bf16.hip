@@ -86,6 +86,23 @@ __device__ inline bf16x8 read_operand(LDS_PTR(const unsigned char) tile, int lan
 // 40 heads of 75 600 598 -> 571 us = 4.1 TB/s); at 64 a wave has half the rows and an eighth of the MFMAs,
 // and there are only four 32 x 32 tiles of H to hand out: four waves.
 constexpr int stats_waves(int d) { return d == 128 ? 8 : 4; }
+constexpr int kNormBlocks = 8;      // (head_dim 128, block 128: two workgroups fill the LDS to the byte)
+
+// Sum over the wave by lane permutations on the vector ALU.
+template <int CTRL> __device__ inline double add_dpp(double x) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xf, 0xf, true);
+  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
+  return x + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ inline double wave_sum(double x) {
+  x = add_dpp<0xb1>(x);              // lane ^ 1
+  x = add_dpp<0x4e>(x);              // lane ^ 2
+  x = add_dpp<0x141>(x);             // mirrored inside 8 lanes
+  x = add_dpp<0x140>(x);             // mirrored inside 16 lanes: every lane has its row's sum
+  x += __shfl_xor(x, 16);
+  return x + __shfl_xor(x, 32);
+}
 
 template <int D, int TPB, bool HETERO>
 __global__ __launch_bounds__(64 * stats_waves(D), D == 128 ? 4 : 2) void stats_bf16_kernel(
@@ -112,7 +129,7 @@ __global__ __launch_bounds__(64 * stats_waves(D), D == 128 ? 4 : 2) void stats_b
   __shared__ float vsub[2][D];          // sub-block value sums Vhat_s
   __shared__ float dks[2][D];           // c_s - kbar_j
   __shared__ float kmean_s[D];
-  __shared__ double hnorm_s[NW];         // HETERO: per-wave sums of squares
+  __shared__ double hnorm_s[HETERO ? kNormBlocks : 1][NW];         // HETERO: per-wave sums of squares
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: row addresses stay scalar
@@ -135,9 +152,20 @@ __global__ __launch_bounds__(64 * stats_waves(D), D == 128 ? 4 : 2) void stats_b
 #pragma unroll
   for (int bt = 0; bt < NB; ++bt) acc[bt] = (f32x16){0};
 
-  // HETERO: 1 / N, and this head's hsum (read per block from L2: 64 more registers would not fit)
+  // HETERO: 1 / N, and the elements of this head's hsum at this lane's accumulator positions (see the store at the end).
+  // Kept in registers; read per block from L2 (16 at a time) only at head_dim 128 with two sub-blocks, where they do not fit
+  // (40 heads of 20 000 tokens 163 us with every block reading them, 135 kept).
+  constexpr bool KEEP_HSUM = !(D == 128 && TPB == 2);
   const float inv_n = 1.f / (float)N;
   const float* hs_head = HETERO ? hsum + bh * (size_t)D * D : nullptr;
+  float hb[HETERO && KEEP_HSUM ? NB : 1][16];
+  auto load_hsum = [&](const float* hp, unsigned off, int bt, float (&x)[16]) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[r] = (hp + (32 * ktile + (r / 4) * 8 + (r % 4)) * D + 32 * (vtile0 + bt))[off];
+  };
+  if (HETERO && KEEP_HSUM)
+#pragma unroll
+    for (int bt = 0; bt < NB; ++bt) load_hsum(hs_head, 4 * h * D + lam, bt, hb[bt]);
 
   // Optional second form of the block outputs, for the attention kernel's centroid phase: the
   // key mean and the value mean of block j as bf16 rows of tiles [bh][npad][D] (the fp32
@@ -323,36 +351,39 @@ __global__ __launch_bounds__(64 * stats_waves(D), D == 128 ? 4 : 2) void stats_b
       __syncthreads();                            // dks / vsub / tot are rewritten by the next block
     }
     if (HETERO) {
-      // acc holds H_j; this lane's elements sit at fixed positions of the matrix
+      // acc holds H_j
       double ss = 0.0;
       const float* hp = hs_head;
       unsigned hoff = 4 * h * D + lam;
-      asm volatile("" : "+s"(hp));    // keeps the loads below inside the block loop (hoisted, they spill), and at
-      if (D == 128) asm volatile("" : "+v"(hoff));    // head_dim 128 their addresses as well
+      if (!KEEP_HSUM) {             // the loads and their addresses stay inside the block loop (hoisted, they spill)
+        asm volatile("" : "+s"(hp));
+        asm volatile("" : "+v"(hoff));
+      }
 #pragma unroll
       for (int bt = 0; bt < NB; ++bt) {
-        float hb[16];                 // the elements of hsum at this lane's accumulator positions (see the store below)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          hb[r] = (hp + (32 * ktile + (r / 4) * 8 + (r % 4)) * D + 32 * (vtile0 + bt))[hoff];
+        float (&hx)[16] = hb[KEEP_HSUM ? bt : 0];
+        if (!KEEP_HSUM) load_hsum(hp, hoff, bt, hx);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const double dlt = (double)fmaf(-hb[r], inv_n, acc[bt][r]);   // both terms carry fp32 rounding already
+          const double dlt = (double)fmaf(-hx[r], inv_n, acc[bt][r]);   // both terms carry fp32 rounding already
           ss = fma(dlt, dlt, ss);
           acc[bt][r] = 0.f;
         }
       }
+      ss = wave_sum(ss);
+      // The norms are finished kNormBlocks at a time, a thread per block.
+      const int at = (j - j_begin) % kNormBlocks;
+      if (lane == 0) hnorm_s[at][wave] = ss;
+      if (at == kNormBlocks - 1 || j == j_end - 1) {
+        __syncthreads();
+        if (tid <= at) {
+          double sum = hnorm_s[tid][0];
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-      if (lane == 0) hnorm_s[wave] = ss;
-      __syncthreads();
-      if (tid == 0) {
-        double sum = hnorm_s[0];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) sum += hnorm_s[w];
-        log_m[bh * N + j] = log(sqrt(sum) + eps);
+          for (int w = 1; w < NW; ++w) sum += hnorm_s[tid][w];
+          log_m[bh * N + j - at + tid] = log(sqrt(sum) + eps);
+        }
+        // hnorm_s is written again only after the next block's barriers
       }
-      // hnorm_s is written again only after the next block's barriers
     }
   }
   if (HETERO) return;
@@ -390,7 +421,10 @@ hipError_t launch_block_stats_bf16(const Dims& dm, const void* q, const void* k,
 // accuracy, the accuracy hsum itself has).
 hipError_t launch_block_heterogeneity_fast(const Dims& dm, const void* k, const void* v, const float* hsum,
                                            double eps, double* log_m, hipStream_t stream) {
-  const StatsPlan plan = stats_plan(dm);
+  StatsPlan plan = stats_plan(dm);
+  // No partial sums are written here: chunks of two blocks at most (24 heads of 72 blocks 25.9 -> 24.6 us, 40 of 47
+  // 27.3 -> 25.5) where a workgroup would have few.
+  if (dm.B == kTile && plan.chunk_blocks > 2 && plan.chunk_blocks <= 4) plan = {2, (dm.N + 1) / 2};
   const dim3 grid(plan.n_chunks, dm.bh());
 #define PISA_HET_FAST(DD, TPB)                                                                              \
   hipLaunchKernelGGL((stats_bf16_kernel<DD, TPB, true>), grid, dim3(64 * stats_waves(DD)), 0, stream, nullptr,               \

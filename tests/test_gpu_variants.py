@@ -94,6 +94,20 @@ def test_spectral_heterogeneity_of_special_blocks(lib, d, dtype, B):
         assert np.abs(np.exp(log_m) - 1e-6 - M).max() <= 1e-9 * M.max(), norm
 
 
+@pytest.mark.parametrize("d,B", [(128, 64), (128, 128), (64, 64), (64, 128)])
+@pytest.mark.parametrize("H,L", [(2, 64 * 9 + 5), (40, 64 * 76 + 13), (40, 64 * 520 + 64)])
+def test_fast_heterogeneity_over_many_blocks(lib, H, L, d, B):
+    """Workgroups of the fast Frobenius kind with 1 to 21 blocks (the norms are finished eight at a time), against the exact
+    kind: both take H_bar from the same fp32 hsum, and the fast one carries fp32 rounding (1e-7 measured)."""
+    g = torch.Generator(device=DEV).manual_seed(L + d)
+    k, v = (torch.randn(1, H, L, d, generator=g, device=DEV).bfloat16() for _ in range(2))
+    shape = lib.make_shape(k, B)
+    st = lib.block_stats(k, k, v, B)
+    exact, fast = (lib.block_heterogeneity(shape, k, v, st["kbar64"], n, 1e-6, hsum=st["hsum"]).exp()
+                   for n in (lib.PISA_NORM_FROBENIUS, lib.PISA_NORM_FROBENIUS_FAST))
+    assert float(((fast - exact).abs().amax(-1) / exact.amax(-1)).max()) <= 1e-6
+
+
 def test_spectral_heterogeneity_of_identical_blocks(lib):
     """All blocks alike: H_j - H_bar is rounding only, log(M + eps) is log(eps) to the last digits."""
     g = torch.Generator().manual_seed(5)
