@@ -90,19 +90,34 @@ StatsPlan matrix_bound_plan(const Dims& dm) {
   return plan_of_chunk(dm, best);
 }
 
+// The smallest chunk with which a launch has at most `groups` workgroups (one per head at least).
+static int chunk_for(const Dims& dm, int groups) {
+  const int chunks = std::min(dm.N, std::max(1, groups / dm.bh()));
+  return (dm.N + chunks - 1) / chunks;
+}
+
 StatsPlan stats_plan(const Dims& dm) {
-  if (dm.dtype == PISA_FP32 && few_blocks(dm)) return matrix_bound_plan(dm);
-  // The streaming kernels keep two workgroups on each of the 256 compute units, and all
-  // their workgroups take about the same time: the launch should be a whole number of rounds
-  // of 512, never a few workgroups more.  Aim at two rounds (one when that still leaves a
-  // workgroup only a handful of blocks, to halve the partial sums written and re-read).
-  const int kSlots = 512;
-  int target = 2 * kSlots;
-  if (few_blocks(dm)) target = kSlots;
-  int want = target / dm.bh();
-  if (want < 1) want = 1;
-  if (want > dm.N) want = dm.N;
-  return plan_of_chunk(dm, (dm.N + want - 1) / want);
+  if (dm.dtype == PISA_FP32) {
+    if (few_blocks(dm)) return matrix_bound_plan(dm);
+    return plan_of_chunk(dm, chunk_for(dm, 1024));
+  }
+  // bf16: all workgroups of a launch take about as long, so it is one round of them, never a few more (head_dim 128: two on
+  // each of the 256 compute units, 64: three).  Two rounds balance no better and write twice the partial sums, which are read
+  // again: statistics with their reduction, us, two rounds / one: 24 heads of 16 384 97.1 / 84.1, 13 of 30 000 97.3 / 83.2,
+  // 5 of 60 000 76.9 / 64.5, 40 of 75 600 570.5 / 567.6; head_dim 64, 24 of 16 384 43.5 / 35.8, 40 of 32 768 139.5 / 127.2.
+  if (!few_blocks(dm)) {
+    const int slots = dm.d == 64 ? 768 : 512;
+    const int one = chunk_for(dm, slots), two = chunk_for(dm, 2 * slots);
+    return plan_of_chunk(dm, 2 * two < one - one / 8 ? two : one);      // two where the heads do not divide the slots
+  }
+  // Few blocks: a workgroup that has a compute unit to itself is nearly twice as fast, and half the partial sums go to
+  // the reduction, so at head_dim 128 the launch has one a unit unless that costs twice the blocks (one call, us, one / two a
+  // unit: 12 heads of 3 000 48.6 / 50.6, 28 of 2 500 67.6 / 69.0, 10 of 4 000 54.0 / 57.0; 24 of 4 608, eight blocks
+  // against four, 111.1 / 109.0).
+  const int beside = chunk_for(dm, 512);
+  if (dm.d == 64) return plan_of_chunk(dm, beside);
+  const int alone = chunk_for(dm, 256);
+  return plan_of_chunk(dm, alone < 2 * beside || beside == 1 ? alone : beside);
 }
 
 static size_t stats_workspace_bytes(const Dims& dm) {

@@ -389,7 +389,8 @@ __global__ __launch_bounds__(1024) void select_small_kernel(const double* __rest
 // The same selection plus, in the workgroups past the first n_groups of a head, the reduction of
 // the statistics pass's partial H sums (independent work on the same inputs' statistics: one
 // launch instead of two on short sequences).
-template <int D>
+// E: elements per thread, 1024 apart (consecutive threads stay on consecutive addresses).
+template <int D, int E>
 __global__ __launch_bounds__(1024) void select_small_reduce_kernel(
     const double* __restrict__ qbar64, const double* __restrict__ kbar64, const double* __restrict__ col_bias,
     int N, double scale, int k_top, int32_t* __restrict__ idx, float* __restrict__ kth_gap, int n_groups,
@@ -398,11 +399,18 @@ __global__ __launch_bounds__(1024) void select_small_reduce_kernel(
   if ((int)blockIdx.x < n_groups) {
     select_small_body<D>(qbar64, kbar64, col_bias, N, scale, k_top, idx, kth_gap, blockIdx.x, blockIdx.y);
   } else {
-    // four elements per thread, 1024 apart (consecutive threads stay on consecutive addresses):
-    // few workgroups, so that the whole launch is resident at once
-    const int e0 = ((int)blockIdx.x - n_groups) * 4096 + (int)threadIdx.x;
-    reduce_h_elements<4>(partial_h, hsum, hpack, n_chunks, D, blockIdx.y, e0, 1024);
+    const int e0 = ((int)blockIdx.x - n_groups) * (E * 1024) + (int)threadIdx.x;
+    reduce_h_elements<E>(partial_h, hsum, hpack, n_chunks, D, blockIdx.y, e0, 1024);
   }
+}
+
+template <int D, int E>
+void launch_select_reduce(const Dims& dm, const double* qbar64, const double* kbar64, const double* col_bias, int k_top,
+                          int32_t* idx, float* kth_gap, const PendingReduce& pending, hipStream_t stream) {
+  const int n_groups = (dm.N + 15) / 16;
+  hipLaunchKernelGGL((select_small_reduce_kernel<D, E>), dim3(n_groups + D * D / (1024 * E), dm.bh()), dim3(1024), 0,
+                     stream, qbar64, kbar64, col_bias, dm.N, (double)dm.scale, k_top, idx, kth_gap, n_groups,
+                     pending.partial_h, pending.hsum, (unsigned short*)pending.hpack, pending.n_chunks);
 }
 
 }  // namespace
@@ -419,16 +427,13 @@ hipError_t launch_select(const Dims& dm, const double* qbar64, const double* kba
   const int nt = (dm.N + kZT - 1) / kZT;
   if (pending && !select_fuses_reduce(dm)) return hipErrorInvalidValue;   // the caller checks first
   if (dm.N <= kFusedMaxN && pending) {                    // selection and H reduction in one launch
-    const int n_groups = (dm.N + 15) / 16;
-    const dim3 fgrid(n_groups + (dm.d * dm.d + 4095) / 4096, dm.bh());
-    if (dm.d == 64)
-      hipLaunchKernelGGL(select_small_reduce_kernel<64>, fgrid, dim3(1024), 0, stream, qbar64, kbar64, col_bias,
-                         dm.N, (double)dm.scale, k_top, idx, kth_gap, n_groups, pending->partial_h,
-                         pending->hsum, (unsigned short*)pending->hpack, pending->n_chunks);
-    else
-      hipLaunchKernelGGL(select_small_reduce_kernel<128>, fgrid, dim3(1024), 0, stream, qbar64, kbar64, col_bias,
-                         dm.N, (double)dm.scale, k_top, idx, kth_gap, n_groups, pending->partial_h,
-                         pending->hsum, (unsigned short*)pending->hpack, pending->n_chunks);
+    // Few heads: one element a thread and sixteen loads in flight, 16 workgroups a head (head_dim 64: 4); with more heads
+    // the launch is resident at once only with four elements a thread (one call, us, four / one: 2 heads of 8 000 with 125
+    // chunks 55.3 / 43.1, 4 of 4 000 39.8 / 32.9, 2 of 1 000 23.6 / 22.9, 12 of 3 000 48.6 / 49.2, 24 of 4 608 109.0 / 111.8).
+    const bool wide = dm.d * dm.d / 1024 * dm.bh() <= 128;
+    auto* launch = dm.d == 64 ? (wide ? launch_select_reduce<64, 1> : launch_select_reduce<64, 4>)
+                              : (wide ? launch_select_reduce<128, 1> : launch_select_reduce<128, 4>);
+    launch(dm, qbar64, kbar64, col_bias, k_top, idx, kth_gap, *pending, stream);
     return hipGetLastError();
   }
   if (dm.N <= kFusedMaxN) {                               // one launch for short sequences

@@ -14,6 +14,8 @@
 //     tokens, so both come from ds_read_b64_tr_b16.
 // The partial H of the chunk goes to scratch; partials are added in chunk order by the
 // caller's reduction kernel, so hsum is run-to-run identical.
+#include <algorithm>
+
 #include "common.h"
 
 namespace pisa {
@@ -422,9 +424,13 @@ hipError_t launch_block_stats_bf16(const Dims& dm, const void* q, const void* k,
 hipError_t launch_block_heterogeneity_fast(const Dims& dm, const void* k, const void* v, const float* hsum,
                                            double eps, double* log_m, hipStream_t stream) {
   StatsPlan plan = stats_plan(dm);
-  // No partial sums are written here: chunks of two blocks at most (24 heads of 72 blocks 25.9 -> 24.6 us, 40 of 47
-  // 27.3 -> 25.5) where a workgroup would have few.
-  if (dm.B == kTile && plan.chunk_blocks > 2 && plan.chunk_blocks <= 4) plan = {2, (dm.N + 1) / 2};
+  // No partial sums are written here: where a workgroup would have few blocks they go in twos (24 heads of 72 blocks
+  // 25.9 -> 24.6 us, 40 of 47 27.3 -> 25.5); blocks of 128, each with its own read of hsum, go as 512 workgroups.
+  if ((long long)dm.N * dm.bh() <= 4096) {
+    const int chunks = std::min(dm.N, std::max(1, 512 / dm.bh()));
+    const int c = dm.B == kTile ? 2 : (dm.N + chunks - 1) / chunks;
+    plan = {c, (dm.N + c - 1) / c};
+  }
   const dim3 grid(plan.n_chunks, dm.bh());
 #define PISA_HET_FAST(DD, TPB)                                                                              \
   hipLaunchKernelGGL((stats_bf16_kernel<DD, TPB, true>), grid, dim3(64 * stats_waves(DD)), 0, stream, nullptr,               \

@@ -94,6 +94,23 @@ def test_spectral_heterogeneity_of_special_blocks(lib, d, dtype, B):
         assert np.abs(np.exp(log_m) - 1e-6 - M).max() <= 1e-9 * M.max(), norm
 
 
+# Reduction of the partial H sums, one element a thread (few heads) and four, over chunk counts around the sixteen and the
+# eight loads in flight; one call (reduction inside the selection's launch) and three calls (a launch of its own)
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("H,n", [(1, 1), (2, 15), (2, 16), (2, 17), (8, 32), (8, 33), (9, 128), (33, 128), (33, 40), (2, 129)])
+def test_reduction_of_partial_sums(lib, H, n, d):
+    """hsum against fp64: |error| <= 1e-4 of the head's largest element, as for the statistics everywhere; the two ways
+    give the same bits."""
+    w = WORKLOADS["flux"].with_(name="reduce", heads=H, seq_len=64 * n - 3, head_dim=d, sparsity=0.8, grid=None, seed=n)
+    q, k, v = (x.to(DEV) for x in make_qkv(w, device="cpu"))
+    res = lib.forward_in_steps(q, k, v, 64, w.sparsity)
+    one, _ = lib.forward(lib.make_shape(q, 64), q, k, v, res["k_top"])
+    assert torch.equal(one, res["out"])
+    ref = _centred_products(k[0, H - 1].cpu(), v[0, H - 1].cpu(), 64).sum(0).numpy()
+    got = res["stats"]["hsum"][0, H - 1].cpu().numpy()
+    assert np.abs(got - ref).max() <= 1e-4 * np.abs(ref).max()
+
+
 @pytest.mark.parametrize("d,B", [(128, 64), (128, 128), (64, 64), (64, 128)])
 @pytest.mark.parametrize("H,L", [(2, 64 * 9 + 5), (40, 64 * 76 + 13), (40, 64 * 520 + 64)])
 def test_fast_heterogeneity_over_many_blocks(lib, H, L, d, B):
