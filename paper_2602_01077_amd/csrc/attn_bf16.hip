@@ -47,6 +47,29 @@
 #include "common.h"
 
 namespace pisa {
+
+struct PB {
+  const __bf16* q;
+  const __bf16* k;
+  const __bf16* v;
+  const __bf16* kcen;     // [bh][npad][D] kbar_j rounded to bf16    (pre-pass)
+  const __bf16* vbar;     // [bh][npad][D] vsum_j / B_j
+  const __bf16* hpack;    // [bh][2][D/16 ks][D/32 dt][64 lanes][8] hsum^T hi / lo in A-operand order
+  const int32_t* idx;
+  __bf16* out;
+  float* lse;
+  int L, B, N, k_top, npad, n_super, total;
+  float scale;
+  int first_order;
+  int by_xcd;             // see the launch
+  int per_xcd, n_whole;   // items per XCD; how many of them a workgroup takes whole (the rest: two, 64 rows each)
+  const int32_t* pair;    // block 64 only, may be null: [bh][2 * n_super] query blocks of each workgroup (-1: none)
+};
+
+// The block-64 kernel for four workgroups on a CU (head_dim 64) is compiled by itself, from this file with PISA_ATTN_FOUR set
+// (build.py): a lane has 128 registers there, and the scheduler the other kernels are built with spills in its walk.
+hipError_t launch_attention_four(const PB& p, int grid, hipStream_t stream);
+
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -74,24 +97,7 @@ template <int D> struct Geo {
 };
 constexpr int QROWS = 128;                   // query rows per workgroup
 constexpr int MASK_WORDS = kMaxBlocks / 32;  // 128 words per block bitmask
-
-struct PB {
-  const __bf16* q;
-  const __bf16* k;
-  const __bf16* v;
-  const __bf16* kcen;     // [bh][npad][D] kbar_j rounded to bf16    (pre-pass)
-  const __bf16* vbar;     // [bh][npad][D] vsum_j / B_j
-  const __bf16* hpack;    // [bh][2][D/16 ks][D/32 dt][64 lanes][8] hsum^T hi / lo in A-operand order
-  const int32_t* idx;
-  __bf16* out;
-  float* lse;
-  int L, B, N, k_top, npad, n_super, total;
-  float scale;
-  int first_order;
-  int by_xcd;             // see the launch
-  int per_xcd, n_whole;   // items per XCD; how many of them a workgroup takes whole (the rest: two, 64 rows each)
-  const int32_t* pair;    // block 64 only, may be null: [bh][2 * n_super] query blocks of each workgroup (-1: none)
-};
+constexpr int kMergeFloats = 4 * 3 * 32;     // [wave][max, sum, tail sum][32] of a 64-row workgroup
 
 __device__ inline unsigned int pack_bf16(float lo, float hi) {
   f32x2 f = {lo, hi};
@@ -879,19 +885,26 @@ __device__ __forceinline__ void attend_64_rows(const PB& p, const size_t bh, con
 
 // LDS map of the staging area (byte offsets): K stages | V stages; Phase 2 reuses it as
 // centroid keys (K stage 0) and centroid values (V stage 0).
-// Three workgroups per CU at head_dim 64 (168 VGPRs, 33 KB LDS each), two at 128.
+// WGS: workgroups on a CU, which the registers of a lane go by.  Two at head_dim 128 (226 VGPRs, 67-77 KB LDS), three at 64
+// (152 VGPRs, 34-45 KB; the dense kernel needs so few that it runs four).  The block-64 kernel at head_dim 64 exists with four
+// as well (128 VGPRs, 40 KB): softmax and products take turns in a wave, and a fourth wave on a SIMD fills what three leave
+// idle, though its code is 1-3 % slower where three are all a CU gets (the rule stands at the launch).  40 heads of 32 768
+// tokens, r = 0.85, three / four: 2 340 / 2 245 us; 40 of 75 600 12 200 / 11 900.
 // TPB: 64-key tiles per block of the selection (1: block 64, two query blocks per workgroup;
 // 2: block 128, one); the dense kernel is built with TPB = 2 (it has no block lists).
-template <int D, bool DENSE, int TPB>
-__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
+template <int D, bool DENSE, int TPB, int WGS = D == 128 ? 2 : 3>
+__global__ __launch_bounds__(256, WGS) void attn_bf16_kernel(PB p) {
+  constexpr bool LISTS = !DENSE && TPB == 1;
+  constexpr bool TIGHT = WGS == 4;              // on registers: cheap values are made anew where they are wanted
   constexpr int ROWB = Geo<D>::ROWB, TILEB = Geo<D>::TILEB, NKS = Geo<D>::NKS, NDT = Geo<D>::NDT;
   constexpr int CPR = Geo<D>::CPR, RPL = Geo<D>::RPL;
   constexpr int KST0 = 0, KST1 = TILEB, VST0 = 2 * TILEB, VST1 = 3 * TILEB;
   __shared__ __attribute__((aligned(1024))) unsigned char stage[4 * TILEB];   // K0 | K1 | V0 | V1
   __shared__ unsigned int chosen[2][MASK_WORDS];
   __shared__ __attribute__((aligned(16))) float bias_s[2][2][kTile];          // [stage parity][query block][centroid]
-  __shared__ float merge_s[4 * 3 * 32];
-  __shared__ unsigned short trip_list[DENSE || TPB == 2 ? 2 : kMaxBlocks + 2];          // Phase-1 walk of a block-64 workgroup
+  // Phase-1 walk of a block-64 workgroup, list_bytes() of it; the 64-row workgroups, which have none, merge there
+  extern __shared__ __attribute__((aligned(16))) unsigned short trip_list[];
+  __shared__ float merge_own[LISTS ? 1 : kMergeFloats];
   __shared__ unsigned short pre_s[DENSE || TPB == 2 ? 1 : MASK_WORDS + 1], pre_a[DENSE || TPB == 2 ? 1 : MASK_WORDS + 1],
       pre_b[DENSE || TPB == 2 ? 1 : MASK_WORDS + 1];                                   // tiles below each mask word, by class
 
@@ -910,7 +923,8 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
     if (!DENSE && TPB == 1 && p.pair) qt = __builtin_amdgcn_readfirstlane(p.pair[(bh * p.n_super + sg) * 2 + half]);
     if (qt >= 0 && qt * kTile < p.L)
       attend_64_rows<D, DENSE, TPB>(p, bh, qt, ShortLds{(LDS_PTR(unsigned char)) & stage[0], (LDS_PTR(unsigned int)) & chosen[0][0],
-                                                        (LDS_PTR(float)) & bias_s[0][0][0], (LDS_PTR(float)) & merge_s[0]});
+                                                        (LDS_PTR(float)) & bias_s[0][0][0],
+                                                        LISTS ? (LDS_PTR(float))&trip_list[0] : (LDS_PTR(float))&merge_own[0]});
     return;
   }
 
@@ -971,9 +985,12 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
   }
 
   // ---- Q^T operand: this lane's query row, D/16 channel slices of 16 ----
-  const int my_blk = (!DENSE && tpb == 1) ? blk[wave >> 1] : -1;
-  const int q_row = (!DENSE && tpb == 1) ? (my_blk < 0 ? L : my_blk * kTile + 32 * (wave & 1) + lam)
-                                         : sg * QROWS + 32 * wave + lam;
+  auto row_of = [&](int t) {                         // of thread t; L: none
+    if constexpr (!LISTS) return sg * QROWS + 32 * (t >> 6) + (t & 31);
+    const int b = t >> 7 ? blk[1] : blk[0];
+    return b < 0 ? L : b * kTile + 32 * ((t >> 6) & 1) + (t & 31);
+  };
+  const int q_row = row_of(tid);
   bf16x8 qreg[NKS];
   {
     const __bf16* qg = p.q + bh * (size_t)L * D;
@@ -1295,14 +1312,16 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
       constexpr int P = decltype(parity_tag)::value;
       load_tile_async<D, true>(lc, kcg + (size_t)g0 * ROWB, kTile, lds_addr + (P ? KST1 : KST0));
       load_tile_async<D, false>(lc, vbg + (size_t)g0 * ROWB, kTile, lds_addr + (P ? VST1 : VST0));
-      if (tid < 2 * kTile) {
-        const int b = tid >> 6, j = g0 + (tid & 63);
+      int t = tid;
+      if (TIGHT) asm volatile("" : "+v"(t));
+      if (t < 2 * kTile) {
+        const int b = t >> 6, j = g0 + (t & 63);
         const bool masked =
             (tpb == 2 && b == 1) ? true : ((chosen[b][(j >> 5) & (MASK_WORDS - 1)] >> (j & 31)) & 1u);
         // log2 B_j for a centroid that stands for its block; computed here (two values per
         // call), so that no ordinary load, and with it no wait on the tile loads just issued,
         // sits in this step
-        bias_s[P][b][tid & 63] = (masked || j >= N) ? -INFINITY : (j == N - 1 ? log2_last : log2_full);
+        bias_s[P][b][t & 63] = (masked || j >= N) ? -INFINITY : (j == N - 1 ? log2_last : log2_full);
       }
     };
     auto absorb = [&](int g0, auto parity_tag) {
@@ -1364,9 +1383,12 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
   }
 
   // ---- normalise and store: register group g of tile dt = channels 32 dt + 8 g + 4 h + 0..3 ----
-  if (q_row < L) {
+  int t = tid;
+  if (TIGHT) asm volatile("" : "+v"(t));
+  const int out_row = row_of(t);
+  if (out_row < L) {
     const float inv_l = 1.f / st.l;
-    __bf16* orow = p.out + (bh * (size_t)L + q_row) * D;
+    __bf16* orow = p.out + (bh * (size_t)L + out_row) * D;
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
@@ -1376,12 +1398,21 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bf16_kernel(PB p) {
         *reinterpret_cast<u32x2*>(orow + 32 * dt + 8 * g + 4 * h) = w;
       }
     if (p.lse && h == 0)
-      p.lse[bh * (size_t)L + q_row] = (st.m + __builtin_amdgcn_logf(st.l)) * 0.69314718055994530942f;
+      p.lse[bh * (size_t)L + out_row] = (st.m + __builtin_amdgcn_logf(st.l)) * 0.69314718055994530942f;
   }
 }
 
+// LDS the block-64 kernel is launched with: the trip list, two entries past its end, and no less than the merge needs.
+unsigned list_bytes(int N) { return (unsigned)std::max((N + 2) * (int)sizeof(unsigned short), kMergeFloats * (int)sizeof(float)); }
+
 }  // namespace
 
+#ifdef PISA_ATTN_FOUR
+hipError_t launch_attention_four(const PB& p, int grid, hipStream_t stream) {
+  hipLaunchKernelGGL((attn_bf16_kernel<64, false, 1, 4>), dim3(grid), dim3(256), list_bytes(p.N), stream, p);
+  return hipGetLastError();
+}
+#else
 // The kernels that walk two tiles per block without a trip list: dense_attention and block 128.
 template <int D> static hipError_t launch_attention_two_tiles(const PB& p, bool dense, int grid, hipStream_t stream) {
   if (dense) hipLaunchKernelGGL((attn_bf16_kernel<D, true, 2>), dim3(grid), dim3(256), 0, stream, p);
@@ -1448,6 +1479,18 @@ static int halved_items(const Dims& dm, const AttnArgs& a, int per_xcd) {
   return over <= kCus / 2 ? over : 0;
 }
 
+// Head_dim 64, block 64: four workgroups on a CU (128 per XCD) or three (96).  Four where three would leave some for a second
+// round that four take at once (81 items per XCD, of them 17 in halves, 1.12; 83 1.07, 95 1.09), and from 128 items on (140
+// 1.06, 157 1.01, 180-2 955 1.02-1.05).  Not where three hold the whole call (0.97-1.00: its code has a scheduler and 152
+// registers), nor between (97 items 0.98, 109 0.97, 117 0.99: a second round either way), nor where an item walks one list,
+// as dense (0.95-0.98), nor where the trip list makes it three after all (2 969 blocks 0.98).
+static bool four_on_a_cu(const Dims& dm, const AttnArgs& a, const PB& p) {
+  constexpr int kStaticLds = 35 * 1024, kLds = 160 * 1024;
+  if (a.k_top < 1 || 4 * a.k_top > 3 * dm.N || kStaticLds + list_bytes(dm.N) > kLds / 4) return false;
+  const int groups = 2 * p.per_xcd - p.n_whole;
+  return p.per_xcd >= 128 || (groups > 96 && groups <= 128);
+}
+
 template <int D>
 static hipError_t launch_attention_bf16_d(const Dims& dm, const AttnArgs& a, hipStream_t stream) {
   PB p{};
@@ -1496,7 +1539,8 @@ static hipError_t launch_attention_bf16_d(const Dims& dm, const AttnArgs& a, hip
     if (e != hipSuccess) return e;
   }
   if (dm.B != kTile) return launch_attention_two_tiles<D>(p, false, grid, stream);
-  hipLaunchKernelGGL((attn_bf16_kernel<D, false, 1>), dim3(grid), dim3(256), 0, stream, p);
+  if (D == 64 && four_on_a_cu(dm, a, p)) return launch_attention_four(p, grid, stream);
+  hipLaunchKernelGGL((attn_bf16_kernel<D, false, 1>), dim3(grid), dim3(256), list_bytes(p.N), stream, p);
   return hipGetLastError();
 }
 
@@ -1530,5 +1574,7 @@ hipError_t static_scratch_ptr(void** out) {
 hipError_t launch_attention_bf16(const Dims& dm, const AttnArgs& a, hipStream_t stream) {
   return dm.d == 64 ? launch_attention_bf16_d<64>(dm, a, stream) : launch_attention_bf16_d<128>(dm, a, stream);
 }
+
+#endif  // PISA_ATTN_FOUR
 
 }  // namespace pisa

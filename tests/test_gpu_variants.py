@@ -204,6 +204,28 @@ def test_bf16_halved_items(lib, L, H, B, r, check, d):
     run_full_case(lib, w, blocks_per_head=sorted({0, 1, n // 2, n - 2, n - 1}), heads=check)
 
 
+# bf16 attention at head_dim 64 and block 64: four workgroups on a CU where a call has 97 to 128 of them per XCD (items past the
+# last round in halves: two) or 128 items and more, an item walks two lists and there is a selected block
+@pytest.mark.parametrize("L,H,r,first_order,approximate", [
+    (128 * 16, 40, 0.8, True, True),              # 80 items, 96 workgroups: three
+    (128 * 27 - 9, 24, 0.8, True, True),          # 81, 98: four
+    (128 * 16 - 64, 48, 0.95, True, True),        # 96, 128: four; an odd number of blocks, two selected
+    (128 * 12 + 63, 59, 0.8, True, True),         # 96 (95.9), 128; the last half of 63 rows, no row for the other
+    (128 * 97, 8, 0.9, True, True),               # 97, 130: three
+    (128 * 15 + 1, 64, 0.5, True, True),          # 128; one row in the last item
+    (128 * 15 + 1, 64, 0.25, True, True),         # 128, just over three quarters selected: three
+    (128 * 16, 65, 0.25, True, True),             # 130, three quarters: four
+    (128 * 16, 64, 1.0, True, True),              # 128, none selected: three
+    (1409, 55, 0.7, True, False), (1409, 55, 0.7, False, True),
+])
+def test_bf16_four_workgroups(lib, L, H, r, first_order, approximate):
+    w = WORKLOADS["flux"].with_(name=f"four-{L}-{H}", heads=H, seq_len=L, head_dim=64, block=64, sparsity=r, grid=None,
+                                seed=L + H)
+    n = -(-L // 64)
+    run_full_case(lib, w, blocks_per_head=sorted({0, 1, n // 2, n - 2, n - 1}), heads=[0, H - 1], first_order=first_order,
+                  approximate=approximate)
+
+
 def test_bf16_halved_items_with_all_xcds_on_a_head(lib):
     """A head too long for an XCD of its own: its 547 items are dealt in groups of 8, the last 35 (from row 65 536 on)
     in halves, with paired query blocks."""
@@ -366,10 +388,10 @@ def _check_heads(lib, q, k, v, B, idx, out, heads, blocks, scale, mode="hybrid",
 
 
 @pytest.mark.parametrize("direction", ["rising", "falling", "spike"])
-@pytest.mark.parametrize("d,H", [(64, 18), (128, 18), (64, 22)])
+@pytest.mark.parametrize("d,H", [(64, 18), (128, 18), (64, 22), (64, 37)])
 def test_runaway_maximum_in_long_calls(lib, direction, d, H):
-    """test_runaway_maximum with items taken whole (18 a head; 64 channels, sparse: at 22 heads), where the
-    maximum is refreshed only when a tile sum nears overflow."""
+    """test_runaway_maximum with items taken whole (18 a head; 64 channels, sparse: at 22 heads, four workgroups on a CU
+    at 37), where the maximum is refreshed only when a tile sum nears overflow."""
     L, B = 2304, 64
     w = WORKLOADS["flux"].with_(name=f"runaway-{direction}", heads=H, seq_len=L, head_dim=d, grid=None, sparsity=0.5)
     q, k, v = make_qkv(w, device="cpu")
@@ -390,7 +412,7 @@ def test_runaway_maximum_in_long_calls(lib, direction, d, H):
     _check_heads(lib, q, k, v, B, res["idx"][0].cpu().numpy(), res["out"], [0, H - 1], blocks, scale, "hybrid", direction)
 
 
-@pytest.mark.parametrize("d,H", [(64, 28), (128, 28), (64, 37)])
+@pytest.mark.parametrize("d,H", [(64, 28), (128, 28), (64, 37), (64, 55)])
 def test_out_of_range_index_entries_in_long_calls(lib, d, H):
     """Entries outside [0, N) at different places of the two rows of a 128-row workgroup: their lists differ in length, so
     that some tiles of either are left without a partner."""
@@ -413,7 +435,7 @@ def test_out_of_range_index_entries_in_long_calls(lib, d, H):
     _check_heads(lib, q, k, v, B, kept, out, [0, H - 1], list(range(n)), scale)
 
 
-@pytest.mark.parametrize("d,scale,H", [(128, 0.2, 29), (64, 0.01, 29), (64, 0.01, 37)])
+@pytest.mark.parametrize("d,scale,H", [(128, 0.2, 29), (64, 0.01, 29), (64, 0.01, 37), (64, 0.01, 55)])
 def test_custom_softmax_scale_in_long_calls(lib, d, scale, H):
     L, B = 1409, 64
     w = WORKLOADS["flux"].with_(name=f"scale-{scale}", heads=H, seq_len=L, head_dim=d, grid=None, sparsity=0.75)
