@@ -3,8 +3,8 @@
 //
 // Workgroup = 4 wavefronts = 128 query rows (two adjacent 64-row query blocks, or one
 // 128-row block); wave w owns rows 32w..32w+31 and sees every key of a staged tile.
-// Two workgroups fit a CU (2 x 75 KB LDS at D = 128, <= 256 VGPRs), so barrier stalls of one
-// are covered by the other.
+// Two workgroups fit a CU (67-77 KB LDS each at D = 128, <= 256 VGPRs; three or four at 64), so barrier stalls of one
+// are covered by the others.
 //
 // Everything is computed transposed with v_mfma_f32_32x32x16_bf16:
 //     S^T (keys x queries) = K_tile (keys x d)   *  Q^T (d x queries)
