@@ -337,6 +337,21 @@ __device__ inline void qk_rows(f32x16& s, const bf16x8 (&qreg)[D / 16], const La
   }
 }
 
+// Logits against a maximum that has taken them in.  exp2(fma(s, c, -m)) subtracts a rounded product from unrounded ones:
+// nothing beside a maximum of ordinary size, anything between -inf and inf beside a huge one.  And a step can consist of
+// nothing but huge ones, keys that a channel of their own masks by the lowest value or -inf: what it then sums up to (inf, or
+// NaN at -inf) stays in l and O, because the rescale that a later key brings is by 0.  So where the maximum is far from 0 the
+// logits are made the rounded products that it was taken of (in place; exp_rows with c = 1 from there on), and the
+// largest key has weight 1 whatever its size.
+__device__ inline bool is_far(float m) { return !(fabsf(m) <= 0x1p20f); }
+__device__ inline void round_logits(f32x16& s, float c) {
+#pragma clang fp contract(off)
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s[r] *= c;
+}
+// What is subtracted: the maximum, or 0 where all keys so far are at -inf.
+__device__ inline float minus_max(float m) { return m == -INFINITY ? 0.f : -m; }
+
 // Online softmax in the log2 domain, in two steps so that the only branch (the rescale of O
 // when some row maximum moved) sits in front of the straight-line exponential part.
 // Register r of S^T half kk <-> key 32 kk + (r/4)*8 + 4h + r%4.
@@ -520,6 +535,11 @@ __device__ inline void absorb_tile(State<D>& st, const bf16x8 (&qreg)[D / 16], c
   bf16x8 pb[4];
   qk_tile<D, KOFF>(s0, s1, qreg, lc);
   const float m_safe = softmax_max<D, TAIL>(st, s0, s1, lc, bias, c);
+  if (!TAIL && __any(is_far(m_safe))) {
+    round_logits(s0, c);
+    round_logits(s1, c);
+    c = 1.f;
+  }
   softmax_exp<D, TAIL, RAGGED>(st, s0, s1, m_safe, pb, lc, nvalid, c);
   pv_tile<D, VOFF>(st, pb, lc);
 }
@@ -535,35 +555,10 @@ __device__ inline void absorb_tile(State<D>& st, const bf16x8 (&qreg)[D / 16], c
 // a row (each with a running maximum of its own) meet in LDS once, before Phase 3, and each wave of the
 // pair finishes half of the channels.  The tiles of one index row are walked straight from its bitmask.
 
-// exp_rows against a maximum that has just taken these keys in: the same rounded product is subtracted from it, so
-// that the largest key has weight 1 whatever its size.  (With 32 keys to a wave's step, a step can consist of nothing but
-// keys that a channel of their own masks by the lowest value or -inf; against the unrounded product such a step
-// sums up to anything between 0 and inf.)
-__device__ inline void exp_rows_at_max(const f32x16& s, float c, float m, bf16x8& p0, bf16x8& p1, float& pa, float& pc) {
-#pragma clang fp contract(off)
-  const float m_safe = m == -INFINITY ? 0.f : m;
-#pragma unroll
-  for (int step = 0; step < 2; ++step) {
-    u32x4 pw;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = 8 * step + 2 * i;
-      const float x0 = __builtin_amdgcn_exp2f(s[r] * c - m_safe);
-      const float x1 = __builtin_amdgcn_exp2f(s[r + 1] * c - m_safe);
-      pw[i] = pack_bf16(x0, x1);
-      if (i & 1) pc += x0 + x1;
-      else pa += x0 + x1;
-    }
-    if (step == 0) p0 = __builtin_bit_cast(bf16x8, pw);
-    else p1 = __builtin_bit_cast(bf16x8, pw);
-  }
-}
-
 // 32 staged keys, start to finish, with the exact softmax step (ragged tile, centroid tiles); see absorb_tile.
 template <int D, bool TAIL, bool RAGGED, int KOFF, int VOFF>
 __device__ inline void absorb_rows(State<D>& st, const bf16x8 (&qreg)[D / 16], const LaneCtx& lc,
                                    LDS_PTR(const float) bias, int nvalid, float c) {
-#pragma clang fp contract(off)
   f32x16 s;
   bf16x8 pb[2];
   qk_rows<D, KOFF, 0>(s, qreg, lc);
@@ -576,9 +571,9 @@ __device__ inline void absorb_rows(State<D>& st, const bf16x8 (&qreg)[D / 16], c
       for (int i = 0; i < 4; ++i) s[4 * g + i] = fmaf(s[4 * g + i], c, b[i]);
     }
   }
-  const float tmax = max_rows(s);
-  raise_max<D>(st, TAIL ? tmax : tmax * c);
-  const float nm = st.m == -INFINITY ? 0.f : -st.m;
+  if (!TAIL) round_logits(s, c);
+  raise_max<D>(st, max_rows(s));
+  const float nm = minus_max(st.m);
   float psum = 0.f;
 #pragma unroll
   for (int step = 0; step < 2; ++step) {
@@ -589,7 +584,7 @@ __device__ inline void absorb_rows(State<D>& st, const bf16x8 (&qreg)[D / 16], c
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const int r = 8 * step + 2 * i + u;
-        x[u] = __builtin_amdgcn_exp2f(TAIL ? s[r] + nm : s[r] * c + nm);      // two roundings: see exp_rows_at_max
+        x[u] = __builtin_amdgcn_exp2f(s[r] + nm);
         if (RAGGED && (r / 4) * 8 + 4 * h + (r % 4) >= nvalid) x[u] = 0.f;
         psum += x[u];
       }
@@ -730,9 +725,10 @@ __device__ __forceinline__ void attend_64_rows(const PB& p, const size_t bh, con
       float pa = 0.f, pc = 0.f;
       exp_rows(sc, c, -st.m, p0, p1, pa, pc);
       if (__any(!(pa + pc < kStaleLimit))) {           // first keys of this wave, or a maximum that ran away
-        raise_max<D>(st, max_rows(sc) * c);
+        round_logits(sc, c);
+        raise_max<D>(st, max_rows(sc));
         pa = pc = 0.f;
-        exp_rows_at_max(sc, c, st.m, p0, p1, pa, pc);
+        exp_rows(sc, 1.f, minus_max(st.m), p0, p1, pa, pc);
       }
       st.l += pa + pc;
       pv_rows<D, V_CUR, 0>(st, p0, p1, lc);
@@ -1259,6 +1255,14 @@ __global__ __launch_bounds__(256, WGS) void attn_bf16_kernel(PB p) {
           pa = pc = 0.f;
           if (do_lo) exp_rows(sc0, c, nm, pb[0], pb[1], pa, pc);
           if (do_hi) exp_rows(sc1, c, nm, pb[2], pb[3], pa, pc);
+          if (__any(is_far(st.m))) {                   // see round_logits
+            if (do_lo) round_logits(sc0, c);
+            if (do_hi) round_logits(sc1, c);
+            nm = minus_max(st.m);
+            pa = pc = 0.f;
+            if (do_lo) exp_rows(sc0, 1.f, nm, pb[0], pb[1], pa, pc);
+            if (do_hi) exp_rows(sc1, 1.f, nm, pb[2], pb[3], pa, pc);
+          }
         }
         st.l += pa + pc;
         if (do_lo) pv_rows<D, V_CUR, 0>(st, pb[0], pb[1], lc);

@@ -339,6 +339,67 @@ def test_keys_masked_by_a_channel(lib, dtype, d, scale, masked, low):
             assert float((lse.double().cpu() - z.logsumexp(-1)).abs().max()) <= (1e-4 if dtype == torch.float32 else 2e-2)
 
 
+# the same masks in calls whose items are taken whole (128 rows a workgroup, mostly; the last ones in halves): one list to an
+# item (dense, block 128, nearly every block selected), two lists (tile 0 is in one of them only, so that it is walked in
+# split trips of 32 keys), four workgroups on a CU at head_dim 64; items per XCD in brackets
+@pytest.mark.parametrize("low", [-float("inf"), -3e38, -1e12])
+@pytest.mark.parametrize("masked", [(0, 32), (0, 64), (0, 200)])
+@pytest.mark.parametrize("d,H,L,B,k_top", [
+    (128, 10, 4096, 64, 32),         # 40
+    (128, 10, 4096 - 21, 64, 60),    # 40, just under all blocks
+    (64, 10, 4096, 64, 56),          # 40, more than three quarters of the blocks
+    (64, 25, 2048 - 9, 64, 16),      # 50: three workgroups on a CU
+    (64, 64, 2048, 64, 16),          # 128: four
+    (128, 10, 4096, 128, 8), (64, 10, 4096 - 70, 128, 8),
+])
+def test_keys_masked_by_a_channel_in_long_calls(lib, d, H, L, B, k_top, masked, low):
+    g = torch.Generator(device=DEV).manual_seed(L + H)
+    q, k, v = (torch.randn(1, H, L, d, generator=g, device=DEV).bfloat16() for _ in range(3))
+    q[..., 0] = 1.0
+    k[..., 0] = 0.0
+    k[:, :, masked[0]:masked[1], 0] = low
+    n, s = lib.num_blocks(L, B), lib.resolved_scale(d)
+    dense, dense_lse = lib.dense_attention(q, k, v, B, want_lse=True)
+    rows = torch.arange(1, k_top + 1, dtype=torch.int32).repeat(n, 1)         # blocks 1 .. k_top or 0, 2 .. k_top
+    rows[::2, 0] = 0
+    idx = rows.repeat(1, H, 1, 1).contiguous().to(DEV)
+    part, part_lse = lib.attention(lib.make_shape(q, B), q, k, v, None, None, None, idx, k_top, want_lse=True)
+    token = torch.arange(L, device=DEV)
+    keep = ~((token >= masked[0]) & (token < masked[1]))
+    chosen = torch.zeros(n, n, dtype=torch.bool, device=DEV).scatter_(1, idx[0, 0].long(), True)
+    attends = chosen[token // B][:, token // B]
+    for h in (0, H // 2, H - 1):
+        z = (q[0, h].double() @ k[0, h].double().T.contiguous()) * s
+        for got, lse, on in ((dense, dense_lse, keep[None].expand(L, L)), (part, part_lse, attends & keep)):
+            w = z.masked_fill(~on, -float("inf"))
+            ref = w.softmax(-1) @ v[0, h].double()
+            err = (got[0, h].double() - ref).abs().amax(-1) / ref.abs().amax(-1)
+            assert float(err.max()) <= TOL[torch.bfloat16], h       # (NaN fails)
+            assert float((lse[0, h].double() - w.logsumexp(-1)).abs().max()) <= 2e-2
+    assert bool(dense.isfinite().all()) and bool(part.isfinite().all())
+
+
+@pytest.mark.parametrize("low", [-float("inf"), -3e38, -1e12])
+@pytest.mark.parametrize("d,H,L,B", [(128, 2, 520, 64), (128, 10, 4096 + 30, 64), (64, 64, 2048 + 63, 64), (128, 30, 4096 + 9, 128)])
+def test_masked_ragged_tile_before_the_centroids(lib, d, H, L, B, low):
+    """The last block is the only exact one and masked throughout: what is left are the centroids of the others."""
+    g = torch.Generator(device=DEV).manual_seed(L)
+    q, k, v = (torch.randn(1, H, L, d, generator=g, device=DEV).bfloat16() for _ in range(3))
+    n, s = lib.num_blocks(L, B), lib.resolved_scale(d)
+    q[..., 0] = 1.0
+    k[..., 0] = 0.0
+    k[:, :, (n - 1) * B:, 0] = low
+    st = lib.block_stats(q, k, v, B)
+    idx = torch.full((1, H, n, 1), n - 1, dtype=torch.int32, device=DEV)
+    out, _ = lib.attention(lib.make_shape(q, B), q, k, v, st["kbar"], st["vsum"], None, idx, 1)
+    for h in (0, H // 2, H - 1):
+        z = (q[0, h].double() @ st["kbar"][0, h, :-1].double().T.contiguous()) * s
+        ref = z.softmax(-1) @ (st["vsum"][0, h, :-1].double() / B)
+        err = (out[0, h].double() - ref).abs().amax(-1) / ref.abs().amax(-1)
+        assert float(err.max()) <= TOL[torch.bfloat16], h
+    assert bool(out.isfinite().all())
+
+
 @pytest.mark.parametrize("d,L,H", [(64, 70, 1), (128, 1000, 2), (128, 64 * 22 + 9, 10), (64, 64 * 40 + 17, 20)])
 def test_fp32_infinite_value_in_the_last_row(lib, d, L, H):
     """The rows a ragged tile lacks must add nothing: with an infinite value in the last row that is there, its channel is
