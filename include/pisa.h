@@ -166,13 +166,14 @@ int32_t pisa_select(const pisa_shape* shape, const double* qbar64, const double*
  * k_top == N reproduces dense_attention; k_top == 0 is the pure approximation.
  * N up to 4096 blocks.  `workspace` must hold pisa_workspace_bytes(shape) when k_top < N and
  * kbar is given (it may be NULL otherwise); its contents are overwritten.
- * bf16, block 64, N >= 256, density k_top / N at most 20 %, more than 320 workgroups of 128 rows
+ * bf16: an item is 128 query rows, at block 64 two query blocks; a workgroup takes one item or half
+ * of one (calls of few items, and the items past the last full round of compute units).  Which
+ * depends on the shape and k_top alone and changes the order of the fp32 sums and nothing else.
+ * Block 64, N >= 256, density k_top / N at most 20 %, more than 320 items (head_dim 64: 384)
  * (batch * heads * ceil(seq_len / 128)), workspace given: which two 64-row
- * query blocks travel in one workgroup is decided from idx (blocks whose rows overlap most are
- * paired, three small launches ahead of the attention kernel), which changes the order of the
+ * query blocks make an item is decided from idx (blocks whose rows overlap most are
+ * paired, three small launches ahead of the attention kernel), which again changes the order of the
  * fp32 sums and nothing else; every entry point decides the same way for the same idx.
- * Calls with few workgroups run a kernel of their own (64 rows a workgroup, no pairing); which one
- * runs depends on the shape and k_top alone.
  * (PISA_NO_PAIRING=1 in the environment, read once per process, keeps neighbours together.)
  */
 int32_t pisa_attention(const pisa_shape* shape, const void* q, const void* k, const void* v,

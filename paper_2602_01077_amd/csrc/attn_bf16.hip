@@ -1535,7 +1535,11 @@ static hipError_t launch_attention_bf16_d(const Dims& dm, const AttnArgs& a, hip
     p.vbar = vbar;
     p.hpack = hpack;
   }
-  if (pairing_pays(dm, a.k_top) && a.workspace && p.n_whole > 0) {
+  // Up to 320 items the three launches of the pairing cost 15 to 20 us that no overlap brings back (attention step, us, paired /
+  // neighbours, head_dim 128, r = 0.85 and 0.95: 2 heads of 16 500 tokens 106 / 91 and 65 / 46, 1 of 40 900 212 / 192 and 110 / 90).
+  // Above, the step gets longer and they stay: 17 us more than neighbours at 88 items per XCD (2 of 45 000, 416 / 399), 1.6 % less
+  // at 2 955 (40 of 75 600).  Where between the two they start to pay has not been measured.
+  if (pairing_pays(dm, a.k_top) && a.workspace && p.n_whole > 0 && p.total > 320) {
     // the pairing scratch follows the pre-pass results (whether or not those are in use)
     unsigned char* after = static_cast<unsigned char*>(a.workspace) +
                            (size_t)dm.bh() * (2 * (size_t)p.npad * D * 2 + 2 * D * D * 2);

@@ -810,10 +810,10 @@ def test_forward_rejects_a_small_workspace(lib):
 
 @pytest.mark.parametrize("L,approximate", [(64 * 300 - 21, True), (64 * 257, True), (64 * 300 - 21, False)])
 def test_query_blocks_paired_by_row_similarity(lib, L, approximate):
-    """From 256 blocks on, the block-64 kernel pairs the query blocks of a workgroup by the overlap of
-    their index rows instead of taking neighbours, in calls that have more than 32 such pairs per XCD.  Whatever the pairing, every row must be written (the output is
+    """From 256 blocks on, the block-64 kernel pairs the query blocks of an item by the overlap of their index rows instead
+    of taking neighbours, in calls of more than 320 items.  Whatever the pairing, every row must be written (the output is
     pre-filled with NaN) and agree with the oracle (sampled blocks: the first, the last, ragged one, and 22 random ones).
-    The sizes above have enough blocks but few pairs, and are taken a query block per workgroup; test_gpu_variants.py
+    The sizes above have enough blocks but at most 300 items, most of them whole and unpaired; test_gpu_variants.py
     repeats the test past that line."""
     w = WORKLOADS["wan"].with_(name="pairing", heads=2, seq_len=L, grid=None, block_offset_std=0.5, sparsity=0.85,
                                seed=81)

@@ -94,6 +94,26 @@ def test_spectral_heterogeneity_of_special_blocks(lib, d, dtype, B):
         assert np.abs(np.exp(log_m) - 1e-6 - M).max() <= 1e-9 * M.max(), norm
 
 
+# Up to 320 items of 128 rows nothing is paired: keep-or-drop without a workspace, which has no room for the tables, gives
+# the same bits as with one.  Past the line it does not (which shows that the check can tell).
+@pytest.mark.parametrize("L,H,d,paired", [
+    (128 * 129, 2, 128, False),          # 33 items per XCD: 32 taken whole, one in halves
+    (128 * 160, 2, 128, False),          # 40
+    (128 * 320 - 50, 1, 128, False),
+    (128 * 190, 2, 64, False),           # 48 at head_dim 64: all in halves
+    (128 * 196 - 9, 2, 64, True),        # 49
+    (128 * 161, 2, 128, True),           # 322 in all
+])
+def test_short_calls_pair_nothing(lib, L, H, d, paired):
+    g = torch.Generator(device=DEV).manual_seed(L)
+    q, k, v = (torch.randn(1, H, L, d, generator=g, device=DEV).bfloat16() for _ in range(3))
+    n, k_top, shape = lib.num_blocks(L, 64), 20, lib.make_shape(q, 64)
+    idx = torch.rand(1, H, n, n, generator=g, device=DEV).topk(k_top).indices.sort().values.int().contiguous()
+    tiny = torch.empty(16, dtype=torch.uint8, device=DEV)
+    with_ws, without = (lib.attention(shape, q, k, v, None, None, None, idx, k_top, workspace=w)[0] for w in (None, tiny))
+    assert torch.equal(with_ws, without) == (not paired)
+
+
 # Reduction of the partial H sums, one element a thread (few heads) and four, over chunk counts around the sixteen and the
 # eight loads in flight; one call (reduction inside the selection's launch) and three calls (a launch of its own)
 @pytest.mark.parametrize("d", [128, 64])
