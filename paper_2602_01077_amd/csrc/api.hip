@@ -66,6 +66,12 @@ static StatsPlan plan_of_chunk(const Dims& dm, int chunk_blocks) {
   return p;
 }
 
+// The smallest chunk with which a launch has at most `groups` workgroups (one per head at least).
+static int chunk_for(const Dims& dm, int groups) {
+  const int chunks = std::min(dm.N, std::max(1, groups / dm.bh()));
+  return (dm.N + chunks - 1) / chunks;
+}
+
 StatsPlan matrix_bound_plan(const Dims& dm) {
   // Kernels bound by the matrix instruction (fp32, fp64) gain nothing from a second workgroup on a
   // compute unit: their time is the number of blocks the fullest of the 256 compute units works
@@ -74,7 +80,8 @@ StatsPlan matrix_bound_plan(const Dims& dm) {
   // 33.0 us, 192 of three 25.7 us.  fp64 sums of 24 heads of 4 608: 432 workgroups of four blocks or
   // 216 of eight, eight on the fullest unit either way, took the same (78 us now); half the partial sums
   // take their reduction from 10.0 to 6.3 us.
-  if (!few_blocks(dm)) return stats_plan(dm);
+  // Many blocks are no different (exact Frobenius norm, us, about 512 workgroups / 1 024 / this: 76 heads of 6 656 tokens
+  // 618 / 600 / 602, 24 of 16 384 463 / 493 / 460, 40 of 20 000 at block 128 894 / 920 / 875).
   int best = 1;
   double best_cost = 1e300;
   // every number of chunks there is, with the shortest chunk that gives it (at most 2 sqrt(N) of them)
@@ -90,17 +97,8 @@ StatsPlan matrix_bound_plan(const Dims& dm) {
   return plan_of_chunk(dm, best);
 }
 
-// The smallest chunk with which a launch has at most `groups` workgroups (one per head at least).
-static int chunk_for(const Dims& dm, int groups) {
-  const int chunks = std::min(dm.N, std::max(1, groups / dm.bh()));
-  return (dm.N + chunks - 1) / chunks;
-}
-
 StatsPlan stats_plan(const Dims& dm) {
-  if (dm.dtype == PISA_FP32) {
-    if (few_blocks(dm)) return matrix_bound_plan(dm);
-    return plan_of_chunk(dm, chunk_for(dm, 1024));
-  }
+  if (dm.dtype == PISA_FP32) return few_blocks(dm) ? matrix_bound_plan(dm) : plan_of_chunk(dm, chunk_for(dm, 1024));
   // bf16: all workgroups of a launch take about as long, so it is one round of them, never a few more (head_dim 128: two on
   // each of the 256 compute units, 64: three).  Two rounds balance no better and write twice the partial sums, which are read
   // again: statistics with their reduction, us, two rounds / one: 24 heads of 16 384 97.1 / 84.1, 13 of 30 000 97.3 / 83.2,

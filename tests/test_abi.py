@@ -199,3 +199,14 @@ def test_chunk_plan_of_the_matrix_bound_sums(lib):
             logits = 8 * bh * n * n                                   # what pisa_select needs
             got = lib.workspace_bytes(lib.PisaShape(1, bh, n * 64, d, 64, lib.PISA_FP32, 0.0))
             assert got == max(need, logits), (n, bh)
+
+
+@pytest.mark.parametrize("dtype", ["PISA_FP32", "PISA_BF16"])
+@pytest.mark.parametrize("heads,n", [(76, 104), (78, 104), (24, 256), (40, 313), (13, 469), (1500, 4), (1, 4097), (2, 3000)])
+def test_chunk_plan_of_the_fp64_sums_past_4096_blocks(lib, heads, n, dtype):
+    """The same rule past 4 096 blocks, whatever the input type."""
+    d = 128
+    cost = lambda c: (-(-heads * -(-n // c) // 256) * c + 0.25 * (heads * -(-n // c)) / 256.0, -c)
+    chunks = -(-n // min(range(1, n + 1), key=cost))
+    got = lib.workspace_bytes(lib.PisaShape(1, heads, n * 64 - 5, d, 64, getattr(lib, dtype), 0.0))
+    assert got == max(heads * (chunks + 1) * d * d * 8, 8 * heads * n * n)
