@@ -114,8 +114,13 @@ StatsPlan stats_plan(const Dims& dm) {
   // against four, 111.1 / 109.0).
   const int beside = chunk_for(dm, 512);
   if (dm.d == 64) return plan_of_chunk(dm, beside);
+  // At block 128 a workgroup alone is 1.6 times as fast (24 heads of 16 384 tokens, 13 blocks to a workgroup alone, seven to each
+  // of two, 104 / 91 us; 40 of 6 500 70 / 62), and one of two blocks is worth it where one block each fills the second
+  // place on half of the units (24 of 2 000, two / one, 22.3 / 23.3; 12 of 3 000, on an eighth of them, 21.4 / 21.1).
   const int alone = chunk_for(dm, 256);
-  return plan_of_chunk(dm, alone < 2 * beside || beside == 1 ? alone : beside);
+  if (dm.B == kTile) return plan_of_chunk(dm, alone < 2 * beside || beside == 1 ? alone : beside);
+  const bool pays = beside == 1 ? dm.N * dm.bh() >= 320 : 5 * alone < 8 * beside;
+  return plan_of_chunk(dm, pays ? alone : beside);
 }
 
 static size_t stats_workspace_bytes(const Dims& dm) {
