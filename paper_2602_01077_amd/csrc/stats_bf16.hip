@@ -373,16 +373,19 @@ __global__ __launch_bounds__(64 * stats_waves(D), D == 128 ? 4 : 2) void stats_b
         }
       }
       ss = wave_sum(ss);
-      // The norms are finished kNormBlocks at a time, a thread per block.
-      const int at = (j - j_begin) % kNormBlocks;
-      if (lane == 0) hnorm_s[at][wave] = ss;
+      // The norms are finished kNormBlocks at a time, a thread per block.  (What goes by the thread is made here: kept over the
+      // block, it spills.)
+      int t = tid;
+      asm volatile("" : "+v"(t));
+      const int at = __builtin_amdgcn_readfirstlane((j - j_begin) % kNormBlocks);
+      if (t % 64 == 0) hnorm_s[at][wave] = ss;
       if (at == kNormBlocks - 1 || j == j_end - 1) {
         __syncthreads();
-        if (tid <= at) {
-          double sum = hnorm_s[tid][0];
+        if (t <= at) {
+          double sum = hnorm_s[t][0];
 #pragma unroll
-          for (int w = 1; w < NW; ++w) sum += hnorm_s[tid][w];
-          log_m[bh * N + j - at + tid] = log(sqrt(sum) + eps);
+          for (int w = 1; w < NW; ++w) sum += hnorm_s[t][w];
+          log_m[bh * N + j - at + t] = log(sqrt(sum) + eps);
         }
         // hnorm_s is written again only after the next block's barriers
       }
