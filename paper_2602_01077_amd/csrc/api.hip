@@ -57,7 +57,7 @@ static int32_t resolve(const pisa_shape* s, Dims* dm) {
 }
 
 // Up to this many blocks in all, the number of blocks the fullest compute unit gets decides.
-static bool few_blocks(const Dims& dm) { return (long long)dm.N * dm.bh() <= 4096; }
+bool few_blocks(const Dims& dm) { return (long long)dm.N * dm.bh() <= 4096; }
 
 static StatsPlan plan_of_chunk(const Dims& dm, int chunk_blocks) {
   StatsPlan p;
@@ -67,7 +67,7 @@ static StatsPlan plan_of_chunk(const Dims& dm, int chunk_blocks) {
 }
 
 // The smallest chunk with which a launch has at most `groups` workgroups (one per head at least).
-static int chunk_for(const Dims& dm, int groups) {
+int chunk_for(const Dims& dm, int groups) {
   const int chunks = std::min(dm.N, std::max(1, groups / dm.bh()));
   return (dm.N + chunks - 1) / chunks;
 }

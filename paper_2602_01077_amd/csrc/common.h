@@ -37,6 +37,8 @@ struct StatsPlan {
   int chunk_blocks;
   int n_chunks;
 };
+bool few_blocks(const Dims& dm);                  // 4 096 in all, or fewer
+int chunk_for(const Dims& dm, int groups);        // the shortest with which a launch has at most `groups` workgroups
 StatsPlan stats_plan(const Dims& dm);
 StatsPlan matrix_bound_plan(const Dims& dm);
 

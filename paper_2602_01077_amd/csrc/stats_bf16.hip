@@ -14,8 +14,6 @@
 //     tokens, so both come from ds_read_b64_tr_b16.
 // The partial H of the chunk goes to scratch; partials are added in chunk order by the
 // caller's reduction kernel, so hsum is run-to-run identical.
-#include <algorithm>
-
 #include "common.h"
 
 namespace pisa {
@@ -427,12 +425,12 @@ hipError_t launch_block_stats_bf16(const Dims& dm, const void* q, const void* k,
 hipError_t launch_block_heterogeneity_fast(const Dims& dm, const void* k, const void* v, const float* hsum,
                                            double eps, double* log_m, hipStream_t stream) {
   StatsPlan plan = stats_plan(dm);
-  // No partial sums are written here: where a workgroup would have few blocks they go in twos (24 heads of 72 blocks
-  // 25.9 -> 24.6 us, 40 of 47 27.3 -> 25.5); blocks of 128, each with its own read of hsum, go as 512 workgroups.
-  if ((long long)dm.N * dm.bh() <= 4096) {
-    const int chunks = std::min(dm.N, std::max(1, 512 / dm.bh()));
-    const int c = dm.B == kTile ? 2 : (dm.N + chunks - 1) / chunks;
-    plan = {c, (dm.N + c - 1) / c};
+  // No partial sums are written here, so up to few_blocks a block of 64 has a workgroup to itself.  In twos, which save every other
+  // read of hsum, / one by one, us: 4 heads of 1 000 tokens 8.7 / 6.1, 48 of 1 000 16.8 / 13.8, 24 of 4 608 24.1 / 22.4, head_dim
+  // 64 6.1 / 4.5, 7.5 / 6.3, 10.4 / 11.0.  Blocks of 128 go as 512 workgroups (24 of 4 608 24.3, one by one 26.4).
+  if (few_blocks(dm)) {
+    const int chunk = dm.B == kTile ? 1 : chunk_for(dm, 512);
+    plan = {chunk, (dm.N + chunk - 1) / chunk};
   }
   const dim3 grid(plan.n_chunks, dm.bh());
 #define PISA_HET_FAST(DD, TPB)                                                                              \

@@ -134,7 +134,7 @@ def test_reduction_of_partial_sums(lib, H, n, d):
 @pytest.mark.parametrize("d,B", [(128, 64), (128, 128), (64, 64), (64, 128)])
 @pytest.mark.parametrize("H,L", [(2, 64 * 9 + 5), (40, 64 * 76 + 13), (40, 64 * 520 + 64)])
 def test_fast_heterogeneity_over_many_blocks(lib, H, L, d, B):
-    """Workgroups of the fast Frobenius kind with 1 to 21 blocks (the norms are finished eight at a time), against the exact
+    """Workgroups of the fast Frobenius kind with 1 to 44 blocks (the norms are finished eight at a time), against the exact
     kind: both take H_bar from the same fp32 hsum, and the fast one carries fp32 rounding (1e-7 measured)."""
     g = torch.Generator(device=DEV).manual_seed(L + d)
     k, v = (torch.randn(1, H, L, d, generator=g, device=DEV).bfloat16() for _ in range(2))
