@@ -485,9 +485,16 @@ template <int D> void launch_d(P32& p, const Dims& dm, hipStream_t stream) {
   // heads of 700 to 4 000 rows: with halves 9-13 % faster (r = 0.85) and 11-16 % (dense) where up to 16 groups are left over,
   // slower from there on.  At head_dim 128 all of up to 32 groups past a round of 64 workgroups are halved: 17 .. 32 groups
   // 5 % faster (at head_dim 64, where a CU holds three workgroups, 13 % slower).
-  // Eight waves against four, us for the attention step: 2 heads of 2 200 rows 28.6 / 30.4 (dense 88 / 103), 8 of 1 000
-  // 22.0 / 21.1 (47.5 / 52.2); past one group a CU 8 of 1 500 38.7 / 31.6 (102 / 94).
-  if (p.per_xcd <= kCusPerXcd) {
+  // Eight waves against four, us for the attention step: 2 heads of 2 200 rows 28.6 / 30.4 (dense 88 / 103); past one group a
+  // CU 8 of 1 500 38.7 / 31.6 (102 / 94).  Where up to one group a CU walks few pieces, what a workgroup does once is most of its
+  // time, and two workgroups of four waves on a CU, half a group each, hide each other's (8 of 700, r = 0.85, nine pieces, eight
+  // waves 20.3, four 18.9, four on halves 17.1; 25 pieces 28.8, 30.7, 27.7; 32 28.6 / 28.4; 36 34.8 / 35.9).
+  const bool approx = !p.dense && p.k_top < dm.N && p.kbar != nullptr;
+  const int pieces = (p.dense ? dm.N : p.k_top) * (dm.B / kPiece) + (approx ? (dm.N + kPiece - 1) / kPiece : 0);
+  if (2 * p.per_xcd > kCusPerXcd && p.per_xcd <= kCusPerXcd && pieces <= 32) {
+    p.n_whole = 0;
+    hipLaunchKernelGGL((attn_fp32_kernel<D, 4>), dim3(8 * 2 * p.per_xcd), dim3(256), 0, stream, p);
+  } else if (p.per_xcd <= kCusPerXcd) {
     p.n_whole = 2 * p.per_xcd <= kCusPerXcd ? 0 : p.per_xcd;
     hipLaunchKernelGGL((attn_fp32_kernel<D, 8>), dim3(8 * (2 * p.per_xcd - p.n_whole)), dim3(512), 0, stream, p);
   } else {

@@ -31,10 +31,16 @@ def test_fp32_rows_per_workgroup(lib, L, H, d, B, r, check):
 
 
 # fp32 attention: the lines of the split, in groups of 32 rows per XCD (an eighth of all): eight waves up to 32, 16 rows
-# to a workgroup up to 16; above, the groups past a round of 32 CUs (at head_dim 128 also up to half a round of 64
-# workgroups) are halved
+# to a workgroup up to 16, and to a workgroup of four waves where a row walks up to 32 pieces of 16 keys; above, the groups past
+# a round of 32 CUs (at head_dim 128 also up to half a round of 64 workgroups) are halved
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("L,H,B,check", [
+    (32 * 15 - 20, 9, 64, [0, 8]),      # 17: eight blocks, two of them exact: 9 pieces
+    (32 * 51 - 7, 4, 64, [0, 3]),       # 26: 26 blocks, six exact: 26
+    (32 * 63, 4, 64, [0, 3]),           # 32: 32 blocks, seven exact: 30
+    (32 * 60, 4, 128, [0, 3]),          # 30: 15 blocks, three exact: 25
+    (32 * 32, 6, 128, [0, 5]),          # 24: 8 blocks, two exact: 17
+    (32 * 80, 3, 64, [0, 2]),           # 30: 40 blocks, eight exact: 35, eight waves
     (1024, 4, 64, [0, 3]),              # 16: all in halves
     (32 * 33 - 20, 4, 128, [0, 3]),     # 17: none, the last half of 12 rows
     (1024, 8, 64, [0, 7]),              # 32
@@ -50,7 +56,7 @@ def test_fp32_split(lib, L, H, B, check, d):
     run_full_case(lib, w, blocks_per_head=sorted({0, 1, n // 2, n - 2, n - 1}), heads=check)
 
 
-@pytest.mark.parametrize("L,H", [(64 * 21 + 1, 3), (64 * 32 + 17, 24)])
+@pytest.mark.parametrize("L,H", [(64 * 21 + 1, 3), (64 * 32 + 17, 24), (450, 10), (512, 14), (513, 14)])
 def test_fp32_all_blocks_selected_is_bitwise_dense(lib, L, H):
     w = WORKLOADS["tiny"].with_(heads=H, seq_len=L, head_dim=128, sparsity=0.0)
     q, k, v = (x.to(DEV) for x in make_qkv(w))
