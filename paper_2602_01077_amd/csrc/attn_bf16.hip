@@ -1246,16 +1246,27 @@ __global__ __launch_bounds__(256, WGS) void attn_bf16_kernel(PB p) {
         float nm = -st.m, pa = 0.f, pc = 0.f;
         if (do_lo) exp_rows(sc0, c, nm, pb[0], pb[1], pa, pc);
         if (do_hi) exp_rows(sc1, c, nm, pb[2], pb[3], pa, pc);
-        if (__any(!(pa + pc < kStaleLimit))) {         // first keys of this wave, or a maximum that ran away
+        // First keys of this wave, or a maximum that ran away: out of the loop's way (in line, dense calls of few items are up to
+        // 1 % slower).
+        if (__builtin_expect(__any(!(pa + pc < kStaleLimit)), 0)) {
           float t = -INFINITY;
           if (do_lo) t = max_rows(sc0);
           if (do_hi) t = fmaxf(t, max_rows(sc1));
           raise_max<D>(st, t * c);
           nm = -st.m;
+          float cc = c;
+          const bool far = __any(is_far(st.m));        // see round_logits
+          if (D == 128 && __builtin_expect(far, 0)) {
+            if (do_lo) round_logits(sc0, c);
+            if (do_hi) round_logits(sc1, c);
+            nm = minus_max(st.m);
+            cc = 1.f;
+          }
           pa = pc = 0.f;
-          if (do_lo) exp_rows(sc0, c, nm, pb[0], pb[1], pa, pc);
-          if (do_hi) exp_rows(sc1, c, nm, pb[2], pb[3], pa, pc);
-          if (__any(is_far(st.m))) {                   // see round_logits
+          if (do_lo) exp_rows(sc0, cc, nm, pb[0], pb[1], pa, pc);
+          if (do_hi) exp_rows(sc1, cc, nm, pb[2], pb[3], pa, pc);
+          // At head_dim 64 the same ahead of these costs registers (dense 120 -> 137, four workgroups on a CU three spills).
+          if (D == 64 && __builtin_expect(far, 0)) {
             if (do_lo) round_logits(sc0, c);
             if (do_hi) round_logits(sc1, c);
             nm = minus_max(st.m);
