@@ -39,8 +39,8 @@
 // point, by the statistics kernels; Phase 3 multiplies by the pre-packed hi/lo split of hsum,
 // staged through LDS once per workgroup.
 //
-// Calls of few items, and the items past the last full round of CUs, are taken by workgroups of 64 rows with the keys split
-// over wave pairs (attend_64_rows); the rule stands at the launch.
+// Calls of few items (in a kernel of their own), and the items past the last full round of CUs, are taken by workgroups of 64
+// rows with the keys split over wave pairs (attend_64_rows); the rule stands at the launch.
 #include <mutex>
 #include <type_traits>
 
@@ -597,6 +597,13 @@ __device__ inline void absorb_rows(State<D>& st, const bf16x8 (&qreg)[D / 16], c
   pv_rows<D, VOFF, 0>(st, pb[0], pb[1], lc);
 }
 
+// The nth item of an XCD.  Workgroup ids are dealt round-robin to the 8 XCDs.  With p.by_xcd each XCD gets a contiguous range of
+// (head, query tile) items, so that one XCD's L2 serves one head; otherwise all XCDs work on the same head, 8 neighbouring items
+// each (the rule stands at the launch).  The grid is rounded up: numbers past an XCD's range leave.
+__device__ inline int item_of(const PB& p, int xcd, int nth) {
+  return p.by_xcd ? xcd * p.per_xcd + nth : (nth >> 3) * 64 + xcd * 8 + (nth & 7);
+}
+
 // LDS of a 64-row workgroup, inside that of the kernel it runs in.
 struct ShortLds {
   LDS_PTR(unsigned char) stage;      // K0 | K1 | V0 | V1
@@ -879,6 +886,24 @@ __device__ __forceinline__ void attend_64_rows(const PB& p, const size_t bh, con
   }
 }
 
+// Calls that are taken in halves altogether: none of the registers and LDS of 128-row items (attention step, us, in the kernel
+// for both / in this one: 2 heads of 1 000 tokens 13.1 / 13.0, dense 24 of 700 17.5 / 17.3, 10 of 2 048 35.0 / 34.8, head_dim 64
+// 11.7 / 11.5 and 24.5 / 24.2).
+template <int D, bool DENSE, int TPB>
+__global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bf16_halves_kernel(PB p) {
+  __shared__ __attribute__((aligned(1024))) unsigned char stage[4 * Geo<D>::TILEB];
+  __shared__ unsigned int chosen[MASK_WORDS];
+  __shared__ __attribute__((aligned(16))) float bias_s[2 * kTile];
+  __shared__ float merge_s[kMergeFloats];
+  const int xcd = blockIdx.x % 8, nth = blockIdx.x / 16, half = blockIdx.x / 8 & 1;
+  const int item = item_of(p, xcd, nth);
+  if (item >= p.total) return;
+  const int qt = 2 * (item % p.n_super) + half;
+  if (qt * kTile < p.L)
+    attend_64_rows<D, DENSE, TPB>(p, item / p.n_super, qt, ShortLds{(LDS_PTR(unsigned char)) & stage[0], (LDS_PTR(unsigned int)) & chosen[0],
+                                                                    (LDS_PTR(float)) & bias_s[0], (LDS_PTR(float)) & merge_s[0]});
+}
+
 // LDS map of the staging area (byte offsets): K stages | V stages; Phase 2 reuses it as
 // centroid keys (K stage 0) and centroid values (V stage 0).
 // WGS: workgroups on a CU, which the registers of a lane go by.  Two at head_dim 128 (226 VGPRs, 67-77 KB LDS), three at 64
@@ -904,12 +929,9 @@ __global__ __launch_bounds__(256, WGS) void attn_bf16_kernel(PB p) {
   __shared__ unsigned short pre_s[DENSE || TPB == 2 ? 1 : MASK_WORDS + 1], pre_a[DENSE || TPB == 2 ? 1 : MASK_WORDS + 1],
       pre_b[DENSE || TPB == 2 ? 1 : MASK_WORDS + 1];                                   // tiles below each mask word, by class
 
-  // Workgroup ids are dealt round-robin to the 8 XCDs.  With p.by_xcd each XCD gets a contiguous range of (head, query
-  // tile) items, so that one XCD's L2 serves one head; otherwise all XCDs work on the same head, 8 neighbouring items each
-  // (the rule stands at the launch).  The grid is rounded up: ids past an XCD's range leave.
   const int xcd = blockIdx.x % 8, j = blockIdx.x / 8;
   const int nth = j < p.n_whole ? j : p.n_whole + (j - p.n_whole) / 2;
-  const int item = p.by_xcd ? xcd * p.per_xcd + nth : (nth >> 3) * 64 + xcd * 8 + (nth & 7);
+  const int item = item_of(p, xcd, nth);
   if (nth >= p.per_xcd || item >= p.total) return;
   const size_t bh = item / p.n_super;
   const int sg = item % p.n_super;
@@ -1434,6 +1456,12 @@ template <int D> static hipError_t launch_attention_two_tiles(const PB& p, bool 
   else hipLaunchKernelGGL((attn_bf16_kernel<D, false, 2>), dim3(grid), dim3(256), 0, stream, p);
   return hipGetLastError();
 }
+template <int D> static hipError_t launch_attention_halves(const PB& p, bool dense, int grid, hipStream_t stream) {
+  if (dense) hipLaunchKernelGGL((attn_bf16_halves_kernel<D, true, 2>), dim3(grid), dim3(256), 0, stream, p);
+  else if (p.B == kTile) hipLaunchKernelGGL((attn_bf16_halves_kernel<D, false, 1>), dim3(grid), dim3(256), 0, stream, p);
+  else hipLaunchKernelGGL((attn_bf16_halves_kernel<D, false, 2>), dim3(grid), dim3(256), 0, stream, p);
+  return hipGetLastError();
+}
 
 size_t attention_workspace_bytes(const Dims& dm) {
   if (dm.dtype != PISA_BF16) return 0;
@@ -1529,7 +1557,7 @@ static hipError_t launch_attention_bf16_d(const Dims& dm, const AttnArgs& a, hip
   p.per_xcd = p.by_xcd ? (p.total + 7) / 8 : (p.total + 63) / 64 * 8;
   p.n_whole = p.per_xcd - halved_items(dm, a, p.per_xcd);
   const int grid = 8 * (2 * p.per_xcd - p.n_whole);
-  if (a.dense) return launch_attention_two_tiles<D>(p, true, grid, stream);
+  if (a.dense) return p.n_whole > 0 ? launch_attention_two_tiles<D>(p, true, grid, stream) : launch_attention_halves<D>(p, true, grid, stream);
   if (a.k_top < dm.N && a.kbar) {
     void *kcen_v, *vbar_v, *hpack_v;                      // kcen | vbar | hpack
     attention_workspace_carve(dm, a.workspace, &kcen_v, &vbar_v, &hpack_v);
@@ -1557,6 +1585,7 @@ static hipError_t launch_attention_bf16_d(const Dims& dm, const AttnArgs& a, hip
     hipError_t e = launch_pair_blocks(dm, a.idx, a.k_top, after, &p.pair, stream);
     if (e != hipSuccess) return e;
   }
+  if (p.n_whole == 0) return launch_attention_halves<D>(p, false, grid, stream);
   if (dm.B != kTile) return launch_attention_two_tiles<D>(p, false, grid, stream);
   if (D == 64 && four_on_a_cu(dm, a, p)) return launch_attention_four(p, grid, stream);
   hipLaunchKernelGGL((attn_bf16_kernel<D, false, 1>), dim3(grid), dim3(256), list_bytes(p.N), stream, p);
