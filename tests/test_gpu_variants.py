@@ -279,6 +279,43 @@ def test_query_blocks_paired_in_long_calls(lib, L, approximate):
     test_gpu_parity.test_query_blocks_paired_by_row_similarity(lib, L, approximate)
 
 
+# the same at head_dim 64, where the build with four workgroups on a CU makes its rows again from the pairs after the walk; items
+# per XCD in brackets
+@pytest.mark.parametrize("L,H,sparsity", [
+    (64 * 256 + 33, 8, 0.85),        # 129: four; an odd number of blocks, the last of 33 rows
+    (64 * 264 - 20, 5, 0.85),        # 83, the last 19 in halves, 102 workgroups: four
+    (64 * 260 - 40, 6, 0.85),        # 98, the last 34 in halves, 132 workgroups: three
+    (64 * 257 + 5, 4, 0.81),         # 65, one in halves: three
+    (64 * 2558, 1, 0.98),            # 160, all XCDs on the head: the longest trip list that leaves room for four
+    (64 * 2558 + 1, 1, 0.98),        # one block more: three; its last has one row
+])
+def test_query_blocks_paired_at_64_channels(lib, L, H, sparsity):
+    w = WORKLOADS["wan"].with_(name=f"pairing64-{L}", heads=H, seq_len=L, head_dim=64, grid=None, block_offset_std=0.5,
+                               sparsity=sparsity, seed=L)
+    scale, n = lib.resolved_scale(64), -(-L // 64)
+    q, k, v = make_qkv(w, device="cpu")
+    qd, kd, vd = (x.to(DEV) for x in (q, k, v))
+    k_top = lib.topk_count(n, sparsity)
+    assert 5 * k_top <= n and H * -(-L // 128) > 384
+    st = lib.block_stats(qd, kd, vd, 64)
+    shape = lib.make_shape(qd, 64)
+    idx, _ = lib.select(shape, st["qbar64"], st["kbar64"], k_top, want_gap=False)
+    out = torch.full_like(qd, float("nan"))
+    lse = torch.full(qd.shape[:3], float("nan"), dtype=torch.float32, device=DEV)
+    lib.attention(shape, qd, kd, vd, st["kbar"], st["vsum"], st["hsum"], idx, k_top, out=out, lse=lse)
+    assert not out.isnan().any() and not lse.isnan().any(), "a query block was left out of the pairing"
+    rng = np.random.default_rng(L)
+    blocks = sorted({0, 1, n - 2, n - 1} | set(rng.choice(n, 12, replace=False).tolist()))
+    rows = rows_of_blocks(blocks, 64, L)
+    for h in {0, H - 1}:
+        Q, K, V = (head_np(x, 0, h) for x in (q, k, v))
+        ref, ref_lse = po.attention_head(Q, K, V, 64, idx[0, h].cpu().numpy(), scale, "hybrid", blocks=blocks,
+                                         stats=po.block_stats(Q, K, V, 64))
+        rel, cos = row_errors(out[0, h].float().cpu().numpy()[rows], ref)
+        assert rel <= TOL[torch.bfloat16] and cos >= COS_MIN, (h, rel, cos)
+        assert np.abs(lse[0, h].cpu().numpy()[rows] - ref_lse).max() <= 2e-2
+
+
 def _heterogeneity_against_svd(lib, k, v, B):
     """Spectral M_j of one head, each within 1e-9 of its own value (numpy SVD in fp64): the fp64 products and a Ritz value
     with a 1e-7 residual (its error is quadratic in the residual) leave room for that."""
