@@ -41,6 +41,7 @@
 //
 // Calls of few items (in a kernel of their own), and the items past the last full round of CUs, are taken by workgroups of 64
 // rows with the keys split over wave pairs (attend_64_rows); the rule stands at the launch.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 

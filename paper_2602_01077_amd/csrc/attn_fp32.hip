@@ -144,8 +144,9 @@ __device__ __forceinline__ void attend_rows(const P32& p, const size_t bh, const
     if (pc >= n_exact) return (pc - n_exact) * kPiece;
     if (p.dense) return pc * kPiece;
     const int j = idx_row[pc >> shift];
+    if ((unsigned)j >= (unsigned)N) return -1;
     const int r = j * p.B + (pc & ((1 << shift) - 1)) * kPiece;
-    return (unsigned)j < (unsigned)N && r < L ? r : -1;
+    return r < L ? r : -1;
   };
   // Loads of one piece (16 rows from `row` of a matrix of n_rows) to `dst` in LDS: K format if KF.  Rows past the
   // end repeat the last one (the reader masks them).

@@ -358,6 +358,21 @@ def test_spectral_heterogeneity_of_multiples_of_the_identity(lib, B, d, dtype, c
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("entry", [2 ** 30, 2 ** 31 - 1, -2 ** 31, -1, 5])
+def test_index_entries_far_out_of_range(lib, dtype, entry):
+    """Ignored whatever their size (64 times 2^30 does not fit an int)."""
+    g = torch.Generator(device=DEV).manual_seed(3)
+    q, k, v = (torch.randn(1, 2, 300, 64, generator=g, device=DEV).to(dtype) for _ in range(3))
+    shape = lib.make_shape(q, 64)
+    idx = torch.tensor([0, 2, 3], dtype=torch.int32, device=DEV).repeat(1, 2, 5, 1).contiguous()
+    want = lib.attention(shape, q, k, v, None, None, None, idx, 3, want_lse=True)
+    got = lib.attention(shape, q, k, v, None, None, None, torch.cat([idx, torch.full_like(idx[..., :1], entry)], -1).contiguous(), 4,
+                        want_lse=True)
+    for a, b in zip(got, want):
+        assert float((a.float() - b.float()).abs().max()) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("d", [64, 128])
 def test_rows_that_attend_nothing(lib, dtype, d):
     """Keep-or-drop with every index entry out of range: log of an empty sum, and 0 / 0."""
