@@ -1486,7 +1486,7 @@ void attention_workspace_carve(const Dims& dm, void* workspace, void** kcen, voi
 // tiles are found there if one XCD has the head to itself (us for the attention step, all XCDs on one head / one head
 // each, r = 0.85: 12 heads of 8 192 125 / 107, 24 of 8 192 212 / 187, 24 of 4 608 85 / 82, 24 of 16 384 713 / 688, at block 128
 // 580 / 549, head_dim 64, 40 of 8 192 184 / 171).  Longer heads mostly miss L2 either way (24 of 32 768 2 599 / 2 592,
-// 40 000 3 803 / 3 818, 48 000 5 497 / 5 512), and from where the K and V of eight heads at once outgrow the 256 MB Infinity
+// 40 000 3 803 / 3 818, 48 000 5 497 / 5 512, head_dim 64, block 128, 24 of 65 536 4 153 / 4 163, 98 000 9 275 / 9 260), and from where the K and V of eight heads at once outgrow the 256 MB Infinity
 // Cache they are better taken one at a time (12 of 65 536 3 591 / 3 625, 40 of 75 600 23.1 / 24.7 ms).  The line: 12 MiB
 // each for K and V of a head, 192 MiB for eight.
 static bool heads_by_xcd(const Dims& dm, const AttnArgs& a) {

@@ -6,7 +6,7 @@ import torch
 
 from oracle import pisa_oracle as po
 
-# Tolerances of the benchmark spec: fp32 build 1e-4, bf16 build 2e-2 with
+# Tolerances: fp32 build 1e-4, bf16 build 2e-2 with
 # per-row cosine >= 0.999.  "Relative" is taken per output row, normalised by the
 # row's largest reference magnitude (an elementwise ratio is unbounded near zeros).
 TOL = {torch.float32: 1e-4, torch.bfloat16: 2e-2}
