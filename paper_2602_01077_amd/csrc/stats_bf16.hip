@@ -372,9 +372,9 @@ __global__ __launch_bounds__(64 * stats_waves(D), D == 128 ? 4 : 2) void stats_b
       }
       ss = wave_sum(ss);
       // The norms are finished kNormBlocks at a time, a thread per block.  (What goes by the thread is made here: kept over the
-      // block, it spills.)
+      // block, it spills, but for the one kernel that has registers to spare.)
       int t = tid;
-      asm volatile("" : "+v"(t));
+      if (!(D == 64 && TPB == 2)) asm volatile("" : "+v"(t));
       const int at = __builtin_amdgcn_readfirstlane((j - j_begin) % kNormBlocks);
       if (t % 64 == 0) hnorm_s[at][wave] = ss;
       if (at == kNormBlocks - 1 || j == j_end - 1) {
