@@ -39,7 +39,7 @@
 // point, by the statistics kernels; Phase 3 multiplies by the pre-packed hi/lo split of hsum,
 // staged through LDS once per workgroup.
 //
-// Calls of few items (in a kernel of their own), and the items past the last full round of CUs, are taken by workgroups of 64
+// Calls of few items (dense and block 64 in a kernel of their own), and the items past the last full round of CUs, are taken by workgroups of 64
 // rows with the keys split over wave pairs (attend_64_rows); the rule stands at the launch.
 #include <algorithm>
 #include <mutex>
@@ -887,9 +887,10 @@ __device__ __forceinline__ void attend_64_rows(const PB& p, const size_t bh, con
   }
 }
 
-// Calls that are taken in halves altogether: none of the registers and LDS of 128-row items (attention step, us, in the kernel
-// for both / in this one: 2 heads of 1 000 tokens 13.1 / 13.0, dense 24 of 700 17.5 / 17.3, 10 of 2 048 35.0 / 34.8, head_dim 64
-// 11.7 / 11.5 and 24.5 / 24.2).
+// Calls that are taken in halves altogether, dense and block 64: none of the registers and LDS of 128-row items (attention step,
+// us, in the kernel for both / in this one: 2 heads of 1 000 tokens 13.1 / 13.0, dense 24 of 700 17.5 / 17.3, 10 of 2 048 35.0 /
+// 34.8, head_dim 64 11.7 / 11.5 and 24.5 / 24.2).  At block 128 the kernel for both is as fast or faster (12 of 1 800 19.0 / 19.3,
+// head_dim 64 12.6 / 12.8), and takes them.
 template <int D, bool DENSE, int TPB>
 __global__ __launch_bounds__(256, D == 128 ? 2 : 3) void attn_bf16_halves_kernel(PB p) {
   __shared__ __attribute__((aligned(1024))) unsigned char stage[4 * Geo<D>::TILEB];
@@ -1459,8 +1460,7 @@ template <int D> static hipError_t launch_attention_two_tiles(const PB& p, bool 
 }
 template <int D> static hipError_t launch_attention_halves(const PB& p, bool dense, int grid, hipStream_t stream) {
   if (dense) hipLaunchKernelGGL((attn_bf16_halves_kernel<D, true, 2>), dim3(grid), dim3(256), 0, stream, p);
-  else if (p.B == kTile) hipLaunchKernelGGL((attn_bf16_halves_kernel<D, false, 1>), dim3(grid), dim3(256), 0, stream, p);
-  else hipLaunchKernelGGL((attn_bf16_halves_kernel<D, false, 2>), dim3(grid), dim3(256), 0, stream, p);
+  else hipLaunchKernelGGL((attn_bf16_halves_kernel<D, false, 1>), dim3(grid), dim3(256), 0, stream, p);
   return hipGetLastError();
 }
 
@@ -1586,8 +1586,8 @@ static hipError_t launch_attention_bf16_d(const Dims& dm, const AttnArgs& a, hip
     hipError_t e = launch_pair_blocks(dm, a.idx, a.k_top, after, &p.pair, stream);
     if (e != hipSuccess) return e;
   }
-  if (p.n_whole == 0) return launch_attention_halves<D>(p, false, grid, stream);
   if (dm.B != kTile) return launch_attention_two_tiles<D>(p, false, grid, stream);
+  if (p.n_whole == 0) return launch_attention_halves<D>(p, false, grid, stream);
   if (D == 64 && four_on_a_cu(dm, a, p)) return launch_attention_four(p, grid, stream);
   hipLaunchKernelGGL((attn_bf16_kernel<D, false, 1>), dim3(grid), dim3(256), list_bytes(p.N), stream, p);
   return hipGetLastError();
